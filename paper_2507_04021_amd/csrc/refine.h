@@ -205,7 +205,7 @@ __device__ int validate_pass(const LaunchArgs &A, uint32_t q, uint32_t r, f3 tx,
 }
 
 // Persistent single-wavefront blocks. A work unit is (key chunk, slice of up
-// to kRefineRxSlice receivers); units are handed out by an atomic counter,
+// to kRefineRxSlice receivers, fewer where units are scarce); units are handed out by an atomic counter,
 // slice-minor so that consecutive units reuse a chunk's key planes.
 //
 // The wavefront deals a unit's (key, receiver) pairs to its lanes in tiles
@@ -271,7 +271,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
     float4 *qpl = avg ? A.spec_ovr + (size_t)blockIdx.x * kRefineQueue * KM * 2 : nullptr;
     const uint32_t n_rx = A.D.n_rx, n_items = A.D.n_items;
     const uint32_t n_chunks = A.chunk_off[n_items];
-    const uint32_t n_slices = (n_rx + kRefineRxSlice - 1) / kRefineRxSlice;
+    // Receivers per unit: kRefineRxSlice keeps the batches of validation passes
+    // full, which is best while there is a unit for every wavefront of the grid;
+    // below that, wavefronts idle while a few walk long chains of passes, so the
+    // slices are halved until every wavefront has a unit or a unit is one
+    // receiver. The sums per (key chunk, receiver) are the same for every slice.
+    // Refinement of a 100k-point office (83 chunks x 17 receivers, 4096
+    // wavefronts) 2.74 -> 0.88 ms; asking for two (four) units per wavefront
+    // slows the 1M-point polarised solve (934 chunks x 64) 3.34 -> 3.42 (4.35).
+    uint32_t slice = kRefineRxSlice;
+    while (slice > 1 && n_chunks * ((n_rx + slice - 1) / slice) < gridDim.x) slice >>= 1;
+    const uint32_t n_slices = (n_rx + slice - 1) / slice;
     const uint32_t n_units = n_chunks * n_slices;
     const bool rec = A.flags & 8;
     uint32_t n_cand = 0, n_valid = 0;
@@ -331,8 +341,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
                     }
                     const Item I = A.items[lo];
                     U[k].c = c;
-                    U[k].r0 = (u % n_slices) * kRefineRxSlice;
-                    U[k].nr = min((uint32_t)kRefineRxSlice, n_rx - U[k].r0);
+                    U[k].r0 = (u % n_slices) * slice;
+                    U[k].nr = min(slice, n_rx - U[k].r0);
                     U[k].q0 = A.key_off[lo] + (c - A.chunk_off[lo]) * kKeyChunk;
                     const uint32_t q1 = min(U[k].q0 + kKeyChunk, A.key_off[lo + 1]);
                     U[k].ne = (q1 - U[k].q0) * U[k].nr;

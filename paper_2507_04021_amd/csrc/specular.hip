@@ -122,8 +122,8 @@ uint32_t refine_cap_k(uint32_t K) {
 
 uint32_t refine_grid(const SolveDims &D) {
     const uint32_t cap = D.width == 8 ? refine_cap_k<8>(D.K) : D.width == 4 ? refine_cap_k<4>(D.K) : refine_cap_k<2>(D.K);
-    const uint32_t units = D.max_key_chunks * ((D.n_rx + kRefineRxSlice - 1) / kRefineRxSlice);
-    return std::max<uint32_t>(1, std::min(cap, units));
+    const uint64_t units = (uint64_t)D.max_key_chunks * D.n_rx;
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cap, units));
 }
 
 // Point-set averaging and the polarised field have kernels of their own, so

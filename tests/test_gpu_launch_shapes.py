@@ -1,0 +1,47 @@
+"""Launch shapes chosen by the sizes of a call: results do not depend on them.
+
+The per-receiver sums are formed in fixed chunks, so a receiver's numbers are
+bitwise the same whichever receivers are solved with it and however the work
+is dealt to the wavefronts.
+"""
+import numpy as np
+import pytest
+
+from paper_2507_04021_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+LOS, SPEC, DIFF = 1, 2, 4
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("a GPU test ran without a visible GPU")
+    import paper_2507_04021_amd as P
+    P.lib()  # raises if the library is not built: no fallback
+    return P
+
+
+@pytest.fixture(scope="module")
+def office(P):
+    sc = scenes.office(seed=2507, target_points=60_000)
+    return P.Scene.from_scene(sc, leaf_size=2, width=4)
+
+
+def _solve(P, scene, rx, rays, K, **kw):
+    r = P.solve(scene, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx, 3.5e9, rays, K=K, flags=LOS | SPEC, **kw)
+    return np.concatenate([t.cpu().numpy().reshape(len(rx), -1) for t in (r.gain, r.h_te, r.h_tm, r.parts)], 1), r
+
+
+@pytest.mark.parametrize("pol", [None, ((1.0, 0.2, -0.3), (0.1, -1.0, 0.4))])
+def test_refinement_slices_do_not_change_a_receiver(P, office, pol):
+    """64 receivers have a refinement unit of 8 receivers for every wavefront; 9 and 1 do not, and get thinner units."""
+    rx = scenes.office_rx()
+    print("[gpu-test] refinement slices", flush=True)
+    full, r = _solve(P, office, rx, 1 << 19, 4, pol=pol)
+    assert r.counter("keys") > 4096 * 8 and r.counter("specular") > 0
+    for take in (slice(0, 9), slice(5, 6), slice(61, 64)):
+        part, _ = _solve(P, office, rx[take], 1 << 19, 4, pol=pol)
+        assert np.array_equal(part, full[take])
