@@ -316,6 +316,7 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.chunk_off = (uint32_t *)at(L.chunk_off);
     A.spec_part = (double *)at(L.spec_part);
     A.spec_res = (p->flags & PCRT_SPECULAR) ? (float4 *)at(L.spec_res) : nullptr;
+    A.spec_hid = (p->flags & PCRT_SPECULAR) ? (int *)at(L.spec_hid) : nullptr;
     A.spec_ovr = ((p->flags & PCRT_SPECULAR) && (p->flags & PCRT_AVERAGE)) ? (float4 *)at(L.spec_ovr) : nullptr;
     A.diff_part = (double *)at(L.diff_part);
     A.los_part = (double *)at(L.los_part);
@@ -394,7 +395,8 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
         L.keylist = b.take(sizeof(uint32_t) * D.max_keys);
         L.spec_part = b.take(sizeof(double) * 5 * (size_t)D.max_key_chunks * D.n_rx);
         L.spec_res = b.take(sizeof(float4) * (size_t)refine_grid(D) * kRefineResPerBlock);
-        if (flags & PCRT_AVERAGE) L.spec_ovr = b.take(sizeof(float4) * 2 * (size_t)refine_grid(D) * kRefineQueue * D.K);
+        L.spec_hid = b.take(sizeof(int) * (size_t)refine_grid(D) * kWave * D.K);
+        if (flags & PCRT_AVERAGE) L.spec_ovr = b.take(sizeof(float4) * 2 * (size_t)refine_grid(D) * kWave * D.K);
         if (rec) {
             const size_t pairs = (size_t)D.rec_keys * D.n_rx;
             L.sp_valid = b.take(pairs);

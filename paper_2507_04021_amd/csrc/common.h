@@ -210,59 +210,6 @@ __device__ __forceinline__ void dps_average(const DevScene &S, f3 o, f3 d, int e
     n = normalize(sn);
 }
 
-// Nearest hit among disks != excl with t in (t_lo, inf), with the tie rule:
-// t* = min t; among hits with t <= t* + eps_tie the smallest (d2, id) wins.
-// Hits within the current window are kept in a short list that is pruned
-// whenever t* shrinks; if the list overflows, a second, exact pass over the
-// final window decides. Returns the disk id or -1; t of the winner.
-struct Cand {
-    float t, d2;
-    int id;
-};
-// Three entries: no bounce of the office overflows them (as with four) and
-// the walks hold fewer registers; one entry sends 1 % of its bounces to the
-// second pass and slows the refinement by 7 %.
-constexpr int kTieList = 3;  // entries of the tie-window candidate list
-
-template <bool kSecond>
-__device__ __forceinline__ void visit_disk(const DevScene &S, int i, f3 o, f3 d, int excl, float t_lo, float eps_tie,
-                                           float &tmin, Cand *c, bool &spill, float t_win, float &best_d2,
-                                           int &best_id, float &best_t) {
-    const float4 dp = ld4(S.disk, (uint32_t)i * 32u);
-    const float4 dn = ld4(S.disk, (uint32_t)i * 32u + 16u);
-    const int id = __float_as_int(dp.w);
-    if (id == excl) return;
-    float t, d2;
-    if (!disk_hit(o, d, xyz(dp), xyz(dn), S.r2, t, d2)) return;
-    if (!(t > t_lo)) return;
-    if (kSecond) {
-        if (t <= t_win && (d2 < best_d2 || (d2 == best_d2 && id < best_id))) {
-            best_d2 = d2;
-            best_id = id;
-            best_t = t;
-        }
-        return;
-    }
-    if (t > tmin + eps_tie) return;
-    if (t < tmin) {
-        tmin = t;
-        const float lim = tmin + eps_tie;
-#pragma unroll
-        for (int k = 0; k < kTieList; ++k)
-            if (c[k].id >= 0 && c[k].t > lim) c[k].id = -1;
-    }
-    bool placed = false;
-#pragma unroll
-    for (int k = 0; k < kTieList; ++k)
-        if (!placed && c[k].id < 0) {
-            c[k].t = t;
-            c[k].d2 = d2;
-            c[k].id = id;
-            placed = true;
-        }
-    if (!placed) spill = true;
-}
-
 // Children of a wide node (8W floats: lo x[W], lo y[W], lo z[W], hi x[W],
 // hi y[W], hi z[W], refs[W], pad): entry distance per child (INFINITY for a
 // child the segment misses) and its reference.
@@ -467,81 +414,6 @@ __device__ __forceinline__ bool wide_step_any(const DevScene &S, int &ref, int &
     }
     ref = nref;
     return true;
-}
-
-template <int W, bool kSecond>
-__device__ __forceinline__ void traverse_closest(const DevScene &S, f3 o, f3 d, f3 inv, int excl, float t_lo,
-                                                 float eps_tie, Stack &stk, float &tmin, Cand *c, bool &spill,
-                                                 float t_win, float &best_d2, int &best_id, float &best_t) {
-    const f3 oi = times(o, inv);
-    int ref = S.root;
-    int sp = 0;
-    for (;;) {
-        if (ref >= 0) {
-            stk.visit();
-            const float tc = kSecond ? t_win : tmin + eps_tie;
-            if constexpr (W > 2) {
-                if (wide_step<W>(S, ref, sp, inv, oi, t_lo, tc, stk)) continue;
-            } else {
-                const uint32_t nb = (uint32_t)ref * 64u;
-                const float4 a = ld4(S.node, nb), b = ld4(S.node, nb + 16u), e = ld4(S.node, nb + 32u),
-                             r = ld4(S.node, nb + 48u);
-                float n0, n1;
-                const bool h0 = box_hit(a.x, a.y, a.z, a.w, b.x, b.y, inv, oi, t_lo, tc, n0);
-                const bool h1 = box_hit(b.z, b.w, e.x, e.y, e.z, e.w, inv, oi, t_lo, tc, n1);
-                const int r0 = __float_as_int(r.x), r1 = __float_as_int(r.y);
-                if (h0 && h1) {
-                    const bool f0 = n0 <= n1;
-                    stk.put(sp++, f0 ? r1 : r0);
-                    ref = f0 ? r0 : r1;
-                    continue;
-                }
-                if (h0) { ref = r0; continue; }
-                if (h1) { ref = r1; continue; }
-            }
-        } else {
-            const int v = -1 - ref;
-            const int first = v >> 3, cnt = (v & 7) + 1;
-            stk.test(cnt);
-            for (int i = 0; i < cnt; ++i)
-                visit_disk<kSecond>(S, first + i, o, d, excl, t_lo, eps_tie, tmin, c, spill, t_win, best_d2, best_id,
-                                    best_t);
-        }
-        if (sp == 0) break;
-        ref = stk.get(--sp);
-    }
-}
-
-template <int W>
-__device__ __forceinline__ int closest_hit(const DevScene &S, f3 o, f3 d, int excl, float t_lo, float eps_tie,
-                                           Stack &stk, float &t_out, bool &spilled) {
-    f3 inv = safe_inv(d);
-    float tmin = INFINITY;
-    Cand c[kTieList];
-#pragma unroll
-    for (int k = 0; k < kTieList; ++k) c[k] = {INFINITY, INFINITY, -1};
-    bool spill = false;
-    float bd2 = INFINITY, bt = INFINITY;
-    int bid = 0x7fffffff;
-    traverse_closest<W, false>(S, o, d, inv, excl, t_lo, eps_tie, stk, tmin, c, spill, 0.f, bd2, bid, bt);
-    spilled = spill;
-    if (!(tmin < INFINITY)) return -1;
-    if (spill) {
-        float dummy = tmin;
-        traverse_closest<W, true>(S, o, d, inv, excl, t_lo, eps_tie, stk, dummy, c, spill, tmin + eps_tie, bd2,
-                                  bid, bt);
-        t_out = bt;
-        return bid;
-    }
-#pragma unroll
-    for (int k = 0; k < kTieList; ++k)
-        if (c[k].id >= 0 && (c[k].d2 < bd2 || (c[k].d2 == bd2 && c[k].id < bid))) {
-            bd2 = c[k].d2;
-            bid = c[k].id;
-            bt = c[k].t;
-        }
-    t_out = bt;
-    return bid;
 }
 
 // Any-hit step at a node of either layout: true if a child was entered (ref

@@ -127,13 +127,13 @@ constexpr uint32_t kSlotChunk = 512;    // slots per label-gradient reduction ch
 constexpr uint32_t kRefineRxSlice = 8;
 // Result slots per refinement block: two open units of kKeyChunk keys x kRefineRxSlice receivers.
 constexpr uint32_t kRefineResPerBlock = 2 * kKeyChunk * kRefineRxSlice;
-constexpr uint32_t kRefineQueue = 128;  // refinement ring of queued candidates (at most 127 are live)
+constexpr uint32_t kRefineQueue = 128;  // refinement ring of queued candidates (at most 127 are queued)
 constexpr uint32_t kMaxGradLabels = 64;   // label-gradient LDS: 64 lanes x 64 labels x 3 doubles
 
 struct SolveLayout {
     size_t items, counters, work, rec_id, rec_xl, rec_cs, rec_coef, rec_slot, hkey, hrep, scan, scan_blk, keylist,
         key_off, chunk_off, spec_part, diff_part, los_part, sp_valid, sp_len, sp_amp, sp_hit, sp_cs, dvis, spill,
-        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr,
+        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid,
         rec_dslot, dhkey, dhrep, dkeylist, dkey_off, dchunk_off, dcnt;
     size_t total;
 };
@@ -183,7 +183,8 @@ struct LaunchArgs {
     uint32_t *chunk_off; // [n_items + 1]
     double *spec_part;
     float4 *spec_res;      // refinement: per block, path amplitudes of its current unit's pairs
-    float4 *spec_ovr;      // refinement with point-set averaging: per block and ring position, replaced planes
+    int *spec_hid;         // refinement: per block, interaction and lane, the validated disk of the lane's candidate
+    float4 *spec_ovr;      // refinement with point-set averaging: per lane and interaction, the replaced plane
     double *diff_part;
     double *los_part;
     uint8_t *dvis;

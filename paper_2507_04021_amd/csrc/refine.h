@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "walk.h"
 
 namespace pcrt {
 
@@ -47,41 +48,94 @@ __device__ __forceinline__ bool refine_planes(int k, f3 tx, f3 rx, const f3 *pp,
     return true;
 }
 
+// The same minimiser for the walks: only the points x_from and x_(from+1) are
+// kept (from < k), the others stream through the tests, so the lanes' walk
+// state stays in registers beside it.
+template <int KM>
+__device__ __forceinline__ bool refine_segment(int k, f3 tx, f3 rx, const f3 *pp, const f3 *pn, float eps_self,
+                                               int from, f3 &a, f3 &b) {
+    f3 img[KM + 1];
+    img[0] = tx;
+#pragma unroll
+    for (int m = 1; m <= KM; ++m)
+        if (m <= k) img[m] = img[m - 1] - (2.f * dot(img[m - 1] - pp[m - 1], pn[m - 1])) * pn[m - 1];
+    f3 cur = rx, nb = rx;  // x_(m+1), x_(m+2), the receiver beyond x_k
+    a = tx;
+    b = tx;
+    bool ok = true;
+#pragma unroll
+    for (int m = KM; m >= 0; --m) {
+        if (m > k) continue;
+        f3 xm = tx;
+        if (m > 0) {
+            f3 seg = img[m] - cur;
+            float den = dot(seg, pn[m - 1]);
+            float s = dot(pp[m - 1] - cur, pn[m - 1]) / den;
+            ok = ok && den != 0.f && s > 0.f && s < 1.f;
+            xm = cur + s * seg;
+        }
+        if (m < KM && m < k) {
+            float da = dot(xm - pp[m], pn[m]);
+            float db = dot(nb - pp[m], pn[m]);
+            ok = ok && da * db > 0.f && fabsf(da) > eps_self && fabsf(db) > eps_self;
+        }
+        if (m == from) a = xm;
+        if (m == from + 1) b = xm;
+        nb = cur;
+        cur = xm;
+    }
+    return ok;
+}
+
 struct PairOut {
     bool valid;
     float len;
     c32 te, tm;
 };
 
-// The representative's interaction planes of key q: its first k hit disks'
-// planes, or with point-set averaging its first k averaged interactions
-// (point and normal from the records).
+// The representative's interaction planes of a key, rec being the record of its
+// last interaction: its first k hit disks' planes, or with point-set averaging
+// its first k averaged interactions (point and normal from the records).
 template <int KM>
 struct KeyPlanes {
     f3 pp[KM], pn[KM];
-    uint32_t ks[KM];  // surface labels
     int k;
 };
 
 template <int KM, bool AVG>
-__device__ __forceinline__ void load_planes(const LaunchArgs &A, uint32_t q, KeyPlanes<KM> &kp) {
+__device__ __forceinline__ void load_planes(const LaunchArgs &A, uint32_t rec, KeyPlanes<KM> &kp) {
     const uint32_t K = A.D.K;
-    const uint32_t rec = A.keylist[q];
     const uint32_t g = rec / K;
     kp.k = (int)(rec % K) + 1;
 #pragma unroll
     for (int m = 0; m < KM; ++m)
         if (m < kp.k) {
             const size_t ri = (size_t)g * K + m;
-            const int id = A.rb.id[ri];
-            const float4 p4 = A.S.pos[id];
-            kp.ks[m] = __float_as_uint(p4.w);
             if (AVG) {
                 kp.pp[m] = xyz(A.rb.xl[ri]);
                 kp.pn[m] = xyz(A.rb.nk[ri]);
             } else {
-                kp.pp[m] = xyz(p4);
+                const int id = A.rb.id[ri];
+                kp.pp[m] = xyz(A.S.pos[id]);
                 kp.pn[m] = xyz(A.S.nrm[id]);
+            }
+        }
+}
+
+// The same with the planes that replaced some of them: ovr[j * kWave] is the
+// disk whose plane replaced plane j, -1 if none (its averaged point and normal
+// are then pl[2j], pl[2j + 1]).
+template <int KM, bool AVG>
+__device__ __forceinline__ void cur_planes(const LaunchArgs &A, uint32_t rec, const int *ovr, const float4 *pl,
+                                           KeyPlanes<KM> &kp) {
+    load_planes<KM, AVG>(A, rec, kp);
+#pragma unroll
+    for (int j = 0; j < KM; ++j)
+        if (j < kp.k) {
+            const int od = ovr[j * kWave];
+            if (od >= 0) {
+                kp.pp[j] = AVG ? xyz(pl[2 * j]) : xyz(A.S.pos[od]);
+                kp.pn[j] = AVG ? xyz(pl[2 * j + 1]) : xyz(A.S.nrm[od]);
             }
         }
 }
@@ -90,71 +144,17 @@ __device__ __forceinline__ f3 rx_point(const LaunchArgs &A, uint32_t r) {
     return mk(A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]);
 }
 
-// One validation pass of a (key, receiver) candidate on its current planes
-// (the key's disk planes, some replaced after earlier passes): a ray from each
-// image point to the next must hit a disk of the expected surface, close in
-// angle (t_a) and plane distance (t_d). The first interaction that fails
-// those two tests asks for another pass with that plane replaced by the hit
-// disk's (kPassRetry: slot, disk), unless retries already equals kappa; any
-// other failure ends the candidate. If every interaction holds, the last
-// point must see the receiver, and the path's field is evaluated. With
-// point-set averaging the validation hit is averaged over its set first
-// (Sec. II-C): its point and normal are tested, and a retry takes them as the
-// new plane (rp, rn).
-enum { kPassDone = 0, kPassRetry = 1 };
-
-template <int KM, int W, bool AVG, bool POL>
-__device__ int validate_pass(const LaunchArgs &A, uint32_t q, uint32_t r, f3 tx, const KeyPlanes<KM> &kp,
-                             int retries, Stack &stk, PairOut &po, int &slot, int &disk, f3 &rp, f3 &rn) {
-    po.valid = false;
+// The field of a validated path: points x[0] = TX, x[1..k], disks hid on planes
+// kp; the last point sees the receiver.
+template <int KM, bool POL>
+__device__ __forceinline__ void path_field(const LaunchArgs &A, uint32_t q, uint32_t r, f3 rx, const f3 *x,
+                                           const int *hid, const KeyPlanes<KM> &kp, PairOut &po) {
     const uint32_t K = A.D.K;
     const int k = kp.k;
-    const f3 rx = rx_point(A, r);
-    f3 x[KM + 1];
-    int hid[KM];
-    if (!refine_planes<KM>(k, tx, rx, kp.pp, kp.pn, A.thr.eps_self, x)) return kPassDone;
-    int prev = -1;
-    bool retry = false, fail = false;
-#pragma unroll
-    for (int m = 1; m <= KM; ++m) {
-        if (m > k || retry || fail) continue;
-        f3 u = normalize(x[m] - x[m - 1]);
-        float t;
-        bool sp;
-        int h = closest_hit<W>(A.S, x[m - 1], u, prev, A.thr.eps_self, A.thr.eps_tie, stk, t, sp);
-        if (h < 0) { fail = true; continue; }
-        float4 hp = A.S.pos[h];
-        if (__float_as_uint(hp.w) != kp.ks[m - 1]) { fail = true; continue; }
-        f3 hn = xyz(A.S.nrm[h]);
-        if (AVG) dps_average(A.S, x[m - 1], u, prev, A.thr.eps_self, A.thr.lambda_d, h, t, hn);
-        f3 qh = x[m - 1] + t * u;
-        bool ang_ok = fabsf(dot(hn, kp.pn[m - 1])) >= A.thr.cos_ta;
-        bool dist_ok = fabsf(dot(qh - kp.pp[m - 1], kp.pn[m - 1])) <= A.thr.t_d;
-        if (!(ang_ok && dist_ok)) {
-            if (retries >= A.thr.kappa) { fail = true; continue; }
-            slot = m - 1;
-            disk = h;
-            if (AVG) {
-                rp = qh;
-                rn = hn;
-            }
-            retry = true;
-            continue;
-        }
-        hid[m - 1] = h;
-        prev = h;
-    }
-    if (fail) return kPassDone;
-    if (retry) return kPassRetry;
     f3 xk = x[1];
-    int hk = hid[0];
 #pragma unroll
     for (int m = 1; m <= KM; ++m)
-        if (m == k) {
-            xk = x[m];
-            hk = hid[m - 1];
-        }
-    if (occluded<W>(A.S, xk, rx, hk, A.thr.eps_self, stk)) return kPassDone;
+        if (m == k) xk = x[m];
     float L = 0.f;
     c32 pte = {1.f, 0.f}, ptm = {1.f, 0.f};
     float csv[KM];
@@ -201,41 +201,57 @@ __device__ int validate_pass(const LaunchArgs &A, uint32_t q, uint32_t r, f3 tx,
                 A.sb.cs[p * K + m] = csv[m];
             }
     }
-    return kPassDone;
 }
 
 // Persistent single-wavefront blocks. A work unit is (key chunk, slice of up
-// to kRefineRxSlice receivers, fewer where units are scarce); units are handed out by an atomic counter,
-// slice-minor so that consecutive units reuse a chunk's key planes.
+// to kRefineRxSlice receivers, fewer where units are scarce); units are handed
+// out by an atomic counter, slice-minor so that consecutive units reuse a
+// chunk's key planes.
 //
 // The wavefront deals a unit's (key, receiver) pairs to its lanes in tiles
 // of 64 and solves the image method for each pair (cheap, no traversal);
-// pairs with a solution join a queue in LDS. Whenever 64 are queued, or no
-// tile is left to run, every lane takes one queued candidate through ONE
-// validation pass. A pass that asks for a plane replacement puts the
-// candidate back at the end of the queue with that replacement recorded
-// (the disk whose plane it takes), so a candidate that needs many passes
-// holds one lane for one pass at a time. Up to two units are open at once:
-// while the last candidates of one unit still cycle through the queue, the
-// tiles of the next unit refill it, so the batches stay full.
+// pairs with a solution join a queue in LDS, with the direction of their
+// first segment. An idle lane takes a queued candidate and validates it: a ray
+// from each image point to the next must hit a disk of the expected surface,
+// close in angle (t_a) and plane distance (t_d). The first interaction that
+// fails those two tests replaces its plane by the hit disk's and starts
+// again from the transmitter with the new image points (kappa times at most);
+// any other failure ends the candidate. If every interaction holds, the last
+// point must see the receiver, and the path's field is evaluated. With
+// point-set averaging the validation hit is averaged over its set first
+// (Sec. II-C): its point and normal are tested, and become the new plane.
+//
+// What bounds it: the closest-hit walks (a few short ones per candidate, most
+// of them first segments that end in a plane replacement), that is L2
+// latency and the lanes that wait for longer walks. So the walks are those of
+// the bounce loop: resumable, leaves parked, the wavefront steps them until at
+// most half of its busy lanes still walk, and the lanes whose walks ended
+// then decide together (plane replacement, next segment or end) and walk on
+// or take the next candidate. A lane keeps its candidate until it ends; what
+// it needs besides the walk (key planes, replaced planes, image points) is
+// loaded and computed again at each decision, which costs less than keeping
+// it in registers through the walks.
 //
 // Sums: a path's amplitudes go to this block's result slots, indexed by the
 // open unit and the pair within it, with a bit in LDS. When a unit is done,
 // lane r adds the paths of receiver r in increasing key order and writes the
 // unit's partial sum of receiver r0 + r for chunk c. The result does not
-// depend on timing or on the order in which passes ran.
+// depend on timing or on the order in which candidates ended. Up to two units
+// are open at once: while the last candidates of one end, the tiles of the
+// next feed the idle lanes.
+//
+// Measured on the 1M-point office (2^20 rays, K = 5, 64 receivers; one pass at
+// a time for a whole batch before): 4.19 -> 3.06 ms; on its polarised solve
+// (2^18 rays) 3.32 -> 2.15, with averaging 1.74 -> 1.32. Lanes decide once at
+// most 1/2, 1/4 or 1/8 of the busy ones still walk: 3.30, 3.06, 3.05 ms (1.54,
+// 1.37, 1.32 with averaging): a decision is a chain of dependent loads, worth
+// waiting for company. When nothing is left to feed idle lanes, all busy lanes
+// are waited for (a solve of 35 candidates 80 -> 66 us).
 constexpr int kRefineOpen = 2;          // units open at once per wavefront
-
-template <int KM>
-struct QEntry {
-    uint32_t e;   // pair within its unit: key * nr + receiver
-    int slot;     // open-unit slot
-    int retries;  // passes so far that ended in a plane replacement
-    int ovr[KM];  // per interaction: the disk whose plane replaced the key's, -1 if none
-};
+constexpr int kRefineRefillShift = 3;   // lanes decide once at most busy / 8 still walk
 
 struct RefUnit {  // an open unit (wavefront-uniform)
-    uint32_t c, r0, nr, q0, ne, t, pending;  // pending: candidates queued or in a pass
+    uint32_t c, r0, nr, q0, ne, t, pending;  // pending: candidates queued or held by a lane
     f3 tx;
     bool open;
 };
@@ -248,49 +264,165 @@ __device__ __forceinline__ void block_sync_global() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Occupancy: four wavefronts per SIMD up to K = 5 (a 128-register budget,
-// with a few spills): on the office two gave 6.1 ms, three 4.8, four 4.7.
 // POL: the polarised field (its own instances, so that the scalar ones keep
-// their register allocation).
+// their register allocation). Three wavefronts per SIMD up to K = 5 (168
+// registers: none spilled up to K = 4, about 100 at K = 5): two gave 3.7 ms on
+// the office (no spills), four 3.2 (247 spilled), three 3.06.
 template <int KM, int W, bool AVG, bool POL>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ? 4 : 2, 8))) void k_refine(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ? 3 : 2, 8))) void k_refine(
     LaunchArgs A) {
     constexpr uint32_t kUnitPairs = kKeyChunk * kRefineRxSlice;
     static_assert(kRefineOpen == 2 && kRefineOpen * kUnitPairs == kRefineResPerBlock, "two open units");
+    static_assert(kRefineOpen * kUnitPairs <= 0x10000, "a queue entry names its pair in 16 bits");
     __shared__ int lds_stack[kStackLds * kWave];
-    __shared__ QEntry<KM> queue[kRefineQueue];
+    __shared__ uint16_t queue[kRefineQueue];       // open-unit slot x kUnitPairs + pair
+    __shared__ uint32_t queue_rec[kRefineQueue];   // record of its key's last interaction
+    __shared__ float queue_u[3][kRefineQueue];     // direction of the candidate's first segment
+    __shared__ int ovr[KM][kWave];                 // per lane and interaction: the disk whose plane replaced the key's
+    __shared__ float tie_list[kTieRows * kWave];
     __shared__ uint32_t vbits[kRefineOpen][kUnitPairs / 32];  // pairs of an open unit that are paths
     const int lane = threadIdx.x;
-    const uint64_t below = (1ull << lane) - 1;
     const uint32_t glane = blockIdx.x * kWave + lane;
     Stack stk{lds_stack + lane, A.S.spill + glane, A.S.spill_lanes};
     float4 *res = A.spec_res + (size_t)blockIdx.x * kRefineOpen * kUnitPairs;
-    // point-set averaging: the current planes of a queued candidate with
-    // retries sit at its ring position, (point, normal) per interaction
-    constexpr bool avg = AVG;
-    float4 *qpl = avg ? A.spec_ovr + (size_t)blockIdx.x * kRefineQueue * KM * 2 : nullptr;
+    // the validated disks of this lane's candidate, interaction m at hid_g[m * kWave]
+    int *hid_g = A.spec_hid + (size_t)blockIdx.x * kWave * KM + lane;
+    // point-set averaging: the replaced planes of this lane's candidate, (point, normal) per interaction
+    float4 *pl_g = AVG ? A.spec_ovr + (size_t)glane * KM * 2 : nullptr;
     const uint32_t n_rx = A.D.n_rx, n_items = A.D.n_items;
     const uint32_t n_chunks = A.chunk_off[n_items];
-    // Receivers per unit: kRefineRxSlice keeps the batches of validation passes
-    // full, which is best while there is a unit for every wavefront of the grid;
-    // below that, wavefronts idle while a few walk long chains of passes, so the
-    // slices are halved until every wavefront has a unit or a unit is one
-    // receiver. The sums per (key chunk, receiver) are the same for every slice.
-    // Refinement of a 100k-point office (83 chunks x 17 receivers, 4096
-    // wavefronts) 2.74 -> 0.88 ms; asking for two (four) units per wavefront
-    // slows the 1M-point polarised solve (934 chunks x 64) 3.34 -> 3.42 (4.35).
+    // Receivers per unit: kRefineRxSlice keeps the lanes fed, which is best while
+    // there is a unit for every wavefront of the grid; below that, wavefronts
+    // idle while a few work through long chains, so the slices are halved until
+    // every wavefront has a unit or a unit is one receiver. The sums per (key
+    // chunk, receiver) are the same for every slice.
     uint32_t slice = kRefineRxSlice;
     while (slice > 1 && n_chunks * ((n_rx + slice - 1) / slice) < gridDim.x) slice >>= 1;
     const uint32_t n_slices = (n_rx + slice - 1) / slice;
     const uint32_t n_units = n_chunks * n_slices;
     const bool rec = A.flags & 8;
+    const float eps_self = A.thr.eps_self, eps_tie = A.thr.eps_tie;
     uint32_t n_cand = 0, n_valid = 0;
     RefUnit U[kRefineOpen];
 #pragma unroll
     for (int k = 0; k < kRefineOpen; ++k) U[k] = RefUnit{0, 0, 0, 0, 0, 0, 0, mk(0.f, 0.f, 0.f), false};
     bool exhausted = false;       // the unit counter has run out
     uint32_t head = 0, tail = 0;  // queue ring positions (wavefront-uniform)
+    // this lane's candidate: entry of the queue, passes that ended in a plane
+    // replacement, segment being walked (from image point seg - 1 to seg)
+    bool busy = false, walking = false;
+    uint32_t ent = 0, krec = 0;
+    int retries = 0, seg = 1, excl = -1;
+    f3 o = mk(0.f, 0.f, 0.f), d = mk(0.f, 0.f, 1.f);
+    const Ties ties{tie_list + lane};
+    Walk w;
+    walk_start(w, ties, A.S.root, o, d);
+    w.ref = kNoRef;
     for (;;) {
+        // lanes whose walks ended: second pass, plane replacement, next segment or end
+        bool ended = false;
+        if (busy && !walking) {
+            if (walk_second_pass(w, ties, A.S.root, eps_tie)) {
+                walking = true;
+            } else {
+                const bool s1 = ent >= kUnitPairs;
+                const uint32_t e = ent % kUnitPairs;
+                const uint32_t nr = s1 ? U[1].nr : U[0].nr;
+                const uint32_t q = (s1 ? U[1].q0 : U[0].q0) + e / nr;
+                const uint32_t r = (s1 ? U[1].r0 : U[0].r0) + e % nr;
+                // the plane and label of the interaction just walked to
+                const int od = ovr[seg - 1][lane];
+                const size_t ri = (size_t)(krec / A.D.K) * A.D.K + seg - 1;
+                const int id0 = A.rb.id[ri];
+                const int idp = od >= 0 ? od : id0;
+                f3 pp, pn;
+                if (AVG) {
+                    pp = od >= 0 ? xyz(pl_g[2 * (seg - 1)]) : xyz(A.rb.xl[ri]);
+                    pn = od >= 0 ? xyz(pl_g[2 * (seg - 1) + 1]) : xyz(A.rb.nk[ri]);
+                } else {
+                    pp = xyz(A.S.pos[idp]);
+                    pn = xyz(A.S.nrm[idp]);
+                }
+                float t;
+                const int h = walk_hit(w, ties, t);
+                const float4 hp = A.S.pos[h < 0 ? 0 : h];
+                // (a replaced plane's disk lies on the same surface)
+                bool good = h >= 0 && __float_as_uint(hp.w) == __float_as_uint(A.S.pos[id0].w), again = false;
+                if (good) {
+                    f3 hn = xyz(A.S.nrm[h]);
+                    if (AVG) dps_average(A.S, o, d, excl, eps_self, A.thr.lambda_d, h, t, hn);
+                    const f3 qh = o + t * d;
+                    const bool ang_ok = fabsf(dot(hn, pn)) >= A.thr.cos_ta;
+                    const bool dist_ok = fabsf(dot(qh - pp, pn)) <= A.thr.t_d;
+                    if (!(ang_ok && dist_ok)) {  // start again on the hit disk's plane
+                        again = retries < A.thr.kappa;
+                        good = again;
+                        retries += 1;
+                        if (again) {
+                            ovr[seg - 1][lane] = h;
+                            if (AVG) {
+                                pl_g[2 * (seg - 1)] = make_float4(qh.x, qh.y, qh.z, 0.f);
+                                pl_g[2 * (seg - 1) + 1] = make_float4(hn.x, hn.y, hn.z, 0.f);
+                            }
+                        }
+                    }
+                }
+                PairOut po;
+                po.valid = false;
+                ended = true;
+                if (good) {
+                    if (!again) hid_g[(seg - 1) * kWave] = h;
+                    excl = again ? -1 : h;
+                    const int from = again ? 0 : seg;  // the next segment starts at image point from
+                    KeyPlanes<KM> kp;
+                    cur_planes<KM, AVG>(A, krec, &ovr[0][lane], pl_g, kp);
+                    if (from < kp.k) {
+                        f3 a, b;
+                        if (refine_segment<KM>(kp.k, s1 ? U[1].tx : U[0].tx, rx_point(A, r), kp.pp, kp.pn, eps_self,
+                                               from, a, b)) {
+                            seg = from + 1;
+                            o = a;
+                            d = normalize(b - a);
+                            walk_start(w, ties, A.S.root, o, d);
+                            walking = true;
+                            ended = false;
+                        }
+                    } else {  // every interaction holds: the last point must see the receiver
+                        const f3 rx = rx_point(A, r);
+                        f3 a, xk;
+                        (void)refine_segment<KM>(kp.k, s1 ? U[1].tx : U[0].tx, rx, kp.pp, kp.pn, eps_self, kp.k - 1, a,
+                                                 xk);
+                        if (!occluded<W>(A.S, xk, rx, h, eps_self, stk)) {
+                            __asm__ volatile("" ::: "memory");  // planes are loaded again, not kept through the walk
+                            cur_planes<KM, AVG>(A, krec, &ovr[0][lane], pl_g, kp);
+                            f3 x[KM + 1];
+                            (void)refine_planes<KM>(kp.k, s1 ? U[1].tx : U[0].tx, rx, kp.pp, kp.pn, eps_self, x);
+                            int hid[KM];
+#pragma unroll
+                            for (int m = 0; m < KM; ++m) hid[m] = m < kp.k ? hid_g[m * kWave] : 0;
+                            path_field<KM, POL>(A, q, r, rx, x, hid, kp, po);
+                        }
+                    }
+                }
+                if (ended) {
+                    if (rec && q < A.D.rec_keys) {
+                        const size_t p = (size_t)q * n_rx + r;
+                        A.sb.valid[p] = po.valid;
+                        A.sb.len[p] = po.valid ? po.len : 0.f;
+                        A.sb.amp[p] = po.valid ? make_float4(po.te.re, po.te.im, po.tm.re, po.tm.im)
+                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+                    if (po.valid) {
+                        ++n_valid;
+                        res[ent] = make_float4(po.te.re, po.te.im, po.tm.re, po.tm.im);
+                        atomicOr(&vbits[s1 ? 1 : 0][e >> 5], 1u << (e & 31));
+                    }
+                    busy = false;
+                }
+            }
+        }
+        U[0].pending -= (uint32_t)__popcll(__ballot(ended && ent < kUnitPairs));
+        U[1].pending -= (uint32_t)__popcll(__ballot(ended && ent >= kUnitPairs));
         // close the units whose tiles are done and whose candidates have all ended
 #pragma unroll
         for (int k = 0; k < kRefineOpen; ++k) {
@@ -308,15 +440,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
                         acc[3] += mr;
                         acc[4] += mi;
                     }
-                double *o = A.spec_part + ((size_t)U[k].c * n_rx + U[k].r0 + lane) * 5;
-                for (int a = 0; a < 5; ++a) o[a] = acc[a];
+                double *out = A.spec_part + ((size_t)U[k].c * n_rx + U[k].r0 + lane) * 5;
+                for (int a = 0; a < 5; ++a) out[a] = acc[a];
             }
             block_sync_global();  // sums read before the slot is reused
             U[k].open = false;
         }
-        const uint32_t live = tail - head;
-        if (live < (uint32_t)kWave) {
-            // image-test tile of an open unit with tiles left, else of a newly opened one
+        // feed the idle lanes: image-test tiles of an open unit, else of a newly opened one
+        const uint64_t idle = __ballot(!busy);
+        const uint32_t n_idle = (uint32_t)__popcll(idle);
+        while (tail - head < n_idle) {
             int s = -1;
 #pragma unroll
             for (int k = 0; k < kRefineOpen; ++k)
@@ -324,13 +457,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
             if (s < 0 && !exhausted) {
 #pragma unroll
                 for (int k = 0; k < kRefineOpen; ++k) {
-                    if (s >= 0 || U[k].open) continue;
+                    if (s >= 0 || U[k].open || exhausted) continue;
                     uint32_t u = 0;
                     if (lane == 0) u = atomicAdd(&A.work[1], 1u);
                     u = __builtin_amdgcn_readfirstlane(u);
                     if (u >= n_units) {
                         exhausted = true;
-                        break;
+                        continue;
                     }
                     const uint32_t c = u / n_slices;
                     int lo = 0, hi = (int)n_items - 1;  // item of this chunk
@@ -355,133 +488,80 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
                     s = k;
                 }
             }
-            auto tile = [&](RefUnit &R, int slot) {
-                const uint32_t e = R.t * kWave + lane;
-                bool cand = false;
-                if (e < R.ne) {
-                    const uint32_t q = R.q0 + e / R.nr, r = R.r0 + e % R.nr;
-                    KeyPlanes<KM> kp;
-                    load_planes<KM, AVG>(A, q, kp);
-                    f3 x[KM + 1];
-                    cand = refine_planes<KM>(kp.k, R.tx, rx_point(A, r), kp.pp, kp.pn, A.thr.eps_self, x);
-                    // launch at the reception points: only where the receiver sees the reception
-                    // point of the set the representative ray ends in (the visibility matrix)
-                    if (cand && A.dps_vis)
-                        cand = A.dps_vis[(size_t)r * A.S.n_sets + A.S.dps_of[A.rb.id[A.keylist[q]]]] != 0;
-                    if (rec) {
-                        if (q >= A.D.rec_keys) {
-                            atomicOr((unsigned long long *)&A.counters[6], 4ull);  // tape capacity exceeded
-                        } else if (!cand) {
-                            const size_t p = (size_t)q * n_rx + r;
-                            A.sb.valid[p] = 0;
-                            A.sb.len[p] = 0.f;
-                            A.sb.amp[p] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        }
+            if (s < 0) break;
+            const bool t1 = s == 1;
+            const uint32_t t0 = t1 ? U[1].t : U[0].t, ne = t1 ? U[1].ne : U[0].ne, nr = t1 ? U[1].nr : U[0].nr;
+            const uint32_t e = t0 * kWave + lane;
+            bool cand = false;
+            uint32_t qrec = 0;
+            f3 u = mk(0.f, 0.f, 1.f);
+            if (e < ne) {
+                const uint32_t q = (t1 ? U[1].q0 : U[0].q0) + e / nr, r = (t1 ? U[1].r0 : U[0].r0) + e % nr;
+                KeyPlanes<KM> kp;
+                qrec = A.keylist[q];
+                load_planes<KM, AVG>(A, qrec, kp);
+                f3 a, b;
+                cand = refine_segment<KM>(kp.k, t1 ? U[1].tx : U[0].tx, rx_point(A, r), kp.pp, kp.pn, eps_self, 0, a, b);
+                // launch at the reception points: only where the receiver sees the reception
+                // point of the set the representative ray ends in (the visibility matrix)
+                if (cand && A.dps_vis)
+                    cand = A.dps_vis[(size_t)r * A.S.n_sets + A.S.dps_of[A.rb.id[qrec]]] != 0;
+                if (cand) u = normalize(b - a);
+                if (rec) {
+                    if (q >= A.D.rec_keys) {
+                        atomicOr((unsigned long long *)&A.counters[6], 4ull);  // tape capacity exceeded
+                    } else if (!cand) {
+                        const size_t p = (size_t)q * n_rx + r;
+                        A.sb.valid[p] = 0;
+                        A.sb.len[p] = 0.f;
+                        A.sb.amp[p] = make_float4(0.f, 0.f, 0.f, 0.f);
                     }
                 }
-                n_cand += cand;
-                const uint64_t m = __ballot(cand);
-                if (cand) {
-                    QEntry<KM> &qe = queue[(tail + (uint32_t)__popcll(m & below)) % kRefineQueue];
-                    qe.e = e;
-                    qe.slot = slot;
-                    qe.retries = 0;
-#pragma unroll
-                    for (int j = 0; j < KM; ++j) qe.ovr[j] = -1;
-                }
-                tail += (uint32_t)__popcll(m);
-                R.pending += (uint32_t)__popcll(m);
-                ++R.t;
-                wave_sync();
-            };
-            if (s == 0) {
-                tile(U[0], 0);
-                continue;
             }
-            if (s == 1) {
-                tile(U[1], 1);
-                continue;
+            n_cand += cand;
+            const uint64_t m = __ballot(cand);
+            if (cand) {
+                const uint32_t at = (tail + mbcnt(m)) % kRefineQueue;
+                queue[at] = (uint16_t)(s * kUnitPairs + e);
+                queue_rec[at] = qrec;
+                queue_u[0][at] = u.x;
+                queue_u[1][at] = u.y;
+                queue_u[2][at] = u.z;
             }
+            const uint32_t n_new = (uint32_t)__popcll(m);
+            tail += n_new;
+            U[0].pending += t1 ? 0u : n_new;
+            U[1].pending += t1 ? n_new : 0u;
+            U[0].t += t1 ? 0u : 1u;
+            U[1].t += t1 ? 1u : 0u;
+            wave_sync();
         }
-        if (live == 0) break;  // no tile to run, nothing queued, every unit closed
-        // one validation pass for up to 64 queued candidates
-        const uint32_t nb = min(live, (uint32_t)kWave);
-        const bool have = (uint32_t)lane < nb;
-        QEntry<KM> me;
-        const uint32_t at = (head + lane) % kRefineQueue;
-        if (have) me = queue[at];
-        head += nb;
+        const uint32_t avail = min(tail - head, n_idle);
+        if (!busy && mbcnt(idle) < avail) {
+            const uint32_t at = (head + mbcnt(idle)) % kRefineQueue;
+            ent = queue[at];
+            krec = queue_rec[at];
+            retries = 0;
+            seg = 1;
+            excl = -1;
+#pragma unroll
+            for (int j = 0; j < KM; ++j) ovr[j][lane] = -1;
+            o = ent >= kUnitPairs ? U[1].tx : U[0].tx;
+            d = mk(queue_u[0][at], queue_u[1][at], queue_u[2][at]);
+            walk_start(w, ties, A.S.root, o, d);
+            busy = walking = true;
+        }
+        head += avail;
         wave_sync();  // taken entries are read before their ring slots are reused
-        bool again = false, ended = false;
-        KeyPlanes<KM> kp;
-        if (have) {
-            const bool s1 = me.slot == 1;
-            const uint32_t nr = s1 ? U[1].nr : U[0].nr;
-            const uint32_t q = (s1 ? U[1].q0 : U[0].q0) + me.e / nr;
-            const uint32_t r = (s1 ? U[1].r0 : U[0].r0) + me.e % nr;
-            const f3 tx = s1 ? U[1].tx : U[0].tx;
-            load_planes<KM, AVG>(A, q, kp);
-#pragma unroll
-            for (int j = 0; j < KM; ++j)
-                if (j < kp.k && me.ovr[j] >= 0) {
-                    if (avg) {
-                        kp.pp[j] = xyz(qpl[((size_t)at * KM + j) * 2]);
-                        kp.pn[j] = xyz(qpl[((size_t)at * KM + j) * 2 + 1]);
-                    } else {
-                        kp.pp[j] = xyz(A.S.pos[me.ovr[j]]);
-                        kp.pn[j] = xyz(A.S.nrm[me.ovr[j]]);
-                    }
-                }
-            PairOut po;
-            int slot = 0, disk = -1;
-            f3 rp = mk(0.f, 0.f, 0.f), rn = mk(0.f, 0.f, 1.f);
-            const int out = validate_pass<KM, W, AVG, POL>(A, q, r, tx, kp, me.retries, stk, po, slot, disk, rp, rn);
-            if (out == kPassRetry) {
-                again = true;
-                me.retries += 1;
-#pragma unroll
-                for (int j = 0; j < KM; ++j)
-                    if (j == slot) {
-                        me.ovr[j] = disk;
-                        if (AVG) {
-                            kp.pp[j] = rp;
-                            kp.pn[j] = rn;
-                        }
-                    }
-            } else {
-                ended = true;
-                if (rec && q < A.D.rec_keys) {
-                    const size_t p = (size_t)q * n_rx + r;
-                    A.sb.valid[p] = po.valid;
-                    A.sb.len[p] = po.valid ? po.len : 0.f;
-                    A.sb.amp[p] = po.valid ? make_float4(po.te.re, po.te.im, po.tm.re, po.tm.im)
-                                           : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-                if (po.valid) {
-                    ++n_valid;
-                    res[me.slot * kUnitPairs + me.e] = make_float4(po.te.re, po.te.im, po.tm.re, po.tm.im);
-                    atomicOr(&vbits[me.slot][me.e >> 5], 1u << (me.e & 31));
-                }
-            }
+        const uint32_t n_busy = (uint32_t)__popcll(__ballot(busy));
+        // nothing is left that could feed an idle lane
+        const bool dry = exhausted && tail == head && !(U[0].open && U[0].t * kWave < U[0].ne) &&
+                         !(U[1].open && U[1].t * kWave < U[1].ne);
+        if (n_busy == 0) {
+            if (!U[0].open && !U[1].open) break;  // no unit left to open, every unit closed
+            continue;
         }
-        U[0].pending -= (uint32_t)__popcll(__ballot(ended && me.slot == 0));
-        U[1].pending -= (uint32_t)__popcll(__ballot(ended && me.slot == 1));
-        const uint64_t m = __ballot(again);
-        if (again) {
-            const uint32_t to = (tail + (uint32_t)__popcll(m & below)) % kRefineQueue;
-            queue[to] = me;
-            if (avg) {  // the replaced planes travel with the candidate
-#pragma unroll
-                for (int j = 0; j < KM; ++j)
-                    if (me.ovr[j] >= 0) {
-                        qpl[((size_t)to * KM + j) * 2] = make_float4(kp.pp[j].x, kp.pp[j].y, kp.pp[j].z, 0.f);
-                        qpl[((size_t)to * KM + j) * 2 + 1] = make_float4(kp.pn[j].x, kp.pn[j].y, kp.pn[j].z, 0.f);
-                    }
-            }
-        }
-        tail += (uint32_t)__popcll(m);
-        if (avg) block_sync_global();  // plane rows written by some lanes are read by others later
-        else wave_sync();
+        walk_round<W>(A.S, w, ties, walking, n_busy, dry ? 6 : kRefineRefillShift, o, d, excl, eps_self, eps_tie, stk);
     }
     flush_visits(stk, A.counters, 11);
     n_cand = warp_sum_u(n_cand);

@@ -8,6 +8,7 @@
 // consecutive ray slots per atomic fetch and hands them to its idle lanes.
 #include "common.h"
 #include "internal.h"
+#include "walk.h"
 
 namespace pcrt {
 
@@ -30,67 +31,11 @@ __device__ __forceinline__ uint32_t key_insert(const HashBufs &hb, uint32_t base
     return 0xffffffffu;
 }
 
-// Resumable closest-hit walk of one lane: the walk of closest_hit (near
-// child first, tie window, candidate list with its exact second pass), its
-// state kept across the bounce loop's iterations; park holds a leaf reached
-// but not yet tested.
-struct Walk {
-    f3 inv, oi;
-    int ref, sp, park;
-    float tmin;
-    Cand c[kTieList];
-    bool spill, pass2;  // candidate list overflowed; second (exact) pass running
-    float t_win, bd2, bt;
-    int bid;
-};
-
-__device__ __forceinline__ void walk_start(Walk &w, int root, f3 o, f3 d) {
-    w.inv = safe_inv(d);
-    w.oi = times(o, w.inv);
-    w.ref = root;
-    w.sp = 0;
-    w.park = kNoRef;
-    w.tmin = INFINITY;
-#pragma unroll
-    for (int q = 0; q < kTieList; ++q) w.c[q] = {INFINITY, INFINITY, -1};
-    w.spill = w.pass2 = false;
-    w.t_win = 0.f;
-    w.bd2 = w.bt = INFINITY;
-    w.bid = 0x7fffffff;
-}
-
-// One node of the walk: true if a child was entered (ref is then that child,
-// the other entered children are on the stack).
-template <int W>
-__device__ __forceinline__ bool node_step(const DevScene &S, Walk &w, float t_lo, float tc, Stack &stk) {
-    if constexpr (W > 2) {
-        return wide_step<W>(S, w.ref, w.sp, w.inv, w.oi, t_lo, tc, stk);
-    } else {
-        const uint32_t nb = (uint32_t)w.ref * 64u;
-        const float4 a = ld4(S.node, nb), b = ld4(S.node, nb + 16u), e = ld4(S.node, nb + 32u), r = ld4(S.node, nb + 48u);
-        float n0, n1;
-        const bool h0 = box_hit(a.x, a.y, a.z, a.w, b.x, b.y, w.inv, w.oi, t_lo, tc, n0);
-        const bool h1 = box_hit(b.z, b.w, e.x, e.y, e.z, e.w, w.inv, w.oi, t_lo, tc, n1);
-        const int r0 = __float_as_int(r.x), r1 = __float_as_int(r.y);
-        if (h0 && h1) {
-            const bool f0 = n0 <= n1;
-            stk.put(w.sp++, f0 ? r1 : r0);
-            w.ref = f0 ? r0 : r1;
-            return true;
-        }
-        if (h0 | h1) {
-            w.ref = h0 ? r0 : r1;
-            return true;
-        }
-        return false;
-    }
-}
-
 // The bounce loop (Sec. II-B) with ballot-compacted ray refill. Every lane
 // keeps one ray's state -- its bounce, origin, direction, unfolded length,
 // chain coefficients and key -- and the state of its current closest-hit
 // walk, which resumes from one iteration to the next. The wavefront steps
-// its walking lanes until at most half of its busy lanes are still walking;
+// its walking lanes until at most a quarter of its busy lanes are still walking;
 // the lanes whose walks ended then finish their bounce together (record the
 // interaction, reflect) and start the next bounce's walk, and lanes whose
 // rays ended are refilled, compacted in lane order by a ballot, from the ray
@@ -101,14 +46,24 @@ __device__ __forceinline__ bool node_step(const DevScene &S, Walk &w, float t_lo
 // share an iteration. A lane never waits for the wavefront's longest walk.
 // Parking only delays when a leaf's disks are tested; the nearest hit and its
 // tie rule do not depend on the visiting order, so the results are those of
-// closest_hit (bitwise, tested). Measured on the 1M-point office (4-wide
+// an unbroken walk (bitwise, tested). Measured on the 1M-point office (4-wide
 // tree, leaf 2): 3.11 ms -> 2.46 ms; without parking the refill alone gave
-// 3.26 ms (node and leaf steps in the same iterations), and half / half
-// thresholds beat one third or two thirds for either.
+// 3.26 ms (node and leaf steps in the same iterations).
+//
+// What bounds it: L2 misses of the node and disk loads, so wavefronts in
+// flight. With the tie lists in LDS (8 KiB per wavefront with the stack) the
+// loop fits five wavefronts per SIMD; with four / five, and refill at half:
+// office 2.23 / 2.25 ms, 64 poses in a room (36M rays) 10.4 / 10.1 ms; refill
+// at a quarter: 2.27 / 2.29 ms and 10.0 / 9.8 ms, the reception-point launch
+// 0.97 -> 0.93 ms. Four wavefronts with the lists in registers and refill at
+// half: 2.34, 10.9 and 1.02 ms.
+constexpr int kTraceRefillShift = 2;  // refill once at most busy / 4 lanes still walk
+
 template <int W>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 3 : 4, 8))) void k_trace(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 3 : 5, 8))) void k_trace(
     LaunchArgs A) {
     __shared__ int lds_stack[kStackLds * kWave];
+    __shared__ float tie_list[kTieRows * kWave];
     const int lane = threadIdx.x;
     const uint32_t glane = blockIdx.x * kWave + lane;
     Stack stk{lds_stack + lane, A.S.spill + glane, A.S.spill_lanes};
@@ -117,23 +72,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     const bool want_geom = A.flags & (4 | 8 | 32);  // points/lengths/cosines: diffuse, tape, averaged planes
     const bool avg = A.flags & 32;                  // weighted-average intersection over point sets
     const float eps_self = A.thr.eps_self, eps_tie = A.thr.eps_tie;
-    enum { kIdle = 0, kWalk = 1, kDone = 2 };
-    int phase = kIdle;
+    bool busy = false, walking = false;  // this lane has a ray; its walk has not ended
     uint32_t g = 0, j = 0, k = 0;
     int it = 0, excl = -1;
     f3 o = mk(0.f, 0.f, 0.f), d = mk(0.f, 0.f, 1.f);
     float L = 0.f;
     c32 pte = {1.f, 0.f}, ptm = {1.f, 0.f};
     uint64_t enc = 0;
+    const Ties ties{tie_list + lane};
     Walk w;
-    walk_start(w, A.S.root, o, d);
+    walk_start(w, ties, A.S.root, o, d);
     uint32_t q_next = 0, q_end = 0;  // this wavefront's reserved ray slots [q_next, q_end)
     bool q_dry = false;
     uint32_t n_int = 0, n_ray = 0, n_spill = 0;
     for (;;) {
         // refill idle lanes, in lane order, from the reserved slots
         for (;;) {
-            const uint64_t idle = __ballot(phase == kIdle);
+            const uint64_t idle = __ballot(!busy);
             if (!idle || q_dry) break;
             if (q_next >= q_end) {
                 uint32_t base = 0;
@@ -149,7 +104,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
             const uint32_t avail = q_end - q_next;
-            if (phase == kIdle && rank < avail) {
+            if (!busy && rank < avail) {
                 g = q_next + rank;
                 it = find_item(A.items, A.D.n_items, g);
                 const Item &I = A.items[it];
@@ -178,87 +133,31 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
                         pte = ptm = {1.f, 0.f};
                         enc = 0;
                         k = 0;
-                        walk_start(w, A.S.root, o, d);
-                        phase = kWalk;
+                        walk_start(w, ties, A.S.root, o, d);
+                        busy = walking = true;
                     }
                 }
             }
             q_next += min((uint32_t)__popcll(idle), avail);
         }
-        const uint32_t n_busy = (uint32_t)__popcll(__ballot(phase != kIdle));
+        const uint32_t n_busy = (uint32_t)__popcll(__ballot(busy));
         if (n_busy == 0) break;  // the slots are used up and every ray has ended
-        // walk until at most half of the busy lanes are still walking; node steps
-        // run until half of the walking lanes hold a leaf (parked), then the
-        // parked leaves are tested together
-        for (;;) {
-            for (;;) {
-                if (phase == kWalk && w.ref < 0 && w.ref != kNoRef && w.park == kNoRef) {
-                    w.park = w.ref;
-                    w.ref = w.sp > 0 ? stk.get(--w.sp) : kNoRef;
-                }
-                const uint32_t n_walk = (uint32_t)__popcll(__ballot(phase == kWalk));
-                const uint32_t n_park = (uint32_t)__popcll(__ballot(phase == kWalk && w.park != kNoRef));
-                if (!__ballot(phase == kWalk && w.ref >= 0) || 2 * n_park >= n_walk) break;
-                if (phase == kWalk && w.ref >= 0) {
-                    stk.visit();
-                    const float tc = w.pass2 ? w.t_win : w.tmin + eps_tie;
-                    if (!node_step<W>(A.S, w, eps_self, tc, stk)) w.ref = w.sp > 0 ? stk.get(--w.sp) : kNoRef;
-                }
-            }
-            if (phase == kWalk && w.park != kNoRef) {
-                const int v = -1 - w.park;
-                const int first = v >> 3, cnt = (v & 7) + 1;
-                stk.test(cnt);
-                for (int i = 0; i < cnt; ++i) {
-                    if (w.pass2)
-                        visit_disk<true>(A.S, first + i, o, d, excl, eps_self, eps_tie, w.tmin, w.c, w.spill, w.t_win,
-                                         w.bd2, w.bid, w.bt);
-                    else
-                        visit_disk<false>(A.S, first + i, o, d, excl, eps_self, eps_tie, w.tmin, w.c, w.spill,
-                                          w.t_win, w.bd2, w.bid, w.bt);
-                }
-                w.park = kNoRef;
-            }
-            if (phase == kWalk && w.ref == kNoRef) phase = kDone;
-            const uint32_t n_walk = (uint32_t)__popcll(__ballot(phase == kWalk));
-            if (n_walk == 0 || 2 * n_walk <= n_busy) break;
-        }
-        if (phase != kDone) continue;
+        walk_round<W>(A.S, w, ties, walking, n_busy, kTraceRefillShift, o, d, excl, eps_self, eps_tie, stk);
+        if (walking || !busy) continue;
         // this lane's walk ended: the second, exact pass if the tie list overflowed, else the bounce
-        if (w.spill && !w.pass2 && w.tmin < INFINITY) {
+        if (walk_second_pass(w, ties, A.S.root, eps_tie)) {
             n_spill += 1;
-            w.pass2 = true;
-            w.t_win = w.tmin + eps_tie;
-            w.ref = A.S.root;
-            w.sp = 0;
-            w.park = kNoRef;
-            phase = kWalk;
+            walking = true;
             continue;
         }
-        int h = -1;
-        float t = INFINITY;
-        if (w.tmin < INFINITY) {
-            if (w.pass2) {
-                h = w.bid;
-                t = w.bt;
-            } else {
-#pragma unroll
-                for (int q = 0; q < kTieList; ++q)
-                    if (w.c[q].id >= 0 && (w.c[q].d2 < w.bd2 || (w.c[q].d2 == w.bd2 && w.c[q].id < w.bid))) {
-                        w.bd2 = w.c[q].d2;
-                        w.bid = w.c[q].id;
-                        w.bt = w.c[q].t;
-                    }
-                h = w.bid;
-                t = w.bt;
-            }
-        }
+        float t;
+        const int h = walk_hit(w, ties, t);
         const size_t rb = (size_t)g * K;
         if (h < 0) {  // the ray leaves the scene
             for (uint32_t kk = k; kk < K; ++kk) A.rb.id[rb + kk] = -1;
             n_int += k;
             n_ray += 1;
-            phase = kIdle;
+            busy = false;
             continue;
         }
         const float4 pn = A.S.nrm[h];
@@ -309,10 +208,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
         if (k == K) {
             n_int += K;
             n_ray += 1;
-            phase = kIdle;
+            busy = false;
         } else {
-            walk_start(w, A.S.root, o, d);
-            phase = kWalk;
+            walk_start(w, ties, A.S.root, o, d);
+            walking = true;
         }
     }
     flush_visits(stk, A.counters, 9);
@@ -343,14 +242,17 @@ uint32_t trace_cap() {
     return cap;
 }
 
+uint32_t trace_cap_w(uint32_t width) {
+    return width == 8 ? trace_cap<8>() : width == 4 ? trace_cap<4>() : trace_cap<2>();
+}
+
 uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays) {
-    const uint32_t cap = D.width == 8 ? trace_cap<8>() : D.width == 4 ? trace_cap<4>() : trace_cap<2>();
     const uint32_t units = (D.T + wave_rays - 1) / wave_rays;
-    return std::max<uint32_t>(1, std::min(cap, units));
+    return std::max<uint32_t>(1, std::min(trace_cap_w(D.width), units));
 }
 
 void launch_trace(const LaunchArgs &A, hipStream_t s) {
-    uint32_t grid = trace_grid(A.D, A.wave_rays);
+    const uint32_t grid = trace_grid(A.D, A.wave_rays);
     switch (A.D.width) {
         case 8: hipLaunchKernelGGL(k_trace<8>, dim3(grid), dim3(kWave), 0, s, A); break;
         case 4: hipLaunchKernelGGL(k_trace<4>, dim3(grid), dim3(kWave), 0, s, A); break;
