@@ -168,6 +168,7 @@ struct LaunchArgs {
     HashBufs hb;
     SpecBufs sb;
     uint32_t wave_rays; // rays a wavefront takes per work fetch (multiple of 64)
+    uint32_t trace_lanes; // lanes of a wavefront that take rays (a power of two)
     f3 pol_tx, pol_rx;  // polarised field: transmit and receive polarisation vectors
     float dps_area;     // point sets: the area rho^2 a voxel diffuse path stands for
     const uint8_t *dps_vis;  // launch at the reception points: [n_rx][n_sets] receiver sees reception point

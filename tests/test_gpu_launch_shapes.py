@@ -45,3 +45,15 @@ def test_refinement_slices_do_not_change_a_receiver(P, office, pol):
     for take in (slice(0, 9), slice(5, 6), slice(61, 64)):
         part, _ = _solve(P, office, rx[take], 1 << 19, 4, pol=pol)
         assert np.array_equal(part, full[take])
+
+
+@pytest.mark.parametrize("n", [1, 3, 257, 4096, 5000, 20_000, 66_000])
+def test_ray_lanes_do_not_change_a_ray(P, office, n):
+    """The first n rays of a budget, traced alone: small launches give a wavefront 4 to 32 rays, larger ones 64."""
+    budget, K = 70_000, 3
+    print("[gpu-test] ray lanes %d" % n, flush=True)
+    _, full = _solve(P, office, scenes.office_rx()[:2], budget, K, want_seq=True)
+    _, part = _solve(P, office, scenes.office_rx()[:2], budget, K, want_seq=True, ray_subset=np.arange(n))
+    assert np.array_equal(part.seq.cpu().numpy(), full.seq.cpu().numpy()[:n])
+    assert part.counter("rays") == n
+    assert part.counter("interactions") == int((full.seq[:n] >= 0).sum())
