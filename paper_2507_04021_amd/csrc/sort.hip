@@ -26,29 +26,6 @@ __global__ void k_rs_hist(const uint64_t *__restrict__ key, uint32_t n, int shif
     hist[threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
 }
 
-// Exclusive scan of a u32 array in one block of 1024 threads (build only).
-__global__ void k_scan_small(uint32_t *__restrict__ a, uint32_t n) {
-    __shared__ uint32_t part[1024];
-    uint32_t per = (n + 1023) / 1024;
-    uint32_t b = threadIdx.x * per, e = min(n, b + per);
-    uint32_t s = 0;
-    for (uint32_t i = b; i < e; ++i) s += a[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        uint32_t v = threadIdx.x >= (uint32_t)o ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    uint32_t run = part[threadIdx.x] - s;
-    for (uint32_t i = b; i < e; ++i) {
-        uint32_t v = a[i];
-        a[i] = run;
-        run += v;
-    }
-}
-
 __global__ void k_rs_scatter(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                              uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, uint32_t n, int shift,
                              const uint32_t *__restrict__ hist, uint32_t tiles) {
@@ -90,43 +67,212 @@ __global__ void k_rs_scatter(const uint64_t *__restrict__ kin, const uint32_t *_
 }
 
 
-__global__ __launch_bounds__(1024) void k_scan_block(uint32_t *a, uint32_t n, uint32_t *blk) {
-    __shared__ uint32_t s[1024];
-    uint32_t i = blockIdx.x * 1024 + threadIdx.x;
-    uint32_t v = i < n ? a[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        uint32_t t = threadIdx.x >= (uint32_t)o ? s[threadIdx.x - o] : 0;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
+// Exclusive scan. Two launches, reduce then scan: tile sums, then every tile
+// adds up the sums before its own (a few hundred to a few thousand words out
+// of L2) and scans itself. Nothing has to be cleared beforehand and no block
+// waits for another. Arrays of one tile take one launch. What bounds it is
+// the launches (a solve has ten or so scans of a few thousand words), then
+// the array's two reads and one write. Against block scans, a one-block scan
+// of their sums and an add pass: 43 200-disk room, nine scans of 4 096 words
+// 86 -> 20 us; 72 M marks of a 64-pose batch 650 -> 230 us.
+constexpr uint32_t kScanOne = 16;  // words per thread of a scan in one block
+
+__device__ __forceinline__ uint32_t wave_scan_u(uint32_t v) {  // inclusive
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t t = __shfl_up(v, o, kWave);
+        if (lane >= o) v += t;
     }
-    if (i < n) a[i] = s[threadIdx.x] - v;
-    if (threadIdx.x == 1023) blk[blockIdx.x] = s[1023];
-    if (blockIdx.x == 0 && threadIdx.x == 0) blk[gridDim.x] = 0;  // becomes the total after the block-sum scan
+    return v;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_add(uint32_t *a, uint32_t n, const uint32_t *blk) {
-    uint32_t i = blockIdx.x * 1024 + threadIdx.x;
-    if (i < n) a[i] += blk[blockIdx.x];
+// Exclusive sum of v over a block of 1024 threads; part: 16 words of LDS.
+__device__ __forceinline__ uint32_t block_scan_u(uint32_t v, uint32_t *part, uint32_t &total) {
+    const uint32_t w = threadIdx.x / kWave;
+    const uint32_t in = wave_scan_u(v);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) part[w] = in;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (uint32_t i = 0; i < 16; ++i) {
+        const uint32_t p = part[i];
+        before += i < w ? p : 0u;
+        all += p;
+    }
+    __syncthreads();
+    total = all;
+    return before + in - v;
+}
+
+// IPT words per thread, four at a time at index 4 t + 4096 k of the tile.
+template <uint32_t IPT>
+__global__ __launch_bounds__(1024) void k_scan_sums(const uint32_t *__restrict__ a, uint32_t n,
+                                                    uint32_t *__restrict__ blk) {
+    __shared__ uint32_t part[16];
+    const uint64_t base = (uint64_t)blockIdx.x * (1024u * IPT);
+    uint32_t s = 0;
+    for (uint32_t k = 0; k < IPT / 4; ++k) {
+        const uint64_t i = base + k * 4096u + threadIdx.x * 4u;
+        if (i + 4 <= n) {
+            const uint4 v = *(const uint4 *)(a + i);
+            s += v.x + v.y + v.z + v.w;
+        } else {
+            for (uint64_t j = i; j < n && j < i + 4; ++j) s += a[j];
+        }
+    }
+    uint32_t total;
+    (void)block_scan_u(s, part, total);
+    if (threadIdx.x == 0) blk[blockIdx.x] = total;
+}
+
+// blk: the tile sums; the array's total goes to blk[total_at] (beyond them).
+template <uint32_t IPT>
+__global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t *__restrict__ a, uint32_t n, uint32_t *blk,
+                                                     uint32_t total_at) {
+    __shared__ uint32_t part[16];
+    uint32_t before = 0, run, all;
+    if (gridDim.x > 1) {
+        uint32_t s = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 1024) s += blk[i];
+        (void)block_scan_u(s, part, before);
+    }
+    const uint64_t base = (uint64_t)blockIdx.x * (1024u * IPT);
+    run = before;
+    for (uint32_t k = 0; k < IPT / 4; ++k) {
+        const uint64_t i = base + k * 4096u + threadIdx.x * 4u;
+        if (base + k * 4096u >= n) break;  // block-uniform
+        uint32_t v[4] = {0, 0, 0, 0};
+        if (i + 4 <= n) {
+            const uint4 q = *(const uint4 *)(a + i);
+            v[0] = q.x;
+            v[1] = q.y;
+            v[2] = q.z;
+            v[3] = q.w;
+        } else {
+            for (uint32_t j = 0; j < 4; ++j) v[j] = i + j < n ? a[i + j] : 0u;
+        }
+        const uint32_t e0 = run + block_scan_u(v[0] + v[1] + v[2] + v[3], part, all);
+        const uint32_t e1 = e0 + v[0], e2 = e1 + v[1], e3 = e2 + v[2];
+        if (i + 4 <= n) {
+            *(uint4 *)(a + i) = make_uint4(e0, e1, e2, e3);
+        } else {
+            const uint32_t e[4] = {e0, e1, e2, e3};
+            for (uint32_t j = 0; j < 4; ++j)
+                if (i + j < n) a[i + j] = e[j];
+        }
+        run += all;
+    }
+    if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) blk[total_at] = run;
+}
+
+// Sort of up to kRsSmall keys in one block: all digit passes in LDS, with the
+// same stable multisplit (a wavefront owns 256 consecutive positions, four
+// rounds of 64). One launch instead of five per digit: the 4 096 records of a
+// small solve 87 -> 30 us with the passes before and after it.
+constexpr uint32_t kRsSmall = 4096;
+constexpr uint32_t kRsSmallRounds = kRsSmall / 1024;
+
+__global__ __launch_bounds__(1024) void k_rs_small(uint64_t *key, uint32_t *val, uint32_t n, int bit_lo, int bit_hi) {
+    __shared__ uint64_t k_s[kRsSmall];
+    __shared__ uint32_t v_s[kRsSmall];
+    __shared__ uint16_t cnt[16][256];  // per wavefront and digit: keys so far, then the digit's start
+    __shared__ uint32_t part[16];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint64_t k[kRsSmallRounds];
+    uint32_t v[kRsSmallRounds], rank[kRsSmallRounds];
+    for (uint32_t r = 0; r < kRsSmallRounds; ++r) {
+        const uint32_t i = wave * (kRsSmall / 16) + r * kWave + lane;
+        k[r] = i < n ? key[i] : ~0ull;
+        v[r] = i < n ? val[i] : 0u;
+    }
+    for (int shift = bit_lo; shift < bit_hi; shift += 8) {
+        for (uint32_t i = threadIdx.x; i < 16u * 256u; i += 1024u) (&cnt[0][0])[i] = 0;
+        __syncthreads();
+        for (uint32_t r = 0; r < kRsSmallRounds; ++r) {
+            const uint32_t i = wave * (kRsSmall / 16) + r * kWave + lane;
+            const bool ok = i < n;
+            const uint32_t dg = (uint32_t)(k[r] >> shift) & 255u;
+            uint64_t peers = __ballot(ok);
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (dg >> b) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t below = mbcnt(peers);
+            rank[r] = ok ? cnt[wave][dg] + below : 0u;
+            wave_sync();
+            if (ok && below == 0) cnt[wave][dg] = (uint16_t)(cnt[wave][dg] + __popcll(peers));
+            wave_sync();
+        }
+        __syncthreads();
+        // thread t: digit t / 4, wavefronts 4 (t % 4) .. + 3, in digit-major order
+        const uint32_t d0 = threadIdx.x / 4, w0 = 4 * (threadIdx.x % 4);
+        uint32_t c[4], s = 0;
+        for (int j = 0; j < 4; ++j) {
+            c[j] = cnt[w0 + j][d0];
+            s += c[j];
+        }
+        uint32_t all, run = block_scan_u(s, part, all);
+        for (int j = 0; j < 4; ++j) {
+            cnt[w0 + j][d0] = (uint16_t)run;
+            run += c[j];
+        }
+        __syncthreads();
+        for (uint32_t r = 0; r < kRsSmallRounds; ++r) {
+            const uint32_t i = wave * (kRsSmall / 16) + r * kWave + lane;
+            if (i < n) {
+                const uint32_t to = cnt[wave][(uint32_t)(k[r] >> shift) & 255u] + rank[r];
+                k_s[to] = k[r];
+                v_s[to] = v[r];
+            }
+        }
+        __syncthreads();
+        for (uint32_t r = 0; r < kRsSmallRounds; ++r) {
+            const uint32_t i = wave * (kRsSmall / 16) + r * kWave + lane;
+            if (i < n) {
+                k[r] = k_s[i];
+                v[r] = v_s[i];
+            }
+        }
+        __syncthreads();
+    }
+    for (uint32_t r = 0; r < kRsSmallRounds; ++r) {
+        const uint32_t i = wave * (kRsSmall / 16) + r * kWave + lane;
+        if (i < n) {
+            key[i] = k[r];
+            val[i] = v[r];
+        }
+    }
 }
 
 uint32_t scan_blk_words(uint32_t n) { return (n + 1023) / 1024 + 1; }
 uint32_t radix_hist_words(uint32_t n) { return 256u * ((n + kRsTile - 1) / kRsTile); }
 
-// In-place exclusive scan; the total lands in blk[ceil(n / 1024)].
+// In-place exclusive scan (a 16-byte aligned); the total lands in
+// blk[ceil(n / 1024)]. Tiles of 4 096 words; beyond 2^22 words of 16 384, so
+// that a tile adds up a few thousand sums at most.
 void exclusive_scan(uint32_t *a, uint32_t n, uint32_t *blk, hipStream_t s) {
-    const uint32_t nb = (n + 1023) / 1024;
-    hipLaunchKernelGGL(k_scan_block, dim3(nb), dim3(1024), 0, s, a, n, blk);
-    hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(1024), 0, s, blk, nb + 1);
-    hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(1024), 0, s, a, n, blk);
+    const uint32_t total_at = (n + 1023) / 1024;
+    if (n <= 1024 * kScanOne) {
+        hipLaunchKernelGGL(k_scan_tiles<kScanOne>, dim3(1), dim3(1024), 0, s, a, n, blk, total_at);
+    } else if (n <= (1u << 22)) {
+        const uint32_t nb = (n + 4095) / 4096;
+        hipLaunchKernelGGL(k_scan_sums<4>, dim3(nb), dim3(1024), 0, s, a, n, blk);
+        hipLaunchKernelGGL(k_scan_tiles<4>, dim3(nb), dim3(1024), 0, s, a, n, blk, total_at);
+    } else {
+        const uint32_t nb = (uint32_t)(((uint64_t)n + 16383) / 16384);
+        hipLaunchKernelGGL(k_scan_sums<16>, dim3(nb), dim3(1024), 0, s, a, n, blk);
+        hipLaunchKernelGGL(k_scan_tiles<16>, dim3(nb), dim3(1024), 0, s, a, n, blk, total_at);
+    }
 }
 
 // Sorts (key, value) by key bits [bit_lo, bit_hi) with 8-bit passes; returns
 // true if the sorted data ended in (k1, v1), false if in (k0, v0).
 bool radix_sort_u64(uint64_t *k0, uint32_t *v0, uint64_t *k1, uint32_t *v1, uint32_t n, int bit_lo, int bit_hi,
                     uint32_t *hist, uint32_t *blk, hipStream_t s) {
+    if (n <= kRsSmall) {
+        hipLaunchKernelGGL(k_rs_small, dim3(1), dim3(1024), 0, s, k0, v0, n, bit_lo, bit_hi);
+        return false;
+    }
     const uint32_t tiles = (n + kRsTile - 1) / kRsTile;
     bool flip = false;
     for (int shift = bit_lo; shift < bit_hi; shift += 8) {

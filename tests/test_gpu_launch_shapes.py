@@ -57,3 +57,20 @@ def test_ray_lanes_do_not_change_a_ray(P, office, n):
     assert np.array_equal(part.seq.cpu().numpy(), full.seq.cpu().numpy()[:n])
     assert part.counter("rays") == n
     assert part.counter("interactions") == int((full.seq[:n] >= 0).sum())
+
+
+@pytest.fixture(scope="module")
+def room(P):
+    sc = scenes.box_room(spacing=0.1, radius=0.08)
+    return sc, P.Scene.from_scene(sc)
+
+
+@pytest.mark.parametrize("rays,K", [(256, 1), (1024, 4), (1280, 4), (5200, 4)])
+def test_record_sort_sizes(P, orc, room, rays, K):
+    """Records of one LDS sort (up to 4 096) and of the device-wide one, against the oracle."""
+    print("[gpu-test] record sort %d x %d" % (rays, K), flush=True)
+    mats, rx = scenes.box_room_materials(scatter=0.3), [scenes.BOX_RX, (2.0, 1.0, 0.7)]
+    r = P.solve(room[1], mats, scenes.BOX_TX, rx, 3.5e9, rays, K=K, flags=DIFF)
+    ref = orc.solve(room[0], mats, scenes.BOX_TX, rx, 3.5e9, rays, K=K, flags=DIFF)
+    assert np.max(np.abs(r.gain.cpu().numpy() / ref.G - 1)) < 1e-4
+
