@@ -438,7 +438,7 @@ void launch_dps_diffuse(const LaunchArgs &A, float area, hipStream_t s) {
     B.counters = A.dcnt;
     fill_u32(B.key_off, 0, A.D.n_items + 1, s);
     fill_u32(B.chunk_off, 0, A.D.n_items + 1, s);
-    launch_keys(B, s);
+    launch_keys(B, false, s);
     const dim3 g(A.D.n_ray_chunks, (A.D.n_rx + kWave - 1) / kWave);
     hipLaunchKernelGGL(k_dps_diffuse, g, dim3(kDpsWaves * kWave), 0, s, A, area);
 }

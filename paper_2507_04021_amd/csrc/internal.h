@@ -237,7 +237,8 @@ __device__ __forceinline__ f3 record_normal(const LaunchArgs &A, uint32_t ri) {
 }
 
 void launch_trace(const LaunchArgs &A, hipStream_t s);
-void launch_keys(const LaunchArgs &A, hipStream_t s);
+// label_keys: the table holds label sequences (not the voxel diffuse keys)
+void launch_keys(const LaunchArgs &A, bool label_keys, hipStream_t s);
 void launch_refine(const LaunchArgs &A, hipStream_t s);
 void launch_refine_pol(const LaunchArgs &A, dim3 grid, hipStream_t s);  // PCRT_POLARIZED instances
 // Morton order of the interaction records: sorts them, fills A.dsort.pack and

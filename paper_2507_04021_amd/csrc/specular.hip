@@ -89,8 +89,105 @@ __global__ void k_plan(LaunchArgs A, const uint32_t *total) {
     }
 }
 
-void launch_keys(const LaunchArgs &A, hipStream_t s) {
+// Key list from the tables, for small ones: one block per transmitter takes
+// the occupied slots of its table, forms each key's record (its representative
+// ray's, at the key's length) and puts them in record order, which is the
+// order of the marks. A record index orders the keys of one transmitter, so
+// a key's place is the number of smaller ones.
+constexpr uint32_t kTableMax = 1024;  // slots per transmitter
+
+__global__ __launch_bounds__(256) void k_keys_table(LaunchArgs A) {
+    __shared__ uint32_t rec[kTableMax];
+    __shared__ uint32_t n_s;
+    const uint32_t it = blockIdx.x, n_items = A.D.n_items;
+    if (threadIdx.x == 0) n_s = 0;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < A.hb.cap; i += 256) {
+        uint64_t e = A.hb.key[(size_t)it * A.hb.cap + i];
+        if (e == 0ull) continue;
+        uint32_t k = 0;  // digits of the key: the surface labels, each + 1
+        for (; e; e /= A.n_surf1) ++k;
+        const uint32_t g = A.items[it].ray_off + A.hb.rep[(size_t)it * A.hb.cap + i];
+        rec[atomicAdd(&n_s, 1u)] = g * A.D.K + k - 1;
+    }
+    __syncthreads();
+    const uint32_t n = n_s;
+    uint32_t *to = n_items == 1 ? A.keylist : A.scan + (size_t)it * A.hb.cap;
+    for (uint32_t i = threadIdx.x; i < n; i += 256) {
+        const uint32_t r = rec[i];
+        uint32_t at = 0;
+        for (uint32_t j = 0; j < n; ++j) at += rec[j] < r;
+        to[at] = r;
+    }
+    if (threadIdx.x) return;
+    if (n_items > 1) {
+        A.key_off[it] = n;  // counts until the ranges are planned
+    } else {
+        A.key_off[0] = A.chunk_off[0] = 0;
+        A.key_off[1] = n;
+        A.chunk_off[1] = (n + kKeyChunk - 1) / kKeyChunk;
+        A.counters[3] = n;
+    }
+}
+
+// Key counts in key_off -> key ranges and reduction chunks (one block).
+__global__ __launch_bounds__(1024) void k_plan_counts(LaunchArgs A) {
+    __shared__ uint32_t keys[1024], chunks[1024];
+    const uint32_t n_items = A.D.n_items, per = (n_items + 1023) / 1024;
+    const uint32_t b = min(n_items, threadIdx.x * per), e = min(n_items, b + per);
+    uint32_t sk = 0, sc = 0;
+    for (uint32_t i = b; i < e; ++i) {
+        sk += A.key_off[i];
+        sc += (A.key_off[i] + kKeyChunk - 1) / kKeyChunk;
+    }
+    keys[threadIdx.x] = sk;
+    chunks[threadIdx.x] = sc;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        const bool add = threadIdx.x >= (uint32_t)o;
+        const uint32_t vk = add ? keys[threadIdx.x - o] : 0, vc = add ? chunks[threadIdx.x - o] : 0;
+        __syncthreads();
+        keys[threadIdx.x] += vk;
+        chunks[threadIdx.x] += vc;
+        __syncthreads();
+    }
+    uint32_t rk = keys[threadIdx.x] - sk, rc = chunks[threadIdx.x] - sc;
+    for (uint32_t i = b; i < e; ++i) {
+        const uint32_t n = A.key_off[i];
+        A.key_off[i] = rk;
+        A.chunk_off[i] = rc;
+        rk += n;
+        rc += (n + kKeyChunk - 1) / kKeyChunk;
+    }
+    if (threadIdx.x == 1023) {
+        A.key_off[n_items] = keys[1023];
+        A.chunk_off[n_items] = chunks[1023];
+        A.counters[3] = keys[1023];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_keys_gather(LaunchArgs A) {
+    const uint32_t it = blockIdx.x, k0 = A.key_off[it], n = A.key_off[it + 1] - k0;
+    for (uint32_t i = threadIdx.x; i < n; i += 256) A.keylist[k0 + i] = A.scan[(size_t)it * A.hb.cap + i];
+}
+
+// Small tables are read themselves; larger ones (and a subset of the rays,
+// whose record is not known from its ray id) go through marks of the records.
+// The line is where a block can hold and order a table in LDS: at 1 024 slots
+// (at most 512 keys) that is two rounds of at most 512 compares, and reading
+// 12 KiB per transmitter is less than its records' marks from 1 000 rays up.
+// 64 poses of 2^16 to 2^20 rays (72 M records, 16 384 slots) 1.25 ms -> 15 us;
+// one link of 2 000 rays 20 -> 6 us.
+void launch_keys(const LaunchArgs &A, bool label_keys, hipStream_t s) {
     const uint32_t n_rec = A.D.T * A.D.K;
+    if (label_keys && !A.subset && A.hb.cap <= kTableMax && (uint64_t)A.hb.cap * A.D.n_items <= n_rec) {
+        hipLaunchKernelGGL(k_keys_table, dim3(A.D.n_items), dim3(256), 0, s, A);
+        if (A.D.n_items > 1) {
+            hipLaunchKernelGGL(k_plan_counts, dim3(1), dim3(1024), 0, s, A);
+            hipLaunchKernelGGL(k_keys_gather, dim3(A.D.n_items), dim3(256), 0, s, A);
+        }
+        return;
+    }
     const uint32_t blk = (n_rec + 255) / 256;
     hipLaunchKernelGGL(k_mark, dim3(blk), dim3(256), 0, s, A, n_rec);
     const uint32_t nb = (n_rec + 1023) / 1024;

@@ -65,6 +65,20 @@ def room(P):
     return sc, P.Scene.from_scene(sc)
 
 
+@pytest.mark.parametrize("rays,K", [(1, 1), (255, 2), (257, 3), (2000, 2), (9000, 3)])
+def test_key_list_from_table_and_from_marks(P, room, rays, K):
+    """A launch of every ray lists its keys from the table, the same rays as a subset from marked records."""
+    print("[gpu-test] key list %d x %d" % (rays, K), flush=True)
+    got = []
+    for sub in (None, np.arange(rays)):
+        r = P.solve(room[1], scenes.box_room_materials(), scenes.BOX_TX, [scenes.BOX_RX], 3.5e9, rays, K=K,
+                    flags=LOS | SPEC | 8, ray_subset=sub)
+        got.append(P.paths(r))
+    assert got[0]["n_keys"] == got[1]["n_keys"] > 0
+    for k in ("key_ray", "key_len", "key_seq", "valid", "length", "amp_te"):
+        assert np.array_equal(got[0][k], got[1][k]), k
+
+
 @pytest.mark.parametrize("rays,K", [(256, 1), (1024, 4), (1280, 4), (5200, 4)])
 def test_record_sort_sizes(P, orc, room, rays, K):
     """Records of one LDS sort (up to 4 096) and of the device-wide one, against the oracle."""
@@ -74,3 +88,14 @@ def test_record_sort_sizes(P, orc, room, rays, K):
     ref = orc.solve(room[0], mats, scenes.BOX_TX, rx, 3.5e9, rays, K=K, flags=DIFF)
     assert np.max(np.abs(r.gain.cpu().numpy() / ref.G - 1)) < 1e-4
 
+
+def test_batch_of_many_transmitters_matches_single_solves(P, room):
+    """130 transmitters: items beyond the first launch of 96, key lists gathered over all of them."""
+    print("[gpu-test] batch of 130", flush=True)
+    tx, n = scenes.trajectory(seed=4021, n=130, min_rays=1, max_rays=3000)
+    mats, rx = scenes.box_room_materials(scatter=0.2), [scenes.BOX_RX, (2.0, 1.0, 0.7)]
+    b = P.solve_batch(room[1], mats, tx, n, rx, 3.5e9, K=2, flags=LOS | SPEC | DIFF)
+    for i in range(0, 130, 7):
+        r = P.solve(room[1], mats, tx[i], rx, 3.5e9, int(n[i]), K=2, flags=LOS | SPEC | DIFF)
+        for x, y in ((b.gain, r.gain), (b.h_te, r.h_te), (b.parts, r.parts)):
+            assert np.array_equal(x[i].cpu().numpy(), y.cpu().numpy()), i
