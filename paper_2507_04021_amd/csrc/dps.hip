@@ -3,21 +3,30 @@
 // set are stored together (centre and id, normal), so the weighted-average
 // intersection (Sec. II-C) reads a set as one contiguous run.
 //
-// Steps: a 63-bit key per point (21 bits per axis, biased voxel index, x
-// major), a stable radix sort of (key, id), set heads where the key changes,
+// Steps: a key per point (its voxel index from the scene's lowest voxel, x major,
+// with the bits that the scene's extent needs per axis, 21 at most), a stable
+// radix sort of (key, id), set heads where the key changes,
 // an exclusive scan of the heads, then one pass that writes the members, the
 // set offsets and the set of every id. Members of a set keep increasing id
 // order (the sort is stable and starts from ids in order).
 #include "common.h"
 #include "internal.h"
 
+#include <cmath>
+
 namespace pcrt {
 
-constexpr int kVoxBits = 21;
 constexpr int64_t kVoxBias = 1ll << 20;  // voxel indices in [-2^20, 2^20)
 
-__global__ void k_voxel_keys(const float4 *__restrict__ pos, uint32_t n, double rho, uint64_t *__restrict__ key,
-                             uint32_t *__restrict__ val, uint32_t *__restrict__ stat) {
+struct VoxelGrid {
+    int64_t lo[3];  // lowest voxel index per axis
+    int bits[3];
+};
+
+// status bit 0: a voxel index beyond +-2^20. A point outside the grid (a refused
+// scene's) is put into its edge voxels.
+__global__ void k_voxel_keys(const float4 *__restrict__ pos, uint32_t n, double rho, VoxelGrid G,
+                             uint64_t *__restrict__ key, uint32_t *__restrict__ val, uint32_t *__restrict__ stat) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const float4 p = pos[i];
         const double c[3] = {p.x, p.y, p.z};
@@ -27,7 +36,8 @@ __global__ void k_voxel_keys(const float4 *__restrict__ pos, uint32_t n, double 
             const double v = floor(c[a] / rho);  // FP64, correctly rounded division
             const bool in = v >= -(double)kVoxBias && v < (double)kVoxBias;
             bad |= !in;
-            k = k << kVoxBits | (in ? (uint64_t)((int64_t)v + kVoxBias) : 0ull);
+            const int64_t top = (1ll << G.bits[a]) - 1, d = in ? (int64_t)v - G.lo[a] : 0ll;
+            k = k << G.bits[a] | (uint64_t)(d < 0 ? 0ll : d > top ? top : d);
         }
         if (bad) atomicOr(stat, 1u);
         key[i] = k;
@@ -96,9 +106,26 @@ hipError_t build_point_sets(const SceneLayout &L, char *ws, uint32_t n, float rh
     uint32_t *stat = (uint32_t *)P(L.dps_stat), *flag = (uint32_t *)P(L.dps_flag);
     const dim3 g(std::min<uint32_t>((n + 255) / 256, 8192)), b(256);
     fill_u32(stat, 0u, 2, s);
-    hipLaunchKernelGGL(k_voxel_keys, g, b, 0, s, (const float4 *)P(L.pos_id), n, (double)rho, k0, v0, stat);
-    const bool in1 = radix_sort_u64(k0, v0, k1, v1, n, 0, 3 * kVoxBits, (uint32_t *)P(L.hist),
-                                    (uint32_t *)P(L.scan_blk), s);
+    // The voxel range of the scene, from the bounds of its centres (floor(c / rho)
+    // is monotonic in c), decides how many key bits there are to sort: 3 digit
+    // passes instead of 8 on the 1M-point office (12 x 8 x 3 m, 6.25 cm voxels).
+    float B[6];
+    hipError_t e = hipMemcpyAsync(B, P(L.bounds), sizeof B, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    VoxelGrid G;
+    int bits = 0;
+    for (int a = 0; a < 3; ++a) {
+        const double lo = std::floor((double)B[a] / (double)rho), hi = std::floor((double)B[3 + a] / (double)rho);
+        const bool in = lo >= -(double)kVoxBias && hi < (double)kVoxBias && lo <= hi;
+        G.lo[a] = in ? (int64_t)lo : -kVoxBias;
+        const uint64_t span = in ? (uint64_t)((int64_t)hi - G.lo[a]) : (uint64_t)(2 * kVoxBias - 1);
+        G.bits[a] = 0;
+        while (span >> G.bits[a]) ++G.bits[a];
+        bits += G.bits[a];
+    }
+    hipLaunchKernelGGL(k_voxel_keys, g, b, 0, s, (const float4 *)P(L.pos_id), n, (double)rho, G, k0, v0, stat);
+    const bool in1 = radix_sort_u64(k0, v0, k1, v1, n, 0, bits, (uint32_t *)P(L.hist), (uint32_t *)P(L.scan_blk), s);
     const uint64_t *key = in1 ? k1 : k0;
     const uint32_t *id = in1 ? v1 : v0;
     hipLaunchKernelGGL(k_set_heads, g, b, 0, s, key, n, flag);

@@ -47,8 +47,9 @@ struct SceneLayout {
     uint32_t n_internal = 1;                        // binary internal nodes (buffer capacity)
     uint32_t builder = kBuildLbvh;
     size_t cbox[2] = {0, 0}, cid[2] = {0, 0}, csz[2] = {0, 0};  // clustering build (builder == kBuildPloc)
-    size_t nn = 0, mflag = 0, kflag = 0, pblk = 0, nsize = 0, noff = 0, leaf_pos = 0, perm2 = 0, pleaf2 = 0;
-    size_t wnode = 0, front0 = 0, front1 = 0, wcnt = 0, wblk = 0;  // wide collapse (width > 2)
+    size_t nsize = 0, noff = 0, leaf_pos = 0, perm2 = 0, pass_st = 0;
+    size_t tile_status[2] = {0, 0}, ticket = 0;     // scans of the passes (clustering) and levels (wide collapse)
+    size_t wnode = 0, front0 = 0, front1 = 0, level_st = 0;         // wide collapse (width > 2)
     size_t qnode = 0, qref = 0;                                     // its compact any-hit copy
     size_t sah_pending = 0, sah_cost = 0, sah_choice = 0;           // its surface-area choices
     size_t dps_pt = 0, dps_off = 0, dps_of = 0, dps_flag = 0, dps_blk = 0, dps_stat = 0, dps_recv = 0;  // point sets
@@ -68,7 +69,6 @@ void launch_visibility(const DevScene &S, const float *rx, uint32_t n_rx, const 
 void launch_recv_copy(const float4 *recv, uint32_t n, float *out, hipStream_t s);
 // Point sets: voxel keys, sort, set boundaries (after build_scene, reusing its sort buffers).
 hipError_t build_point_sets(const SceneLayout &L, char *ws, uint32_t n, float rho, hipStream_t s);
-hipError_t build_wide(const SceneLayout &L, char *ws, hipStream_t s, int broot, uint32_t *levels, uint32_t *nodes);
 hipError_t build_scene(const float *pos, const float *nrm, const uint16_t *mat, const uint32_t *surf, uint32_t n,
                        float r, uint32_t leaf, char *ws, const SceneLayout &L, hipStream_t s, uint32_t *wide_levels,
                        uint32_t *wide_nodes, int *root);
