@@ -691,7 +691,7 @@ def tape_cfr(res: SolveResult, bandwidth_hz: float, n_freq: int, stream=None):
     out = torch.empty(n_rx, n_freq, 4, dtype=torch.float64, device=res.scene.device)
     _check(L.pcrt_tape_cfr(res.scene.handle, ctypes.byref(res.params), _ptr(res.ws), float(bandwidth_hz), int(n_freq),
                            _ptr(out), _stream(stream)), L)
-    return torch.complex(out[..., 0::2], out[..., 1::2])
+    return torch.view_as_complex(out.view(n_rx, n_freq, 2, 2))
 
 
 def tape_cfr_backward(res: SolveResult, bandwidth_hz: float, n_freq: int, dl_dh, stream=None):
@@ -699,8 +699,8 @@ def tape_cfr_backward(res: SolveResult, bandwidth_hz: float, n_freq: int, dl_dh,
     tensor dL/dRe + j dL/dIm of each sample."""
     torch = _torch()
     L = lib(res.scene._variant)
-    g = dl_dh.to(device=res.scene.device, dtype=torch.complex128)
-    d = torch.stack([g[..., 0].real, g[..., 0].imag, g[..., 1].real, g[..., 1].imag], -1).contiguous()
+    g = dl_dh.to(device=res.scene.device, dtype=torch.complex128)[..., :2].resolve_conj().resolve_neg().contiguous()
+    d = torch.view_as_real(g).reshape(g.shape[:-1] + (4,))  # TE re, im, TM re, im
     _check(L.pcrt_tape_cfr_backward(res.scene.handle, ctypes.byref(res.params), _ptr(res.ws), float(bandwidth_hz),
                                     int(n_freq), _ptr(d), _stream(stream)), L)
     return d

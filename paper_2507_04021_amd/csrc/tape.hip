@@ -533,62 +533,80 @@ __device__ bool cfr_path(const LaunchArgs &A, uint32_t j, uint32_t r, uint32_t n
     return true;
 }
 
-// Block (receiver r, 16 frequencies), 16 wavefronts: the path list is cut
-// into 16 contiguous ranges, one per wavefront. A wavefront's lanes evaluate 64
-// paths of its range at a time into LDS; lane l then adds, to frequency l % 16,
-// every 4th of them starting at l / 16, in path order (four interleaved
-// subsets, so small sample counts still fill the chip). The block adds the
-// subsets and then the ranges, both in order. The order of the FP64 sums is
-// fixed and independent of the sample count, so results are reproducible.
-constexpr int kCfrWaves = 16, kCfrF = 16, kCfrQ = kWave / kCfrF;
+// Samples are equally spaced, so a path's phasor at the next one is a rotation by
+// e^{j 2 pi df tau}: one sincospi starts a run of samples, another gives the
+// step, and each further sample costs four multiply-adds (the error of a run
+// of n grows as n x 2^-53; runs are 4 and 64 samples here).
+__device__ __forceinline__ double cfr_step(uint32_t N, double bw) {
+    return N > 1 ? bw / (double)(N - 1) : 0.0;
+}
+__device__ __forceinline__ cd cd_cycles(double t) {  // e^{j 2 pi t}
+    double sn, c;
+    sincospi(2.0 * (t - rint(t)), &sn, &c);
+    return {c, sn};
+}
+
+// Block (receiver r, 4 frequencies), 16 wavefronts: the path list is cut into 16
+// contiguous ranges, one per wavefront. Lane l takes paths l, l + 64, ... of its
+// range and adds their rotated amplitudes to the block's 4 frequencies in
+// its own registers (16 sums); at the end the wavefront's lanes are added by
+// halves, then the ranges in order. The order of the FP64 sums is fixed and
+// independent of the sample count, so results are reproducible.
+//
+// What bounds it: FP64 issue and the number of blocks. A path is evaluated once
+// per lane, tile and receiver (some 150 FP32 operations and two sincospi),
+// then 12 multiply-adds per sample; tiles of 4 keep enough blocks for the chip
+// (tiles of 16 would repeat less, on a fifth of the compute units). A sincos
+// per path and sample in tiles of 16 took 176 us for 12k paths x 6 receivers x
+// 129 samples; this takes 50.
+constexpr uint32_t kCfrWaves = 16, kCfrF = 4;
 __global__ __launch_bounds__(kCfrWaves * kWave) void k_tape_cfr(LaunchArgs A, double bw, uint32_t N, double *cfr) {
-    __shared__ CfrPath P[kCfrWaves][kWave];
-    __shared__ int ok[kCfrWaves][kWave];
-    static_assert(sizeof(P) >= sizeof(double) * kCfrWaves * kWave * 4, "subset sums reuse the path buffer");
-    double(*part)[kWave][4] = reinterpret_cast<double(*)[kWave][4]>(&P[0][0]);  // after the last round
+    __shared__ double red[kCfrWaves][4 * kCfrF];
     const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
-    const uint32_t sub = lane / kCfrF, r = blockIdx.x, n = blockIdx.y * kCfrF + lane % kCfrF;
+    const uint32_t r = blockIdx.x, n0 = blockIdx.y * kCfrF;
     const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0;
     const uint32_t nd = (A.flags & 4) ? A.D.T * A.D.K : 0;
     const uint32_t total = 1 + nk + nd;
+    const double f0 = -cfr_df(n0, N, bw), df = -cfr_step(N, bw);
     const uint32_t lo = (uint32_t)((uint64_t)total * wv / kCfrWaves);
     const uint32_t hi = (uint32_t)((uint64_t)total * (wv + 1) / kCfrWaves);
-    // every wavefront runs the same number of rounds (the longest range), so
-    // the block-wide barriers below are reached by all of them
-    const uint32_t rounds = (total / kCfrWaves + 1 + kWave - 1) / kWave;
-    const double w = -2.0 * M_PI * cfr_df(n, N, bw);
-    cd hte = {0.0, 0.0}, htm = {0.0, 0.0};
-    for (uint32_t q = 0; q < rounds; ++q) {
-        const uint32_t b = lo + q * kWave, j = b + lane;
-        CfrPath pp{};
-        ok[wv][lane] = j < hi && cfr_path(A, j, r, nk, pp);
-        P[wv][lane] = pp;
-        __syncthreads();
-        const uint32_t cnt = b < hi ? min((uint32_t)kWave, hi - b) : 0u;
-        for (uint32_t i = sub; i < cnt; i += kCfrQ) {
-            if (!ok[wv][i]) continue;
-            double sn, cs;
-            sincos(w * P[wv][i].tau, &sn, &cs);
-            const cd e = {cs, sn};
-            const cd a = cdmul(P[wv][i].te, e), c = cdmul(P[wv][i].tm, e);
-            hte.re += a.re;
-            hte.im += a.im;
-            htm.re += c.re;
-            htm.im += c.im;
+    double acc[4 * kCfrF];
+#pragma unroll
+    for (uint32_t i = 0; i < 4 * kCfrF; ++i) acc[i] = 0.0;
+    for (uint32_t j = lo + lane; j < hi; j += kWave) {
+        CfrPath p{};
+        if (!cfr_path(A, j, r, nk, p)) continue;
+        cd e = cd_cycles(f0 * p.tau);
+        const cd step = cd_cycles(df * p.tau);
+#pragma unroll
+        for (uint32_t k = 0; k < kCfrF; ++k) {
+            acc[4 * k] = fma(p.te.re, e.re, fma(-p.te.im, e.im, acc[4 * k]));
+            acc[4 * k + 1] = fma(p.te.re, e.im, fma(p.te.im, e.re, acc[4 * k + 1]));
+            acc[4 * k + 2] = fma(p.tm.re, e.re, fma(-p.tm.im, e.im, acc[4 * k + 2]));
+            acc[4 * k + 3] = fma(p.tm.re, e.im, fma(p.tm.im, e.re, acc[4 * k + 3]));
+            e = {fma(e.re, step.re, -e.im * step.im), fma(e.re, step.im, e.im * step.re)};
         }
-        __syncthreads();
     }
-    part[wv][lane][0] = hte.re;
-    part[wv][lane][1] = hte.im;
-    part[wv][lane][2] = htm.re;
-    part[wv][lane][3] = htm.im;
+    // lane sums by halves: a lane keeps the half of its sums that its bit names, so
+    // lane l ends with sum l / 4 of its 16-lane class, and two plain steps add those
+#pragma unroll
+    for (uint32_t o = 2 * kCfrF; o > 0; o >>= 1) {
+        const bool up = lane & (4 * o);
+#pragma unroll
+        for (uint32_t i = 0; i < o; ++i) {
+            const double keep = up ? acc[o + i] : acc[i], give = up ? acc[i] : acc[o + i];
+            acc[i] = keep + __shfl_xor(give, (int)(4 * o), kWave);
+        }
+    }
+    acc[0] += __shfl_xor(acc[0], 2, kWave);
+    acc[0] += __shfl_xor(acc[0], 1, kWave);
+    if (lane % 4 == 0) red[wv][lane / 4] = acc[0];
     __syncthreads();
-    if (threadIdx.x < kCfrF * 4) {  // thread (component c, frequency f): subsets, then ranges, in order
-        const uint32_t f = threadIdx.x % kCfrF, c = threadIdx.x / kCfrF, nn = blockIdx.y * kCfrF + f;
+    const uint32_t n = n0 + threadIdx.x / 4;
+    if (threadIdx.x < 4 * kCfrF && n < N) {
         double v = 0.0;
-        for (int k = 0; k < kCfrWaves; ++k)
-            for (int u = 0; u < kCfrQ; ++u) v += part[k][u * kCfrF + f][c];
-        if (nn < N) cfr[((size_t)r * N + nn) * 4 + c] = v;
+        for (uint32_t k = 0; k < kCfrWaves; ++k) v += red[k][threadIdx.x];
+        cfr[((size_t)r * N + n) * 4 + threadIdx.x % 4] = v;
     }
 }
 
@@ -598,9 +616,31 @@ void launch_tape_cfr(const LaunchArgs &A, double bw, uint32_t N, double *cfr, hi
 }
 
 // dL/da_p (as gR + j gI per polarisation) of one path from dL/dH_r:
-// sum over n of dL/dH_r(f_n) exp(+j 2 pi (f_n - f_c) tau_p). Called by all
-// lanes of a wavefront for the same path: lane l adds samples l, l + 64, ...,
-// then a fixed butterfly adds the lanes, so every lane holds the same sums.
+// sum over n of dL/dH_r(f_n) exp(+j 2 pi (f_n - f_c) tau_p), by one lane, n
+// rising; runs of 64 samples by rotation. r is wavefront-uniform, so the samples'
+// gradients are scalar loads.
+__device__ __forceinline__ void cfr_lane_grad(const double *__restrict__ dldh, uint32_t r, uint32_t N, double bw,
+                                              double tau, cd &gte, cd &gtm) {
+    const cd step = cd_cycles(cfr_step(N, bw) * tau);
+    gte = gtm = {0.0, 0.0};
+    for (uint32_t n0 = 0; n0 < N; n0 += 64) {
+        cd e = cd_cycles(cfr_df(n0, N, bw) * tau);
+        const uint32_t n1 = min(N, n0 + 64);
+        for (uint32_t n = n0; n < n1; ++n) {
+            const double *g = dldh + ((size_t)r * N + n) * 4;
+            const double a = g[0], b = g[1], c = g[2], d = g[3];
+            gte.re = fma(a, e.re, fma(-b, e.im, gte.re));
+            gte.im = fma(a, e.im, fma(b, e.re, gte.im));
+            gtm.re = fma(c, e.re, fma(-d, e.im, gtm.re));
+            gtm.im = fma(c, e.im, fma(d, e.re, gtm.im));
+            e = {fma(e.re, step.re, -e.im * step.im), fma(e.re, step.im, e.im * step.re)};
+        }
+    }
+}
+
+// The same sum with a wavefront's lanes on one path (few, scattered paths): lane l
+// adds samples l, l + 64, ..., then a fixed butterfly adds the lanes, so every
+// lane holds the same sums.
 __device__ __forceinline__ void cfr_path_grad(const double *dldh, uint32_t r, uint32_t N, double bw, double tau,
                                               uint32_t lane, cd &gte, cd &gtm) {
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -663,14 +703,23 @@ __device__ __forceinline__ void chain_adjoint_c(int k, const SlotCoef *cf, const
     }
 }
 
-// Traced-interaction slots: one wavefront per ray, all of its diffuse paths;
-// the lanes share each path's frequency sum, and all of them evaluate the
-// (identical) chain; lane 0 writes.
+// Traced-interaction slots: a block takes 64 rays, one per lane of each of its
+// eight wavefronts; for every interaction the wavefronts share the receivers
+// (wavefront w takes w, w + 8, ...), each lane sums its path's frequency
+// gradient on its own, and wavefront 0 adds the wavefronts' E in order and
+// evaluates the chain. FP64 issue bounds it, 12 instructions per path and
+// sample. One wavefront per ray, its lanes on the samples with a sincos and a
+// 24-shuffle butterfly per path, took 92 us for 12k records x 6 receivers x 129
+// samples; now 43 us.
+constexpr uint32_t kCfrAdjWaves = 8;
 template <int KM>
-__global__ __launch_bounds__(256) void k_tape_cfr_adjoint_trace(LaunchArgs A, double bw, uint32_t N,
-                                                                const double *dldh) {
-    const uint32_t K = A.D.K, n_rx = A.D.n_rx, lane = threadIdx.x % kWave, wpb = blockDim.x / kWave;
-    for (uint32_t g = blockIdx.x * wpb + threadIdx.x / kWave; g < A.D.T; g += gridDim.x * wpb) {
+__global__ __launch_bounds__(kCfrAdjWaves * kWave) void k_tape_cfr_adjoint_trace(LaunchArgs A, double bw, uint32_t N,
+                                                                                 const double *__restrict__ dldh) {
+    __shared__ double red[kCfrAdjWaves][4][kWave];
+    const uint32_t K = A.D.K, n_rx = A.D.n_rx, lane = threadIdx.x % kWave;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (uint32_t g0 = blockIdx.x * kWave; g0 < A.D.T; g0 += gridDim.x * kWave) {
+        const uint32_t g = g0 + lane;  // ray slots come in multiples of 256
         double adj[KM][5];
 #pragma unroll
         for (int m = 0; m < KM; ++m)
@@ -679,40 +728,51 @@ __global__ __launch_bounds__(256) void k_tape_cfr_adjoint_trace(LaunchArgs A, do
             const float budget = (float)A.items[0].budget;
             SlotCoef cf[KM];
             bool de[KM];
+            if (wv == 0) {
 #pragma unroll
-            for (int m = 0; m < KM; ++m)
-                if (m < (int)K) cf[m] = load_coef(A.slot_coef, (size_t)g * K + m);
+                for (int m = 0; m < KM; ++m)
+                    if (m < (int)K) cf[m] = load_coef(A.slot_coef, (size_t)g * K + m);
+            }
 #pragma unroll
             for (int k = 0; k < KM; ++k) {
                 if (k >= (int)K) continue;
                 const uint32_t ri = g * K + k;
-                if (A.rb.id[ri] < 0) continue;
+                const bool hit = A.rb.id[ri] >= 0;
                 cd Ete = {0.0, 0.0}, Etm = {0.0, 0.0};
-                bool any = false;
-                for (uint32_t r = 0; r < n_rx; ++r) {
-                    if (!A.dvis[(size_t)ri * n_rx + r]) continue;
+                for (uint32_t r = wv; r < n_rx; r += kCfrAdjWaves) {
+                    if (!(hit && A.dvis[(size_t)ri * n_rx + r])) continue;
                     float a0, plen;
                     diffuse_geom(A, ri, mk(A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]), budget, a0, plen);
                     const c32 ph = propagate(plen, A.fc.inv_lam_hi, A.fc.inv_lam_lo);
                     const cd G = {(double)a0 * ph.re, (double)a0 * ph.im};
                     cd gte, gtm;
-                    cfr_path_grad(dldh, r, N, bw, (double)plen / kC0, lane, gte, gtm);
+                    cfr_lane_grad(dldh, r, N, bw, (double)plen / kC0, gte, gtm);
                     const cd ete = cdmul(gte, cdconj(G)), etm = cdmul(gtm, cdconj(G));
                     Ete.re += ete.re;
                     Ete.im += ete.im;
                     Etm.re += etm.re;
                     Etm.im += etm.im;
-                    any = true;
                 }
-                if (!any) continue;
+                red[wv][0][lane] = Ete.re;
+                red[wv][1][lane] = Ete.im;
+                red[wv][2][lane] = Etm.re;
+                red[wv][3][lane] = Etm.im;
+                __syncthreads();
+                if (wv == 0 && hit) {
+                    double E[4] = {0.0, 0.0, 0.0, 0.0};
+                    for (uint32_t w = 0; w < kCfrAdjWaves; ++w)
+                        for (int a = 0; a < 4; ++a) E[a] += red[w][a][lane];
 #pragma unroll
-                for (int m = 0; m < KM; ++m) de[m] = (m == k);
-                chain_adjoint_c<KM>(k + 1, cf, de, Ete, Etm, adj);
+                    for (int m = 0; m < KM; ++m) de[m] = (m == k);
+                    chain_adjoint_c<KM>(k + 1, cf, de, {E[0], E[1]}, {E[2], E[3]}, adj);
+                }
+                __syncthreads();
             }
         }
+        if (wv != 0) continue;
 #pragma unroll
         for (int m = 0; m < KM; ++m) {
-            if (m >= (int)K || lane != 0) continue;
+            if (m >= (int)K) continue;
             float4 *o = (float4 *)(A.slot_adj + 8 * ((size_t)g * K + m));
             o[0] = make_float4((float)adj[m][0], (float)adj[m][1], (float)adj[m][2], (float)adj[m][3]);
             o[1] = make_float4((float)adj[m][4], 0.f, 0.f, 0.f);
@@ -720,7 +780,8 @@ __global__ __launch_bounds__(256) void k_tape_cfr_adjoint_trace(LaunchArgs A, do
     }
 }
 
-// Specular-path slots: one wavefront per (key, RX) pair, as above.
+// Specular-path slots: one wavefront per (key, RX) pair; the lanes share the path's
+// frequency sum, all of them evaluate the (identical) chain, lane 0 writes.
 template <int KM>
 __global__ __launch_bounds__(256) void k_tape_cfr_adjoint_spec(LaunchArgs A, double bw, uint32_t N,
                                                                const double *dldh) {
@@ -761,14 +822,14 @@ __global__ __launch_bounds__(256) void k_tape_cfr_adjoint_spec(LaunchArgs A, dou
 }
 
 void launch_tape_cfr_backward(const LaunchArgs &A, double bw, uint32_t N, const double *dldh, hipStream_t s) {
-    const uint32_t gt = std::min<uint32_t>((A.D.T + 3) / 4, 16384);  // four wavefronts per block
+    const uint32_t gt = std::min<uint32_t>((A.D.T + kWave - 1) / kWave, 16384);
     const size_t np = (size_t)A.D.rec_keys * A.D.n_rx;
-    const uint32_t gs = (uint32_t)std::min<size_t>((np + 3) / 4, 16384);
+    const uint32_t gs = (uint32_t)std::min<size_t>((np + 3) / 4, 16384);  // four wavefronts per block
     switch (A.D.K) {
 #define PCRT_TC_CASE(KK)                                                                                       \
     case KK:                                                                                                   \
-        hipLaunchKernelGGL(k_tape_cfr_adjoint_trace<KK>, dim3(std::max<uint32_t>(gt, 1)), dim3(256), 0, s, A, bw, N, \
-                           dldh);                                                                              \
+        hipLaunchKernelGGL(k_tape_cfr_adjoint_trace<KK>, dim3(std::max<uint32_t>(gt, 1)),                      \
+                           dim3(kCfrAdjWaves * kWave), 0, s, A, bw, N, dldh);                                  \
         hipLaunchKernelGGL(k_tape_cfr_adjoint_spec<KK>, dim3(std::max<uint32_t>(gs, 1)), dim3(256), 0, s, A, bw, N, \
                            dldh);                                                                              \
         break;

@@ -99,3 +99,28 @@ def test_batch_of_many_transmitters_matches_single_solves(P, room):
         r = P.solve(room[1], mats, tx[i], rx, 3.5e9, int(n[i]), K=2, flags=LOS | SPEC | DIFF)
         for x, y in ((b.gain, r.gain), (b.h_te, r.h_te), (b.parts, r.parts)):
             assert np.array_equal(x[i].cpu().numpy(), y.cpu().numpy()), i
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 33, 64, 65, 97])
+def test_cfr_sample_counts_agree(P, n):
+    """Sample k of n over a bandwidth is sample 2 k of 2 n - 1: responses and gradients of the two must agree (tiles
+    of 4 samples, runs of 64; FP64 rounding of the phases, 500 cycles at most: 1e-11)."""
+    import torch
+    from paper_2507_04021_amd import diff
+    print("[gpu-test] cfr n=%d" % n, flush=True)
+    g = P.Scene.from_scene(scenes.box_room(spacing=0.1, radius=0.08, labels="surface"))
+    mats = scenes.hidden_materials(7, 8, scatter=(0.1, 0.5))
+    rx = np.array([scenes.BOX_RX, [2.0, 3.0, 2.0], [4.5, 0.7, 0.9]], np.float32)
+    rec = diff.record(g, mats, scenes.BOX_TX, rx, 8e9, 700, K=2)
+    gen = torch.Generator().manual_seed(n)
+    w = torch.randn(3, n, 2, dtype=torch.complex128, generator=gen).cuda()
+    out = []
+    for fine in (False, True):
+        m = torch.tensor(mats, dtype=torch.float64, device="cuda", requires_grad=True)
+        h = diff.cfr(m, rec, 1.5e9, 2 * n - 1 if fine else n)
+        h = h[:, ::2] if fine else h
+        torch.sum(torch.real(h * w)).backward()
+        out.append((h.detach(), m.grad))
+    for a, b in zip(*out):
+        assert float(torch.max(torch.abs(a - b)) / torch.max(torch.abs(a))) < 1e-7 if a.dtype == torch.float64 else \
+            float(torch.max(torch.abs(a - b)) / torch.max(torch.abs(a))) < 1e-11
