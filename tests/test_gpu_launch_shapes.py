@@ -124,3 +124,65 @@ def test_cfr_sample_counts_agree(P, n):
     for a, b in zip(*out):
         assert float(torch.max(torch.abs(a - b)) / torch.max(torch.abs(a))) < 1e-7 if a.dtype == torch.float64 else \
             float(torch.max(torch.abs(a - b)) / torch.max(torch.abs(a))) < 1e-11
+
+
+@pytest.mark.parametrize("n,n_labels", [(1, 1), (127, 8), (128, 16), (129, 17), (2049, 64), (32769, 8)])
+def test_mlp_gradients_at_the_edges_of_a_block(P, n, n_labels):
+    """A block takes 128 rows at a time, at most 256 blocks do, and labels are taken 16 at a time. The bar is that of
+    the kernel against the reference at its rounding points: (2^-8 + n 2^-24) of the sum of |terms|."""
+    import torch
+    from oracle import mlp as R
+    from paper_2507_04021_amd import mlp as M
+    rng = np.random.default_rng(n)
+    params = R.init_params(n_labels, seed=3)
+    labels = rng.integers(0, n_labels, n)
+    cosv = rng.uniform(0.0, 1.0, n).astype(np.float32)
+    g_out = rng.normal(size=(n, 8)).astype(np.float32)
+    g_out[:, 5:] = 0
+    net = M.MaterialMLP(params)
+    lab, cs = torch.tensor(labels.astype(np.int16), device="cuda"), torch.tensor(cosv, device="cuda")
+    grads = net.backward_rows(lab, cs, 28e9, torch.tensor(g_out, device="cuda"))
+    ref, mag = R.backward(params, labels, cosv.astype(np.float64), 28e9, g_out[:, :5], precision="kernel",
+                          magnitudes=True)
+    for k, v in ref.items():
+        got = grads[k].cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - v) <= (2.0 ** -8 + n * 2.0 ** -24) * mag[k]), k
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_mlp_row_without_a_finite_gradient_reaches_its_own_label_only(P, bad):
+    import torch
+    from oracle import mlp as R
+    from paper_2507_04021_amd import mlp as M
+    params = R.init_params(20, seed=4)
+    net = M.MaterialMLP(params)
+    n = 200
+    labels = np.arange(n) % 20
+    g = np.ones((n, 8), np.float32)
+    lab = torch.tensor(labels.astype(np.int16), device="cuda")
+    cs = torch.linspace(0, 1, n, device="cuda")
+    ref = net.backward_rows(lab, cs, 28e9, torch.tensor(g, device="cuda"))["emb"].cpu().numpy()
+    g[37, 0] = bad
+    got = net.backward_rows(lab, cs, 28e9, torch.tensor(g, device="cuda"))["emb"].cpu().numpy()
+    assert not np.isfinite(got[17]).any()
+    keep = np.arange(20) != 17
+    # the same sums in another order: 10 rows of a label, each addition off by at most 2^-24 of the sum of |terms|
+    g[37, 0] = 1
+    _, mag = R.backward(params, labels, cs.cpu().numpy().astype(np.float64), 28e9, g[:, :5], precision="kernel",
+                        magnitudes=True)
+    assert np.all(np.abs(got - ref)[keep] <= 20 * 2.0 ** -24 * mag["emb"][keep])
+
+
+def test_mlp_forward_rows_do_not_depend_on_the_batch(P):
+    """Few rows take one tile per wavefront, many take eight: a row's outputs are bitwise the same."""
+    import torch
+    from oracle import mlp as R
+    from paper_2507_04021_amd import mlp as M
+    net = M.MaterialMLP(R.init_params(8, seed=5))
+    n = 300_000
+    lab = torch.tensor((np.arange(n) * 7 % 9).astype(np.int16), device="cuda")
+    cs = torch.rand(n, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    big, small = torch.zeros(n, 8, device="cuda"), torch.zeros(1000, 8, device="cuda")
+    net.forward_rows(lab, cs, 28e9, big)
+    net.forward_rows(lab[:1000], cs[:1000], 28e9, small)
+    assert torch.equal(big[:1000], small)
