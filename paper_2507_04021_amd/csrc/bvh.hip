@@ -17,15 +17,26 @@ namespace pcrt {
 // Validates and normalises each point; writes the by-id tables and the
 // per-block bounds of disk centres. status bits: 1 non-finite position,
 // 2 zero or non-finite normal.
-__global__ void k_ingest(const float *__restrict__ pos, const float *__restrict__ nrm,
-                         const uint16_t *__restrict__ mat, const uint32_t *__restrict__ surf, uint32_t n,
-                         float4 *__restrict__ pos_id, float4 *__restrict__ nrm_id, float *__restrict__ blk_bounds,
-                         uint32_t *__restrict__ stat) {
-    __shared__ float red[6][256];
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    uint32_t bad = 0, ms = 0, mm = 0;
-    if (i < n) {
+__device__ __forceinline__ void max_to(uint32_t v, uint32_t *to) {  // (looks first: most blocks add nothing)
+    if (v > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(to, v);
+}
+
+// A block takes kIngest points: an atomic on one word costs 11 ns whoever issues it, and one per
+// wavefront and statistic was nearly all of the 0.36 ms this took for 1M points (now 0.022; 68 MB read and written,
+// 0.014 at the rate of a large copy).
+constexpr uint32_t kIngest = 1024;
+__global__ __launch_bounds__(256) void k_ingest(const float *__restrict__ pos, const float *__restrict__ nrm,
+                                                const uint16_t *__restrict__ mat, const uint32_t *__restrict__ surf,
+                                                uint32_t n, float4 *__restrict__ pos_id, float4 *__restrict__ nrm_id,
+                                                float *__restrict__ blk_bounds, uint32_t *__restrict__ stat) {
+    __shared__ float red[6][4];
+    __shared__ uint32_t redi[3][4];
+    float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    uint32_t st[3] = {0, 0, 0};  // bad, largest surface, largest material
+    for (uint32_t k = 0; k < kIngest / 256; ++k) {
+        const uint32_t i = blockIdx.x * kIngest + k * 256 + threadIdx.x;
+        if (i >= n) break;
+        uint32_t bad = 0;
         float px = pos[3 * i], py = pos[3 * i + 1], pz = pos[3 * i + 2];
         float nx = nrm[3 * i], ny = nrm[3 * i + 1], nz = nrm[3 * i + 2];
         if (!(isfinite(px) && isfinite(py) && isfinite(pz))) bad |= 1;
@@ -33,41 +44,43 @@ __global__ void k_ingest(const float *__restrict__ pos, const float *__restrict_
         if (!(l2 > 0.f) || !isfinite(l2)) bad |= 2;
         float il = bad & 2 ? 0.f : 1.0f / sqrtf(l2);
         uint32_t s = surf[i], m = mat[i];
-        ms = s;
-        mm = m;
         pos_id[i] = make_float4(px, py, pz, __uint_as_float(s));
         nrm_id[i] = make_float4(nx * il, ny * il, nz * il, __uint_as_float(m));
+        st[0] |= bad;
+        st[1] = max(st[1], s);
+        st[2] = max(st[2], m);
         if (!bad) {
-            lo[0] = hi[0] = px;
-            lo[1] = hi[1] = py;
-            lo[2] = hi[2] = pz;
+            const float p[3] = {px, py, pz};
+            for (int a = 0; a < 3; ++a) {
+                b[a] = fminf(b[a], p[a]);
+                b[3 + a] = fmaxf(b[3 + a], p[a]);
+            }
         }
     }
-    for (int a = 0; a < 3; ++a) {
-        red[a][threadIdx.x] = lo[a];
-        red[3 + a][threadIdx.x] = hi[a];
-    }
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int a = 0; a < 3; ++a) {
-                red[a][threadIdx.x] = fminf(red[a][threadIdx.x], red[a][threadIdx.x + s]);
-                red[3 + a][threadIdx.x] = fmaxf(red[3 + a][threadIdx.x], red[3 + a][threadIdx.x + s]);
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int a = 0; a < 6; ++a) blk_bounds[6 * blockIdx.x + a] = red[a][0];
-    // one atomic per wavefront (one per point took 0.36 ms of a 1M-point build, this 0.02)
     for (int o = 32; o > 0; o >>= 1) {
-        bad |= __shfl_xor(bad, o, kWave);
-        ms = max(ms, (uint32_t)__shfl_xor(ms, o, kWave));
-        mm = max(mm, (uint32_t)__shfl_xor(mm, o, kWave));
+        for (int a = 0; a < 3; ++a) {
+            b[a] = fminf(b[a], __shfl_xor(b[a], o, kWave));
+            b[3 + a] = fmaxf(b[3 + a], __shfl_xor(b[3 + a], o, kWave));
+        }
+        st[0] |= __shfl_xor(st[0], o, kWave);
+        st[1] = max(st[1], (uint32_t)__shfl_xor(st[1], o, kWave));
+        st[2] = max(st[2], (uint32_t)__shfl_xor(st[2], o, kWave));
     }
     if (threadIdx.x % kWave == 0) {
+        for (int a = 0; a < 6; ++a) red[a][threadIdx.x / kWave] = b[a];
+        for (int a = 0; a < 3; ++a) redi[a][threadIdx.x / kWave] = st[a];
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        const float *r = red[threadIdx.x];
+        blk_bounds[6 * blockIdx.x + threadIdx.x] =
+            threadIdx.x < 3 ? fminf(fminf(r[0], r[1]), fminf(r[2], r[3])) : fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
+    }
+    if (threadIdx.x == 64) {
+        const uint32_t bad = redi[0][0] | redi[0][1] | redi[0][2] | redi[0][3];
         if (bad) atomicOr(&stat[0], bad);
-        atomicMax(&stat[1], ms);
-        atomicMax(&stat[2], mm);
+        max_to(max(max(redi[1][0], redi[1][1]), max(redi[1][2], redi[1][3])), &stat[1]);
+        max_to(max(max(redi[2][0], redi[2][1]), max(redi[2][2], redi[2][3])), &stat[2]);
     }
 }
 
@@ -372,11 +385,12 @@ __device__ __forceinline__ uint64_t tile_prefix(uint64_t *status, uint32_t tile,
     return before;
 }
 
-// Exclusive prefix of v (two 31-bit counts) over the launch's 256-thread tiles;
-// total: the inclusive prefix of this tile.
+// Exclusive prefix of v (two 31-bit counts) over the launch's tiles of 64 kWaves
+// threads; total: the inclusive prefix of this tile.
+template <uint32_t kWaves>
 __device__ __forceinline__ uint64_t tiles_scan(uint64_t *status, uint32_t tile, uint64_t v, uint64_t &total,
                                                uint32_t *fail) {
-    __shared__ uint64_t part[5];
+    __shared__ uint64_t part[kWaves + 1];
     const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     uint64_t in = v;
     for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
@@ -385,15 +399,16 @@ __device__ __forceinline__ uint64_t tiles_scan(uint64_t *status, uint32_t tile, 
     }
     if (lane == kWave - 1) part[w] = in;
     __syncthreads();
-    const uint64_t all = part[0] + part[1] + part[2] + part[3];
+    uint64_t all = 0;
+    for (uint32_t i = 0; i < kWaves; ++i) all += part[i];
     if (w == 0) {
         const uint64_t b = tile_prefix(status, tile, all, fail);
-        if (lane == 0) part[4] = b;
+        if (lane == 0) part[kWaves] = b;
     }
     __syncthreads();
-    uint64_t before = part[4];
+    uint64_t before = part[kWaves];
     for (uint32_t i = 0; i < w; ++i) before += part[i];
-    total = part[4] + all;
+    total = part[kWaves] + all;
     __syncthreads();
     return before + in - v;
 }
@@ -441,52 +456,54 @@ __device__ __forceinline__ int ploc_nearest(const float (&bx)[6][N], int l, int 
     return bj;
 }
 
-// One clustering pass in one launch: a block loads the boxes of its 256
-// clusters and 2 kPlocRadius on either side, finds the nearest neighbours of
-// its own and of those within kPlocRadius (so it knows which pairs are
-// mutual), and writes merged and kept clusters at their scanned places. A
-// launch covers at least the pass's m clusters; blocks beyond them end at
-// once. Ten launches and a host round trip per pass before: 51 passes of a
-// 1M-point build 3.6 -> 0.5 ms, with the tail below.
-__global__ __launch_bounds__(256) void k_ploc_pass(Clusters in, float *__restrict__ obox, int *__restrict__ oid,
-                                                   uint32_t *__restrict__ osize, PassBufs B, uint32_t pass,
-                                                   int2 *__restrict__ child, uint32_t *__restrict__ nsize,
-                                                   float *__restrict__ ibox) {
-    constexpr int R = kPlocRadius, N = 256 + 4 * R;
+// One clustering pass in one launch: a block loads the boxes of its
+// kPlocTile clusters and 2 kPlocRadius on either side, finds the nearest
+// neighbours of its own and of those within kPlocRadius (one per thread; so it
+// knows which pairs are mutual), and writes merged and kept clusters at their
+// scanned places. A launch covers at least the pass's m clusters; blocks
+// beyond them end at once, without a ticket (11 ns each). Ten launches and a
+// host round trip per pass took 3.6 ms for the 51 passes of a 1M-point build;
+// this 0.69 with tiles of 256 clusters, 0.46 with these, and the tail below 0.06.
+constexpr int kPlocThreads = 1024, kPlocTile = kPlocThreads - 2 * kPlocRadius;
+__global__ __launch_bounds__(kPlocThreads) void k_ploc_pass(Clusters in, float *__restrict__ obox,
+                                                            int *__restrict__ oid, uint32_t *__restrict__ osize,
+                                                            PassBufs B, uint32_t pass, int2 *__restrict__ child,
+                                                            uint32_t *__restrict__ nsize, float *__restrict__ ibox) {
+    constexpr int R = kPlocRadius, N = kPlocThreads + 2 * R;
     __shared__ float bx[6][N];
-    __shared__ int nn[256 + 2 * R];
+    __shared__ int nn[kPlocThreads];
     __shared__ uint32_t tile_s;
     pass_clear(B, pass);
+    const uint32_t m = B.st[pass].m, node_base = B.st[pass].base;
+    if ((uint64_t)blockIdx.x * kPlocTile >= m) return;
     if (threadIdx.x == 0) tile_s = atomicAdd(&B.ticket[pass & 1], 1u);
     __syncthreads();
-    const uint32_t tile = tile_s, m = B.st[pass].m, node_base = B.st[pass].base;
-    if ((uint64_t)tile * 256 >= m) return;
-    const int t0 = (int)(tile * 256);  // bx[.][l] is cluster t0 + l - 2R, nn[l] that of cluster t0 + l - R
-    for (int i = (int)threadIdx.x; i < 6 * N; i += 256) {
+    const uint32_t tile = tile_s;
+    if ((uint64_t)tile * kPlocTile >= m) return;
+    const int t0 = (int)(tile * kPlocTile);  // bx[.][l] is cluster t0 + l - 2R, nn[l] and thread l cluster t0 + l - R
+    for (int i = (int)threadIdx.x; i < 6 * N; i += kPlocThreads) {
         const int l = i / 6, a = i % 6, g = t0 + l - 2 * R;
         if (g >= 0 && g < (int)m) bx[a][l] = in.box[6 * (size_t)g + a];
     }
     __syncthreads();
-    for (int l = (int)threadIdx.x; l < 256 + 2 * R; l += 256) {
-        const int g = t0 + l - R;
-        if (g < 0 || g >= (int)m) continue;
-        const int lo = max(0, g - R) - t0 + 2 * R, hi = min((int)m - 1, g + R) - t0 + 2 * R;
-        const int j = ploc_nearest<N>(bx, l + R, lo, hi);
-        nn[l] = j < 0 ? -1 : j + t0 - 2 * R;
+    const int i = t0 + (int)threadIdx.x - R;
+    if (i >= 0 && i < (int)m) {
+        const int lo = max(0, i - R) - t0 + 2 * R, hi = min((int)m - 1, i + R) - t0 + 2 * R;
+        const int j = ploc_nearest<N>(bx, (int)threadIdx.x + R, lo, hi);
+        nn[threadIdx.x] = j < 0 ? -1 : j + t0 - 2 * R;
     }
     __syncthreads();
-    const int i = t0 + (int)threadIdx.x;
-    const bool ok = i < (int)m;
-    const int j = ok ? nn[threadIdx.x + R] : -1;
+    const bool ok = (int)threadIdx.x >= R && (int)threadIdx.x < kPlocThreads - R && i < (int)m;
+    const int j = ok ? nn[threadIdx.x] : -1;
     const bool mutual = j >= 0 && nn[j - t0 + R] == i;
     const bool merge = mutual && i < j, keep = ok && !(mutual && i > j);
     uint64_t total;
-    const uint64_t at = tiles_scan(B.status[pass & 1], tile, (uint64_t)keep | (uint64_t)merge << 31, total, B.ticket + 3);
+    const uint64_t at = tiles_scan<kPlocThreads / kWave>(B.status[pass & 1], tile, (uint64_t)keep | (uint64_t)merge << 31, total, B.ticket + 3);
     const uint32_t p = (uint32_t)at & 0x7fffffffu;
-    if (tile == (m - 1) / 256 && threadIdx.x == 0)
+    if (tile == (m - 1) / kPlocTile && threadIdx.x == 0)
         B.st[pass + 1] = {(uint32_t)total & 0x7fffffffu, node_base + (uint32_t)(total >> 31)};
     if (!keep) return;
-    const int l = (int)threadIdx.x + 2 * R;
+    const int l = (int)threadIdx.x + R;
     if (!merge) {
         for (int a = 0; a < 6; ++a) obox[6 * (size_t)p + a] = bx[a][l];
         oid[p] = in.id ? in.id[i] : ~i;
@@ -592,10 +609,9 @@ __global__ __launch_bounds__(kPlocTail) void k_ploc_tail(Clusters in, PassBufs B
 }
 
 // Depth-first offsets and depths, one creation pass at a time from the root's
-// down (a node's parent is always created in a later pass). Returns the depth
-// of the node's leaf children (its internal ancestors), 0 if it has none.
-__device__ __forceinline__ uint32_t dfs_node(uint32_t node, const int2 *child, const uint32_t *nsize, uint32_t *noff,
-                                             uint32_t *ndepth, uint32_t *leaf_pos) {
+// down (a node's parent is always created in a later pass).
+__device__ __forceinline__ void dfs_node(uint32_t node, const int2 *child, const uint32_t *nsize, uint32_t *noff,
+                                         uint32_t *ndepth, uint32_t *leaf_pos) {
     const uint32_t o = noff[node], d = ndepth[node];
     const int2 c = child[node];
     const uint32_t sa = c.x < 0 ? 1u : nsize[c.x];
@@ -609,38 +625,29 @@ __device__ __forceinline__ uint32_t dfs_node(uint32_t node, const int2 *child, c
         noff[c.y] = o + sa;
         ndepth[c.y] = d + 1;
     }
-    return c.x < 0 || c.y < 0 ? d : 0u;
-}
-
-__device__ __forceinline__ void wave_max_to(uint32_t v, uint32_t *to) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor(v, o, kWave));
-    if (threadIdx.x % kWave == 0 && v) atomicMax(to, v);
 }
 
 __global__ __launch_bounds__(256) void k_dfs_pass(const int2 *child, const uint32_t *nsize, uint32_t lo, uint32_t hi,
-                                                  uint32_t *noff, uint32_t *ndepth, uint32_t *leaf_pos,
-                                                  uint32_t *depth) {
+                                                  uint32_t *noff, uint32_t *ndepth, uint32_t *leaf_pos) {
     const uint32_t node = lo + blockIdx.x * 256 + threadIdx.x;
-    wave_max_to(node < hi ? dfs_node(node, child, nsize, noff, ndepth, leaf_pos) : 0u, depth);
+    if (node < hi) dfs_node(node, child, nsize, noff, ndepth, leaf_pos);
 }
 
-// The passes from p0 on (each of a few thousand nodes at most) in one block,
+// The passes from p0 on (each of at most kTopNodes nodes) in one block,
 // which starts at the root.
 __global__ __launch_bounds__(1024) void k_dfs_top(const PassState *st, uint32_t p0, uint32_t p1, const int2 *child,
                                                   const uint32_t *nsize, uint32_t *noff, uint32_t *ndepth,
-                                                  uint32_t *leaf_pos, uint32_t *depth) {
+                                                  uint32_t *leaf_pos) {
     if (threadIdx.x == 0) {
         noff[st[p1].base - 1] = 0;
         ndepth[st[p1].base - 1] = 1;
     }
     __syncthreads();
-    uint32_t d = 0;
     for (uint32_t p = p1; p-- > p0;) {
         for (uint32_t node = st[p].base + threadIdx.x; node < st[p + 1].base; node += 1024)
-            d = max(d, dfs_node(node, child, nsize, noff, ndepth, leaf_pos));
+            dfs_node(node, child, nsize, noff, ndepth, leaf_pos);
         __syncthreads();
     }
-    wave_max_to(d, depth);
 }
 
 __global__ void k_dfs_leaves(uint32_t n, const uint32_t *__restrict__ leaf_pos, const uint32_t *__restrict__ sorted_id,
@@ -650,15 +657,29 @@ __global__ void k_dfs_leaves(uint32_t n, const uint32_t *__restrict__ leaf_pos, 
     perm[leaf_pos[i]] = sorted_id[i];
 }
 
-__global__ void k_dfs_nodes(uint32_t n_int, const uint32_t *__restrict__ leaf_pos, const uint32_t *__restrict__ noff,
-                            const uint32_t *__restrict__ nsize, int2 *__restrict__ child, int2 *__restrict__ range) {
-    const uint32_t node = blockIdx.x * blockDim.x + threadIdx.x;
-    if (node >= n_int) return;
-    int2 c = child[node];
-    if (c.x < 0) c.x = ~(int)leaf_pos[~c.x];
-    if (c.y < 0) c.y = ~(int)leaf_pos[~c.y];
-    child[node] = c;
-    range[node] = make_int2((int)noff[node], (int)(noff[node] + nsize[node] - 1));
+// References to leaves and ranges, and the depth of the deepest leaf (a node's depth counts the node and its
+// ancestors): a maximum per block of kDfsNodes, as an atomic per wavefront and pass made up most of the passes above.
+constexpr uint32_t kDfsNodes = 1024;
+__global__ __launch_bounds__(256) void k_dfs_nodes(uint32_t n_int, const uint32_t *__restrict__ leaf_pos,
+                                                   const uint32_t *__restrict__ noff, const uint32_t *__restrict__ nsize,
+                                                   const uint32_t *__restrict__ ndepth, int2 *__restrict__ child,
+                                                   int2 *__restrict__ range, uint32_t *depth) {
+    __shared__ uint32_t red[4];
+    uint32_t d = 0;
+    for (uint32_t k = 0; k < kDfsNodes / 256; ++k) {
+        const uint32_t node = blockIdx.x * kDfsNodes + k * 256 + threadIdx.x;
+        if (node >= n_int) break;
+        int2 c = child[node];
+        if (c.x < 0 || c.y < 0) d = max(d, ndepth[node]);
+        if (c.x < 0) c.x = ~(int)leaf_pos[~c.x];
+        if (c.y < 0) c.y = ~(int)leaf_pos[~c.y];
+        child[node] = c;
+        range[node] = make_int2((int)noff[node], (int)(noff[node] + nsize[node] - 1));
+    }
+    for (int o = 32; o > 0; o >>= 1) d = max(d, (uint32_t)__shfl_xor(d, o, kWave));
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) max_to(max(max(red[0], red[1]), max(red[2], red[3])), depth);
 }
 
 // --------------------------------------------------------- wide nodes
@@ -768,7 +789,7 @@ __device__ __forceinline__ void sah_node(const float4 *__restrict__ bnode, int n
 // Trees whose nodes are numbered by creation pass (the clustering builder): a
 // node's children were created in earlier passes, so the rows are filled pass
 // by pass, without the climb's atomics and device-scope fences (1M points:
-// 2.76 -> 0.12 ms). Nodes inside a collapsed leaf get rows that nobody reads.
+// 2.76 -> 0.14 ms). Nodes inside a collapsed leaf get rows that nobody reads.
 template <int W>
 __global__ __launch_bounds__(256) void k_sah_pass(const float4 *__restrict__ bnode, uint32_t lo, uint32_t hi,
                                                   float *cost, uint8_t *choice) {
@@ -895,7 +916,7 @@ __global__ __launch_bounds__(256) void k_wide_level(const float4 *__restrict__ b
             for (int j = 0; j < c; ++j) k += sl[j].ref >= 0;
         }
         uint64_t total;
-        k = (uint32_t)tiles_scan(B.status[level & 1], tile, k, total, B.ticket + 3);
+        k = (uint32_t)tiles_scan<4>(B.status[level & 1], tile, k, total, B.ticket + 3);
         if (tile == (nf - 1) / 256 && threadIdx.x == 0) B.st[level + 1] = {(uint32_t)total, base_next};
         float *o = wnode + (size_t)(base_cur + i) * 8 * W;
         for (int j = 0; j < (i < nf ? W : 0); ++j) {
@@ -1102,7 +1123,7 @@ static hipError_t read_back(void *to, const void *from, size_t bytes, hipStream_
 // reads the cluster count every few passes (a launch sized for an older
 // count only starts blocks that end at once), then hands the tail over.
 constexpr uint32_t kPlocBatch = 4;      // passes between two looks at the count
-constexpr uint32_t kTopNodes = 4096;    // passes of at most so many nodes share one block's launch
+constexpr uint32_t kTopNodes = 1024;    // passes of at most so many nodes share one block's launch
 
 // First of the last passes that one block goes through (later passes are smaller
 // or of the same order; at least the root's is among them).
@@ -1134,7 +1155,7 @@ hipError_t build_ploc(const SceneLayout &L, char *ws, uint32_t n, const uint32_t
     while (st.back().m > (uint32_t)kPlocTail) {
         const uint32_t m = st.back().m;
         for (uint32_t k = 0; k < kPlocBatch; ++k, ++pass)
-            hipLaunchKernelGGL(k_ploc_pass, dim3(cdiv(m, 256)), dim3(256), 0, s, clusters(pass), cbox[(pass + 1) & 1],
+            hipLaunchKernelGGL(k_ploc_pass, dim3(cdiv(m, kPlocTile)), dim3(kPlocThreads), 0, s, clusters(pass), cbox[(pass + 1) & 1],
                                cid[(pass + 1) & 1], csz[(pass + 1) & 1], B, pass, child, nsize, ibox);
         st.resize(pass + 1);
         const hipError_t e = read_back(&st[pass + 1 - kPlocBatch], B.st + pass + 1 - kPlocBatch,
@@ -1155,14 +1176,14 @@ hipError_t build_ploc(const SceneLayout &L, char *ws, uint32_t n, const uint32_t
     if (st[last].m != 1 || st[last].base != n - 1) return hipErrorUnknown;  // a pass merged nothing
     *root = (int)(n - 2);
     const uint32_t p0 = top_pass(st);
-    hipLaunchKernelGGL(k_dfs_top, dim3(1), dim3(1024), 0, s, B.st, p0, last, child, nsize, noff, ndepth, leaf_pos, depth);
+    hipLaunchKernelGGL(k_dfs_top, dim3(1), dim3(1024), 0, s, B.st, p0, last, child, nsize, noff, ndepth, leaf_pos);
     for (uint32_t p = p0; p-- > 0;)
         hipLaunchKernelGGL(k_dfs_pass, dim3(cdiv(st[p + 1].base - st[p].base, 256)), dim3(256), 0, s, child, nsize,
-                           st[p].base, st[p + 1].base, noff, ndepth, leaf_pos, depth);
+                           st[p].base, st[p + 1].base, noff, ndepth, leaf_pos);
     hipLaunchKernelGGL(k_dfs_leaves, dim3(cdiv(n, 256)), dim3(256), 0, s, n, leaf_pos, sorted_id,
                        (uint32_t *)P(L.perm2));
-    hipLaunchKernelGGL(k_dfs_nodes, dim3(cdiv(n - 1, 256)), dim3(256), 0, s, n - 1, leaf_pos, noff, nsize, child,
-                       range);
+    hipLaunchKernelGGL(k_dfs_nodes, dim3(cdiv(n - 1, kDfsNodes)), dim3(256), 0, s, n - 1, leaf_pos, noff, nsize, ndepth,
+                       child, range, depth);
     return hipGetLastError();
 }
 
@@ -1243,8 +1264,9 @@ hipError_t build_scene(const float *pos, const float *nrm, const uint16_t *mat, 
     uint32_t *hist = (uint32_t *)P(L.hist);
     uint32_t blk = cdiv(n, 256);
     fill_u32(stat, 0, (L.ticket - L.stat) / 4 + 4, s);
-    hipLaunchKernelGGL(k_ingest, dim3(blk), dim3(256), 0, s, pos, nrm, mat, surf, n, pos_id, nrm_id, blkb, stat);
-    hipLaunchKernelGGL(k_bounds, dim3(1), dim3(256), 0, s, blkb, blk, bounds);
+    const uint32_t iblk = cdiv(n, kIngest);
+    hipLaunchKernelGGL(k_ingest, dim3(iblk), dim3(256), 0, s, pos, nrm, mat, surf, n, pos_id, nrm_id, blkb, stat);
+    hipLaunchKernelGGL(k_bounds, dim3(1), dim3(256), 0, s, blkb, iblk, bounds);
     hipLaunchKernelGGL(k_morton, dim3(blk), dim3(256), 0, s, pos_id, n, bounds, c0, i0);
     const bool in_tmp = radix_sort_u64(c0, i0, c1, i1, n, 0, 64, hist, (uint32_t *)P(L.scan_blk), s);
     if (in_tmp) {
