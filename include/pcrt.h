@@ -130,7 +130,7 @@ pcrt_status pcrt_scene_destroy(pcrt_scene *scene);
  * float[n_point_sets][3]. Errors: EINVAL without point sets or NULL pointers. */
 pcrt_status pcrt_reception_points(const pcrt_scene *scene, float *out, void *stream);
 
-/* Device workspace of pcrt_visibility (traversal stack spill; >= 256 bytes). */
+/* Device workspace of pcrt_visibility (traversal stack spill and work counters; >= 256 bytes). */
 pcrt_status pcrt_visibility_workspace_size(const pcrt_scene *scene, size_t *bytes);
 
 /* Visibility matrix: vis[r][j] = 1 when receiver r sees reception point j,

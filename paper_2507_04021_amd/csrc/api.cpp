@@ -589,10 +589,12 @@ static size_t visibility_spill_bytes(const pcrt_scene *sc) {
     const uint32_t depth = sc->info.stack_entries > (uint32_t)kStackLds ? sc->info.stack_entries - kStackLds : 0;
     return sizeof(int) * (size_t)depth * visibility_grid(sc->info.width) * kWave;
 }
+// then a counter of work units per XCD (64 B each)
+static size_t visibility_ws(const pcrt_scene *sc) { return visibility_spill_bytes(sc) + 64 * kXcds; }
 
 pcrt_status pcrt_visibility_workspace_size(const pcrt_scene *scene, size_t *bytes) {
     if (!scene || !bytes) return fail(PCRT_EINVAL, "scene and bytes are required");
-    *bytes = std::max<size_t>(256, visibility_spill_bytes(scene));
+    *bytes = visibility_ws(scene);
     return ok();
 }
 
@@ -602,7 +604,7 @@ pcrt_status pcrt_visibility(const pcrt_scene *scene, const float *rx, uint32_t n
     if (!scene->dev.dps_pt) return fail(PCRT_EINVAL, "the scene has no point sets (dps_voxel = 0)");
     if (n_rx == 0) return fail(PCRT_EINVAL, "n_rx must be > 0");
     if (!(eps_self >= 0.f) || !std::isfinite(eps_self)) return fail(PCRT_EINVAL, "eps_self must be >= 0");
-    const size_t need = std::max<size_t>(256, visibility_spill_bytes(scene));
+    const size_t need = visibility_ws(scene);
     if (ws_bytes < need) return fail(PCRT_ENOMEM, "visibility workspace too small: need %zu bytes", need);
     if ((uint64_t)n_rx * scene->info.n_point_sets > 0xffffffffull)
         return fail(PCRT_EUNSUPPORTED, "n_rx x point sets must stay below 2^32");
@@ -610,7 +612,8 @@ pcrt_status pcrt_visibility(const pcrt_scene *scene, const float *rx, uint32_t n
     S.spill = (int *)ws;
     S.spill_lanes = visibility_grid(scene->info.width) * kWave;
     launch_visibility(S, rx, n_rx, (const float4 *)(scene->ws + scene->L.dps_recv), scene->info.n_point_sets,
-                      eps_self > 0.f ? eps_self : 1e-3f, vis, (hipStream_t)stream);
+                      eps_self > 0.f ? eps_self : 1e-3f, vis,
+                      (uint32_t *)((char *)ws + visibility_spill_bytes(scene)), (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return ok();
 }

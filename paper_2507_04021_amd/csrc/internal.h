@@ -65,7 +65,7 @@ void launch_diffraction(const DevScene &S, const pcrt_edge *edges, uint32_t n_ed
 // Visibility of the point sets' reception points from receivers (one uint8 per pair).
 uint32_t visibility_grid(uint32_t width);
 void launch_visibility(const DevScene &S, const float *rx, uint32_t n_rx, const float4 *recv, uint32_t n_sets,
-                       float eps_self, uint8_t *out, hipStream_t s);
+                       float eps_self, uint8_t *out, uint32_t *taken, hipStream_t s);
 void launch_recv_copy(const float4 *recv, uint32_t n, float *out, hipStream_t s);
 // Point sets: voxel keys, sort, set boundaries (after build_scene, reusing its sort buffers).
 hipError_t build_point_sets(const SceneLayout &L, char *ws, uint32_t n, float rho, hipStream_t s);

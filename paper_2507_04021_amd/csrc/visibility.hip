@@ -9,51 +9,64 @@
 // started together share their start and their path through the upper tree.
 // Walks are resumable with ballot-compacted refill, as in the diffuse
 // connections: the wavefront steps its walking lanes until at most a quarter
-// of its busy lanes still walk, then hands the idle lanes the chunk's next
-// sets in lane order. Each output byte is written by the lane that decided
-// it, so the result does not depend on the schedule. On the office's 64 x
-// 181 523 matrix: 2.65 ms with one 64-set batch per unit and no refill,
-// 1.7 ms with refill over 1024-set units. Persistent
-// single-wavefront blocks; the blocks of XCD x work through the x-th eighth
-// of the (set chunk, receiver) units, receiver-minor, so one XCD's L2 serves
-// one region of the scene.
+// of its busy lanes still walk, then hands the idle lanes the next sets in
+// lane order, from the next unit when one is handed out (every lane has its
+// own receiver, so a wavefront is never drained between units). Each output
+// byte is written by the lane that decided it, so the result does not depend
+// on the schedule. Persistent single-wavefront blocks; the blocks of XCD x
+// take the x-th eighth of the (set chunk, receiver) units, receiver-minor, so
+// one XCD's L2 serves one region of the scene, each unit from a counter per
+// XCD (`taken`): walks of one unit take several times as long as another's,
+// and dealt in advance, with a drain at the end of each of its one or two units,
+// the slowest wavefront set the time. On the office's 64 x 181 523 matrix: 2.65 ms
+// with one 64-set batch per unit and no refill, 2.2 ms with refill over
+// 1024-set units dealt in advance, 1.63 ms so.
 #include "common.h"
 #include "internal.h"
 
 namespace pcrt {
 
-constexpr uint32_t kVisChunk = 1024;  // sets per work unit (office: 128 / 256 / 512 / 1024 / 2048 ->
-                                      // 2.65 / 2.16 / 2.0 / 1.7 / 1.89 ms)
+constexpr uint32_t kVisChunk = 128;  // sets per work unit (office, scene build included: 64 / 128 / 256 / 512 / 1024 ->
+                                     // 3.67 / 3.68 / 3.72 / 3.80 / 4.03 ms)
 constexpr int kVisRefillShift = 2;    // refill once at most busy / 4 lanes still walk
 
 template <int W>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 4 : 6, 8))) void k_visibility(
     DevScene S, const float *__restrict__ rx, uint32_t n_rx, const float4 *__restrict__ recv, uint32_t n_sets,
-    float eps_self, uint8_t *__restrict__ out, uint32_t share) {
+    float eps_self, uint8_t *__restrict__ out, uint32_t share, uint32_t *__restrict__ taken) {
     __shared__ int lds_stack[kStackLds * kWave];
     const int lane = threadIdx.x;
     const uint32_t glane = blockIdx.x * kWave + lane;
     Stack stk{lds_stack + lane, S.spill + glane, S.spill_lanes};
     const uint32_t n_units = (n_sets + kVisChunk - 1) / kVisChunk * n_rx;
-    const uint32_t xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds, i = blockIdx.x / kXcds;
-    for (uint32_t k = i; k < share; k += nb) {
-        const uint32_t u = xcd * share + k;
-        if (u >= n_units) break;
-        const uint32_t c = u / n_rx, r = u % n_rx;
-        const f3 a = mk(rx[3 * r], rx[3 * r + 1], rx[3 * r + 2]);
-        const uint32_t j0 = c * kVisChunk, j1 = min(n_sets, j0 + kVisChunk);
-        uint32_t next = j0;                   // next set of the chunk to hand out (wave-uniform)
-        bool walking = false, hit = false;
-        uint32_t j = 0;
-        int ref = kNoRef, sp = 0, park = kNoRef;  // kNoRef / kNoRef whenever the lane is not walking
-        f3 d = mk(0.f, 0.f, 1.f), inv = mk(1.f, 1.f, 1.f), oi = mk(0.f, 0.f, 0.f);
-        float t_hi = 0.f;
-        Octant oq = octant<W>(inv);
-        for (;;) {
-            const uint64_t idle = __ballot(!walking);
+    const uint32_t xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
+    const uint32_t end = n_units > xcd * share ? min(share, n_units - xcd * share) : 0;  // units of this XCD
+    uint32_t t = blockIdx.x / kXcds - nb;   // lane 0: the unit to take next, less nb (the first of each wavefront are dealt)
+    uint32_t next = 0, j1 = 0, r = 0;       // the current unit's next and last set, its receiver (wave-uniform)
+    bool walking = false, hit = false;
+    f3 a = mk(0.f, 0.f, 0.f);
+    size_t o = 0;
+    uint32_t j = 0;
+    int ref = kNoRef, sp = 0, park = kNoRef;  // kNoRef / kNoRef whenever the lane is not walking
+    f3 d = mk(0.f, 0.f, 1.f), inv = mk(1.f, 1.f, 1.f), oi = mk(0.f, 0.f, 0.f);
+    float t_hi = 0.f;
+    Octant oq = octant<W>(inv);
+    for (;;) {
+        for (uint64_t idle = __ballot(!walking); idle; idle = __ballot(!walking)) {
+            if (next >= j1) {  // the unit is handed out: the next one
+                const uint32_t k = nb + __builtin_amdgcn_readfirstlane(t);
+                if (k >= end) break;
+                const uint32_t u = xcd * share + k, c = u / n_rx;
+                r = u % n_rx;
+                next = c * kVisChunk;
+                j1 = min(n_sets, next + kVisChunk);
+                if (lane == 0) t = atomicAdd(&taken[16 * xcd], 1u);  // (used at the next unit: no wait here)
+            }
             const uint32_t avail = min(j1 - next, (uint32_t)__popcll(idle));
             if (!walking && mbcnt(idle) < avail) {
                 j = next + mbcnt(idle);
+                o = (size_t)r * n_sets + j;
+                a = mk(rx[3 * r], rx[3 * r + 1], rx[3 * r + 2]);
                 // the set-up of occluded(a, recv[j]), walked from the receiver
                 const f3 dv = xyz(recv[j]) - a;
                 const float L = len(dv);
@@ -69,48 +82,48 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
                 walking = true;
             }
             next += avail;
-            const uint32_t n_busy = (uint32_t)__popcll(__ballot(walking));
-            if (n_busy == 0) break;  // the chunk's sets are all decided
-            uint32_t n_walk = n_busy;
+        }
+        const uint32_t n_busy = (uint32_t)__popcll(__ballot(walking));
+        if (n_busy == 0) break;  // nothing left
+        uint32_t n_walk = n_busy;
+        for (;;) {
             for (;;) {
-                for (;;) {
-                    if (ref < 0 && ref != kNoRef && park == kNoRef) {
-                        park = ref;
+                if (ref < 0 && ref != kNoRef && park == kNoRef) {
+                    park = ref;
+                    ref = sp > 0 ? stk.get(--sp) : kNoRef;
+                }
+                const uint32_t n_park = (uint32_t)__popcll(__ballot(park != kNoRef));
+                if (!__ballot(ref >= 0) || 2 * n_park >= n_walk) break;
+                if (ref >= 0) {
+                    stk.visit();
+                    if (!step_any<W>(S, ref, sp, oq, inv, oi, eps_self, t_hi, stk))
                         ref = sp > 0 ? stk.get(--sp) : kNoRef;
-                    }
-                    const uint32_t n_park = (uint32_t)__popcll(__ballot(park != kNoRef));
-                    if (!__ballot(ref >= 0) || 2 * n_park >= n_walk) break;
-                    if (ref >= 0) {
-                        stk.visit();
-                        if (!step_any<W>(S, ref, sp, oq, inv, oi, eps_self, t_hi, stk))
-                            ref = sp > 0 ? stk.get(--sp) : kNoRef;
-                    }
                 }
-                if (park != kNoRef) {
-                    const int v = -1 - park;
-                    const int first = v >> 3, cnt = (v & 7) + 1;
-                    stk.test(cnt);
-                    for (int q = 0; q < cnt; ++q) {
-                        const float4 dp = ld4(S.disk, (uint32_t)(first + q) * 32u);
-                        const float4 dn = ld4(S.disk, (uint32_t)(first + q) * 32u + 16u);
-                        float t, d2;
-                        const bool h = disk_hit(a, d, xyz(dp), xyz(dn), S.r2, t, d2);
-                        if (h & (__float_as_int(dn.w) != (int)j) & (t > eps_self) & (t < t_hi)) {
-                            hit = true;
-                            break;
-                        }
-                    }
-                    park = kNoRef;
-                    if (hit) ref = kNoRef;
-                }
-                const bool done = walking && ref == kNoRef && park == kNoRef;
-                if (done) {
-                    out[(size_t)r * n_sets + j] = hit ? 0 : 1;
-                    walking = false;
-                }
-                n_walk = (uint32_t)__popcll(__ballot(walking));
-                if (n_walk == 0 || (n_walk << kVisRefillShift) <= n_busy) break;
             }
+            if (park != kNoRef) {
+                const int v = -1 - park;
+                const int first = v >> 3, cnt = (v & 7) + 1;
+                stk.test(cnt);
+                for (int q = 0; q < cnt; ++q) {
+                    const float4 dp = ld4(S.disk, (uint32_t)(first + q) * 32u);
+                    const float4 dn = ld4(S.disk, (uint32_t)(first + q) * 32u + 16u);
+                    float th, d2;
+                    const bool h = disk_hit(a, d, xyz(dp), xyz(dn), S.r2, th, d2);
+                    if (h & (__float_as_int(dn.w) != (int)j) & (th > eps_self) & (th < t_hi)) {
+                        hit = true;
+                        break;
+                    }
+                }
+                park = kNoRef;
+                if (hit) ref = kNoRef;
+            }
+            const bool done = walking && ref == kNoRef && park == kNoRef;
+            if (done) {
+                out[o] = hit ? 0 : 1;
+                walking = false;
+            }
+            n_walk = (uint32_t)__popcll(__ballot(walking));
+            if (n_walk == 0 || (n_walk << kVisRefillShift) <= n_busy) break;
         }
     }
 }
@@ -127,17 +140,18 @@ uint32_t visibility_grid(uint32_t width) {
 }
 
 void launch_visibility(const DevScene &S, const float *rx, uint32_t n_rx, const float4 *recv, uint32_t n_sets,
-                       float eps_self, uint8_t *out, hipStream_t s) {
+                       float eps_self, uint8_t *out, uint32_t *taken, hipStream_t s) {
+    fill_u32(taken, 0, 16 * kXcds, s);
     const uint32_t grid = visibility_grid((uint32_t)S.width);
     const uint32_t n_units = (n_sets + kVisChunk - 1) / kVisChunk * n_rx;
     const uint32_t share = (n_units + kXcds - 1) / kXcds;
     switch (S.width) {
         case 8: hipLaunchKernelGGL(k_visibility<8>, dim3(grid), dim3(kWave), 0, s, S, rx, n_rx, recv, n_sets, eps_self,
-                                   out, share); break;
+                                   out, share, taken); break;
         case 4: hipLaunchKernelGGL(k_visibility<4>, dim3(grid), dim3(kWave), 0, s, S, rx, n_rx, recv, n_sets, eps_self,
-                                   out, share); break;
+                                   out, share, taken); break;
         default: hipLaunchKernelGGL(k_visibility<2>, dim3(grid), dim3(kWave), 0, s, S, rx, n_rx, recv, n_sets,
-                                    eps_self, out, share); break;
+                                    eps_self, out, share, taken); break;
     }
 }
 
