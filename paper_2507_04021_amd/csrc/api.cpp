@@ -586,7 +586,7 @@ pcrt_status pcrt_scene_create(const pcrt_points *pts, const pcrt_bvh_opts *opts,
 }
 
 static size_t visibility_spill_bytes(const pcrt_scene *sc) {
-    const uint32_t depth = sc->info.stack_entries > (uint32_t)kStackLds ? sc->info.stack_entries - kStackLds : 0;
+    const uint32_t depth = sc->info.stack_entries > (uint32_t)kStackLdsVisibility ? sc->info.stack_entries - kStackLdsVisibility : 0;
     return sizeof(int) * (size_t)depth * visibility_grid(sc->info.width) * kWave;
 }
 // then a counter of work units per XCD (64 B each)

@@ -12,6 +12,9 @@ namespace pcrt {
 constexpr int kMaxK = 8;          // max interactions per path
 constexpr int kWave = 64;         // wavefront width
 constexpr int kStackLds = 23;     // traversal stack entries kept in LDS per lane (5.75 KiB per wavefront)
+// ... of the visibility matrix: 5 KiB, so 32 of its wavefronts (64 registers) share a compute unit's 160 KiB. Scan of the
+// 1M-point office: 3.66 ms with 23 entries, 3.58 with 20, 3.60 with 16.
+constexpr int kStackLdsVisibility = 20;
 constexpr int kStackMax = 96;     // max stack entries (LDS + global spill)
 constexpr int kRayChunk = 256;    // rays per diffuse reduction chunk (item ray ranges are padded to this);
                                    // office connections: 128 -> 30.3 ms, 256 -> 29.8, 512 -> 30.7
@@ -70,7 +73,7 @@ struct DevScene {
     const float4 *nrm;   // by id: (n.xyz, material bits)
     const float *bounds; // scene bounds of the disk centres: lo xyz, hi xyz
     int width;           // node width: 2 (binary nodes, 64 B) or 4 / 8 (wide nodes, 32 W bytes)
-    int *spill;          // global spill of traversal stacks, [stack bound - kStackLds][spill_lanes]
+    int *spill;          // global spill of traversal stacks, [stack bound - entries in LDS][spill_lanes]
     uint32_t spill_lanes;
     int root;
     float r2;
@@ -101,11 +104,13 @@ struct Item {  // one transmitter of a (batched) solve, 32 B
 };
 
 // ---------------------------------------------------- traversal stack
-// Entries 0..kStackLds-1 live in LDS ([depth][lane] so lanes hit distinct
+// Entries 0..N-1 live in LDS ([depth][lane] so lanes hit distinct
 // banks); deeper entries spill to a per-lane global region.
-struct Stack {
+template <int N>
+struct StackOf {
+    static constexpr int kLds = N;
     int *lds;        // this lane's column base: lds[s * kWave]
-    int *gl;         // this lane's spill column base: gl[(s - kStackLds) * lanes]
+    int *gl;         // this lane's spill column base: gl[(s - N) * lanes]
     uint32_t lanes;
     uint32_t nv = 0, nd = 0;  // node visits, disk tests (instrumented builds only)
     __device__ __forceinline__ void visit() {
@@ -115,18 +120,19 @@ struct Stack {
         if (kCountVisits) nd += n;
     }
     __device__ __forceinline__ void put(int s, int v) {
-        if (s < kStackLds) lds[s * kWave] = v;
-        else gl[(size_t)(s - kStackLds) * lanes] = v;
+        if (s < N) lds[s * kWave] = v;
+        else gl[(size_t)(s - N) * lanes] = v;
     }
     __device__ __forceinline__ int get(int s) const {
         // The LDS read is always in bounds; the global read only for spilled
         // entries (keeps the common pop an LDS access, not a generic one).
-        int v = lds[min(s, kStackLds - 1) * kWave];
+        int v = lds[min(s, N - 1) * kWave];
         __asm__ volatile("" : "+v"(v));  // opaque use: the LDS read stays a read of its own
-        if (s >= kStackLds) v = gl[(size_t)(s - kStackLds) * lanes];
+        if (s >= N) v = gl[(size_t)(s - N) * lanes];
         return v;
     }
 };
+using Stack = StackOf<kStackLds>;
 
 // Rank of this lane among the lanes set in a ballot mask (lanes below it).
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
@@ -385,9 +391,9 @@ __device__ __forceinline__ bool wide_step(const DevScene &S, int &ref, int &sp, 
 // Any-hit step at a wide node: only the nearest entered child is singled out
 // (walked next); the other entered children are pushed in slot order. The
 // order cannot change an any-hit answer, only how soon it is found.
-template <int W>
+template <int W, class St>
 __device__ __forceinline__ bool wide_step_any(const DevScene &S, int &ref, int &sp, const Octant &q, f3 inv, f3 oi,
-                                              float t_lo, float t_hi, Stack &stk) {
+                                              float t_lo, float t_hi, St &stk) {
     float tn[W];
     int cr[W];
     wide_hits<W>(S, ref, q, inv, oi, t_lo, t_hi, tn, cr);
@@ -403,7 +409,7 @@ __device__ __forceinline__ bool wide_step_any(const DevScene &S, int &ref, int &
     int nref = cr[0];
 #pragma unroll
     for (int j = 1; j < W; ++j) nref = jb == j ? cr[j] : nref;
-    if (sp + (W - 1) <= kStackLds) {  // every push lands in LDS: no spill test per push
+    if (sp + (W - 1) <= St::kLds) {  // every push lands in LDS: no spill test per push
 #pragma unroll
         for (int j = 0; j < W; ++j)
             if (tn[j] < INFINITY && j != jb) stk.lds[(sp++) * kWave] = cr[j];
@@ -419,9 +425,9 @@ __device__ __forceinline__ bool wide_step_any(const DevScene &S, int &ref, int &
 // Any-hit step at a node of either layout: true if a child was entered (ref
 // is then that child, the other entered children are on the stack), false
 // if the segment enters none.
-template <int W>
+template <int W, class St>
 __device__ __forceinline__ bool step_any(const DevScene &S, int &ref, int &sp, const Octant &oq, f3 inv, f3 oi,
-                                         float t_lo, float t_hi, Stack &stk) {
+                                         float t_lo, float t_hi, St &stk) {
     if constexpr (W > 2) {
         return wide_step_any<W>(S, ref, sp, oq, inv, oi, t_lo, t_hi, stk);
     } else {
@@ -459,8 +465,8 @@ constexpr int kNoRef = -0x7fffffff - 1;
 // disk tests: the walk order, and so the stack bound, are those of the plain
 // depth-first walk, and the answer is the same.
 // excl: a disk id, or with BY_SET a point set whose disks are all ignored.
-template <int W, bool BY_SET = false>
-__device__ __forceinline__ bool occluded(const DevScene &S, f3 a, f3 b, int excl, float eps_self, Stack &stk) {
+template <int W, bool BY_SET = false, class St>
+__device__ __forceinline__ bool occluded(const DevScene &S, f3 a, f3 b, int excl, float eps_self, St &stk) {
     const f3 dv = b - a;
     const float L = len(dv);
     const f3 d = (1.0f / L) * dv;
@@ -639,7 +645,8 @@ __device__ __forceinline__ uint32_t warp_sum_u(uint32_t v) {
 }
 
 // Instrumented builds: add this lane's visit counts to counters[slot], [slot+1].
-__device__ __forceinline__ void flush_visits(const Stack &stk, uint64_t *counters, int slot) {
+template <class St>
+__device__ __forceinline__ void flush_visits(const St &stk, uint64_t *counters, int slot) {
     if (!kCountVisits) return;
     uint64_t v = stk.nv, d = stk.nd;
     for (int o = 32; o > 0; o >>= 1) {

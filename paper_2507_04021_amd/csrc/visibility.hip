@@ -34,10 +34,10 @@ template <int W>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 4 : 6, 8))) void k_visibility(
     DevScene S, const float *__restrict__ rx, uint32_t n_rx, const float4 *__restrict__ recv, uint32_t n_sets,
     float eps_self, uint8_t *__restrict__ out, uint32_t share, uint32_t *__restrict__ taken) {
-    __shared__ int lds_stack[kStackLds * kWave];
+    __shared__ int lds_stack[kStackLdsVisibility * kWave];
     const int lane = threadIdx.x;
     const uint32_t glane = blockIdx.x * kWave + lane;
-    Stack stk{lds_stack + lane, S.spill + glane, S.spill_lanes};
+    StackOf<kStackLdsVisibility> stk{lds_stack + lane, S.spill + glane, S.spill_lanes};
     const uint32_t n_units = (n_sets + kVisChunk - 1) / kVisChunk * n_rx;
     const uint32_t xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
     const uint32_t end = n_units > xcd * share ? min(share, n_units - xcd * share) : 0;  // units of this XCD
