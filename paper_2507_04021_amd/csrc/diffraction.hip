@@ -8,8 +8,9 @@
 // The geometry, the coefficient and the amplitude are evaluated in FP64 (a
 // few thousand pairs; the shadow and reflection boundary terms cancel poles
 // against zeros, which FP32 would resolve poorly); the visibility walks are
-// the FP32 any-hit walks of the diffuse connections, one lane per pair, the
-// lanes of a wavefront sharing the receiver.
+// the FP32 any-hit walks of the diffuse connections. A pair is a serial chain
+// (geometry, walks, transition functions: about 60 us of latency), so few
+// pairs take four lanes each, many one; the lanes of a wavefront share the receiver.
 #include "common.h"
 #include "internal.h"
 
@@ -66,10 +67,15 @@ __device__ z64 transition_fn(double x) {
     if (x < 20.0) {
         const double u = sqrt(x);
         z64 a = {u, 0.0}, sum = {u, 0.0};
-        for (int m = 1; m < 200; ++m) {
-            a = zscale(zmul(a, {0.0, -1.0}), x / m);  // a_m = a_{m-1} (-j) x / m
-            sum = zadd(sum, zscale(a, 1.0 / (2 * m + 1)));
-            if (m > x && hypot(a.re, a.im) < 1e-18 * hypot(sum.re, sum.im)) break;
+        // four terms between two looks at the size of the last (the quotients then overlap)
+        for (int m0 = 1; m0 < 200; m0 += 4) {
+#pragma unroll
+            for (int m = m0; m < m0 + 4; ++m) {
+                a = zscale(zmul(a, {0.0, -1.0}), x / m);  // a_m = a_{m-1} (-j) x / m
+                sum = zadd(sum, zscale(a, 1.0 / (2 * m + 1)));
+            }
+            const double mag = fabs(a.re) + fabs(a.im);  // (one of them is zero)
+            if (m0 > x && mag * mag < 1e-36 * (sum.re * sum.re + sum.im * sum.im)) break;
         }
         const double h = 0.5 * sqrt(kPi) * 0.70710678118654752440;  // sqrt(pi)/2 * cos(pi/4)
         const z64 tail = {h - sum.re, -h - sum.im};
@@ -79,7 +85,7 @@ __device__ z64 transition_fn(double x) {
     double prev = 1.0;
     for (int m = 1; m < 60; ++m) {
         const z64 nt = zmul(t, {0.0, (2.0 * m - 1.0) / (2.0 * x)});  // t_m = t_{m-1} (2m-1) j / (2x)
-        const double mag = hypot(nt.re, nt.im);
+        const double mag = fabs(nt.re) + fabs(nt.im);  // (one of them is zero)
         if (mag >= prev || mag < 1e-18) break;
         t = nt;
         prev = mag;
@@ -138,14 +144,19 @@ struct DiffArgs {
     float4 *amp;  // [n_rx][n_edges]: TE re, im, TM re, im (0 where no path)
 };
 
-template <int W>
+// kL = 1: a lane per pair. kL = 4: four lanes per pair; the pair's two visibility
+// walks run side by side and every lane takes one of the four terms of the
+// coefficient (the serial chain of a pair: FP64 geometry, two walks, four
+// transition functions). Its stacks are whole in LDS, so it needs no spill columns beyond the one-lane kernel's.
+template <int W, int kL>
 __global__ __launch_bounds__(kWave) void k_diffraction(DiffArgs A) {
-    __shared__ int lds_stack[kStackLds * kWave];
-    const int lane = threadIdx.x;
+    constexpr int kEntries = kL == 1 ? kStackLds : kStackMax;
+    __shared__ int lds_stack[kEntries * kWave];
+    const int lane = threadIdx.x, sub = lane % kL, lead = lane - sub;
     const uint32_t glane = blockIdx.x * kWave + lane;
-    Stack stk{lds_stack + lane, A.S.spill + glane, A.S.spill_lanes};
-    const uint32_t p = glane;
-    if (p >= A.n_rx * A.n_edges) return;
+    StackOf<kEntries> stk{lds_stack + lane, A.S.spill + (kL == 1 ? glane : 0u), A.S.spill_lanes};
+    const uint32_t p = glane / kL;
+    if (p >= A.n_rx * A.n_edges) return;  // (all lanes of a pair together)
     const uint32_t r = p / A.n_edges, i = p % A.n_edges;
     const pcrt_edge E = A.edges[i];
     float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -168,42 +179,77 @@ __global__ __launch_bounds__(kWave) void k_diffraction(DiffArgs A) {
     const d3 D = dadd(a, dmul(t, ev));
     const d3 vi = dsub(tx, D), vo = dsub(rx, D);
     const double sp = dlen(vi), s = dlen(vo);
-    const double phip = wedge_angle(vi, e, t0, n0), phi = wedge_angle(vo, e, t0, n0);
+    // value v of the pair's lane q
+    auto of = [&](double v, int q) { return kL == 1 ? v : __shfl(v, lead + q, kWave); };
+    double phip, phi;
+    if (kL == 1) {
+        phip = wedge_angle(vi, e, t0, n0);
+        phi = wedge_angle(vo, e, t0, n0);
+    } else {
+        const double ph = wedge_angle(sub & 1 ? vo : vi, e, t0, n0);
+        phip = of(ph, 0);
+        phi = of(ph, 1);
+    }
     ok = ok && sp > 0.0 && s > 0.0 && phip > 0.0 && phip < n * kPi && phi > 0.0 && phi < n * kPi;
-    if (ok) {  // both ends see the edge point (segments cut short by trim at the edge)
-        const d3 ui = dmul(1.0 / sp, vi), uo = dmul(1.0 / s, vo);
-        const d3 ci = dadd(D, dmul(A.trim, ui)), co = dadd(D, dmul(A.trim, uo));
-        ok = !occluded<W>(A.S, mk((float)tx.x, (float)tx.y, (float)tx.z), mk((float)ci.x, (float)ci.y, (float)ci.z),
-                          -1, A.eps_self, stk);
-        ok = ok && !occluded<W>(A.S, mk((float)rx.x, (float)rx.y, (float)rx.z),
-                                mk((float)co.x, (float)co.y, (float)co.z), -1, A.eps_self, stk);
-        if (ok) {
-            const double sin_b0 = dlen(dcross(ui, e));
-            const double kL = A.k * s * sp * sin_b0 * sin_b0 / (s + sp);
-            const double bm = phi - phip, bp = phi + phip;
-            const z64 f1 = utd_term(bm, n, kL, +1.0), f2 = utd_term(bm, n, kL, -1.0);
-            const z64 f3 = utd_term(bp, n, kL, -1.0), f4 = utd_term(bp, n, kL, +1.0);
-            const uint32_t l0 = min((uint32_t)E.label0, A.n_labels - 1), ln = min((uint32_t)E.label1, A.n_labels - 1);
-            z64 r0te, r0tm, rnte, rntm;
+    // both ends see the edge point (segments cut short by trim at the edge)
+    const d3 ui = dmul(1.0 / sp, vi), uo = dmul(1.0 / s, vo);
+    auto blocked = [&](d3 from, d3 u) {
+        const d3 c = dadd(D, dmul(A.trim, u));
+        return occluded<W>(A.S, mk((float)from.x, (float)from.y, (float)from.z),
+                           mk((float)c.x, (float)c.y, (float)c.z), -1, A.eps_self, stk);
+    };
+    if (kL == 1) {
+        ok = ok && !blocked(tx, ui);
+        ok = ok && !blocked(rx, uo);
+    } else {
+        bool hit = false;
+        if (ok && sub < 2) hit = blocked(sub ? rx : tx, sub ? uo : ui);
+        const uint64_t m = __ballot(hit);
+        ok = ok && !((m >> lead) & 3u);
+    }
+    if (ok) {  // (alike in all lanes of a pair)
+        const double sin_b0 = dlen(dcross(ui, e));
+        const double kLen = A.k * s * sp * sin_b0 * sin_b0 / (s + sp);
+        const double bm = phi - phip, bp = phi + phip;
+        const uint32_t l0 = min((uint32_t)E.label0, A.n_labels - 1), ln = min((uint32_t)E.label1, A.n_labels - 1);
+        z64 f[4], r0te, r0tm, rnte, rntm;
+        if (kL == 1) {
+            f[0] = utd_term(bm, n, kLen, +1.0);
+            f[1] = utd_term(bm, n, kLen, -1.0);
+            f[2] = utd_term(bp, n, kLen, -1.0);
+            f[3] = utd_term(bp, n, kLen, +1.0);
             face_gamma(A.mats[3 * l0], A.mats[3 * l0 + 1] * A.inv_we0, sin(phip), r0te, r0tm);
             face_gamma(A.mats[3 * ln], A.mats[3 * ln + 1] * A.inv_we0, sin(n * kPi - phi), rnte, rntm);
-            const z64 pre = zscale(zexpj(-kPi / 4.0), -1.0 / (2.0 * n * sqrt(2.0 * kPi * A.k) * sin_b0));
-            const z64 common = zadd(f1, f2);
-            const z64 dte = zmul(pre, zadd(common, zadd(zmul(r0te, f3), zmul(rnte, f4))));
-            const z64 dtm = zmul(pre, zadd(common, zadd(zmul(r0tm, f3), zmul(rntm, f4))));
-            const z64 base = zscale(zexpj(-A.k * (sp + s)), A.lam / (4.0 * kPi) / sp * sqrt(sp / (s * (s + sp))));
-            const z64 ate = zmul(base, dte), atm = zmul(base, dtm);
-            out = make_float4((float)ate.re, (float)ate.im, (float)atm.re, (float)atm.im);
+        } else {
+            const z64 mine = utd_term(sub < 2 ? bm : bp, n, kLen, sub == 0 || sub == 3 ? 1.0 : -1.0);
+            for (int q = 0; q < 4; ++q) f[q] = {of(mine.re, q), of(mine.im, q)};
+            const uint32_t l = sub & 1 ? ln : l0;
+            z64 te, tm;
+            face_gamma(A.mats[3 * l], A.mats[3 * l + 1] * A.inv_we0, sin(sub & 1 ? n * kPi - phi : phip), te, tm);
+            r0te = {of(te.re, 0), of(te.im, 0)};
+            r0tm = {of(tm.re, 0), of(tm.im, 0)};
+            rnte = {of(te.re, 1), of(te.im, 1)};
+            rntm = {of(tm.re, 1), of(tm.im, 1)};
         }
+        const z64 pre = zscale(zexpj(-kPi / 4.0), -1.0 / (2.0 * n * sqrt(2.0 * kPi * A.k) * sin_b0));
+        const z64 common = zadd(f[0], f[1]);
+        const z64 dte = zmul(pre, zadd(common, zadd(zmul(r0te, f[2]), zmul(rnte, f[3]))));
+        const z64 dtm = zmul(pre, zadd(common, zadd(zmul(r0tm, f[2]), zmul(rntm, f[3]))));
+        const z64 base = zscale(zexpj(-A.k * (sp + s)), A.lam / (4.0 * kPi) / sp * sqrt(sp / (s * (s + sp))));
+        const z64 ate = zmul(base, dte), atm = zmul(base, dtm);
+        out = make_float4((float)ate.re, (float)ate.im, (float)atm.re, (float)atm.im);
     }
-    A.amp[(size_t)r * A.n_edges + i] = out;
+    if (sub == 0) A.amp[(size_t)r * A.n_edges + i] = out;
 }
 
-// Per receiver, the paths in edge order (FP64): G, h_TE re, im, h_TM re, im.
-__global__ void k_diffraction_sum(const float4 *amp, uint32_t n_edges, uint32_t n_rx, double *out) {
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < n_rx; r += gridDim.x * blockDim.x) {
+// Per receiver (a wavefront), the paths (FP64): G, h_TE re, im, h_TM re, im. Lane l adds
+// edges l, l + 64, ... in order, one fixed butterfly the lanes. (One lane per receiver, in order: 22 us for 64 receivers
+// and 160 edges.)
+__global__ __launch_bounds__(kWave) void k_diffraction_sum(const float4 *amp, uint32_t n_edges, uint32_t n_rx,
+                                                           double *out) {
+    for (uint32_t r = blockIdx.x; r < n_rx; r += gridDim.x) {
         double acc[5] = {0, 0, 0, 0, 0};
-        for (uint32_t i = 0; i < n_edges; ++i) {
+        for (uint32_t i = threadIdx.x; i < n_edges; i += kWave) {
             const float4 v = amp[(size_t)r * n_edges + i];
             const double tr = v.x, ti = v.y, mr = v.z, mi = v.w;
             acc[0] += 0.5 * (tr * tr + ti * ti + mr * mr + mi * mi);
@@ -212,9 +258,16 @@ __global__ void k_diffraction_sum(const float4 *amp, uint32_t n_edges, uint32_t 
             acc[3] += mr;
             acc[4] += mi;
         }
-        for (int a = 0; a < 5; ++a) out[(size_t)r * 5 + a] = acc[a];
+        for (int a = 0; a < 5; ++a) acc[a] = wave_sum_d(acc[a]);
+        if (threadIdx.x == 0)
+            for (int a = 0; a < 5; ++a) out[(size_t)r * 5 + a] = acc[a];
     }
 }
+
+// Four lanes per pair while their wavefronts (24 KiB of stacks each, 6 to a compute unit) are resident together; beyond,
+// the chip is full and the geometry done four times over is lost. 64 receivers x 160 edges of the 1M-point office, call
+// to call: 108 us with one lane per pair, 77 with four, 64 with the series' terms taken by fours.
+constexpr uint32_t kFourLanePairs = 6 * 256 * kWave / 4;
 
 uint32_t diffraction_blocks(uint32_t n_edges, uint32_t n_rx) { return (n_edges * n_rx + kWave - 1) / kWave; }
 
@@ -236,13 +289,14 @@ void launch_diffraction(const DevScene &S, const pcrt_edge *edges, uint32_t n_ed
     A.eps_self = eps_self;
     A.trim = 2.0f * sqrtf(S.r2);
     A.amp = amp;
-    const dim3 g(diffraction_blocks(n_edges, n_rx));
-    switch (S.width) {
-        case 8: hipLaunchKernelGGL(k_diffraction<8>, g, dim3(kWave), 0, s, A); break;
-        case 4: hipLaunchKernelGGL(k_diffraction<4>, g, dim3(kWave), 0, s, A); break;
-        default: hipLaunchKernelGGL(k_diffraction<2>, g, dim3(kWave), 0, s, A); break;
-    }
-    hipLaunchKernelGGL(k_diffraction_sum, dim3((n_rx + 255) / 256), dim3(256), 0, s, amp, n_edges, n_rx, out);
+    const uint32_t pairs = n_edges * n_rx;
+    const bool four = pairs <= kFourLanePairs;
+    const dim3 g(four ? (4 * pairs + kWave - 1) / kWave : diffraction_blocks(n_edges, n_rx));
+    auto *k = S.width == 8   ? (four ? k_diffraction<8, 4> : k_diffraction<8, 1>)
+              : S.width == 4 ? (four ? k_diffraction<4, 4> : k_diffraction<4, 1>)
+                             : (four ? k_diffraction<2, 4> : k_diffraction<2, 1>);
+    hipLaunchKernelGGL(k, g, dim3(kWave), 0, s, A);
+    hipLaunchKernelGGL(k_diffraction_sum, dim3(std::min(n_rx, 1u << 16)), dim3(kWave), 0, s, amp, n_edges, n_rx, out);
 }
 
 }  // namespace pcrt

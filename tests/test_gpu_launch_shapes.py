@@ -186,3 +186,24 @@ def test_mlp_forward_rows_do_not_depend_on_the_batch(P):
     net.forward_rows(lab, cs, 28e9, big)
     net.forward_rows(lab[:1000], cs[:1000], 28e9, small)
     assert torch.equal(big[:1000], small)
+
+
+@pytest.mark.parametrize("n_rx,n_edges", [(1, 1), (3, 5), (1, 17), (13, 40)])
+def test_diffraction_lanes_per_pair_agree(P, office, n_rx, n_edges):
+    """Up to 24 576 pairs take four lanes each, more take one. A pair's FP64 steps are the same up to the contraction of
+    products and sums, which its series may blow up to 1e-9 of the amplitude: at most one rounding of the FP32 result
+    apart. The sums of a receiver add at most 2^-52 of the terms' magnitudes per edge."""
+    edges = scenes.office_edges(scenes.office(seed=2507, target_points=60_000))
+    edges = (edges[0][:n_edges], edges[1][:n_edges])
+    rx = scenes.office_rx()[:n_rx]
+    out, amp = P.diffraction(office, edges, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx, 3.5e9, want_pairs=True)
+    reps = 24_576 // (n_rx * n_edges) + 1
+    big, bamp = P.diffraction(office, edges, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, np.tile(rx, (reps, 1)), 3.5e9,
+                              want_pairs=True)
+    bamp = np.asarray(bamp)[-n_rx:]
+    assert np.array_equal(amp != 0, bamp != 0)
+    for part in (np.real, np.imag):
+        assert np.all(np.abs(part(amp) - part(bamp)) <= 2.0 ** -23 * np.abs(amp))
+    tol = (2.0 ** -22 + n_edges * 2.0 ** -52) * np.abs(amp).sum((1, 2))
+    d = np.abs(out.cpu().numpy() - big.cpu().numpy()[-n_rx:])
+    assert np.all(d[:, 1:] <= tol[:, None]) and np.all(d[:, 0] <= tol * np.abs(amp).max())
