@@ -188,6 +188,7 @@ Plan make_plan(const pcrt_scene *sc, const pcrt_solve_params *p, std::vector<Ite
     D.n_rx = p->n_rx;
     D.n_items = (uint32_t)items.size();
     D.width = sc->info.width;
+    D.n_sets = sc->info.n_point_sets;
     uint64_t off = 0, total = 0, max_rays = 0;
     for (auto &it : items) {
         it.ray_off = (uint32_t)off;
@@ -346,6 +347,7 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.spec_hid = (p->flags & PCRT_SPECULAR) ? (int *)at(L.spec_hid) : nullptr;
     A.spec_ovr = ((p->flags & PCRT_SPECULAR) && (p->flags & PCRT_AVERAGE)) ? (float4 *)at(L.spec_ovr) : nullptr;
     A.diff_part = (double *)at(L.diff_part);
+    A.vis_words = (uint64_t *)at(L.vis_words);
     A.los_part = (double *)at(L.los_part);
     A.dvis = ((p->flags & PCRT_RECORD) && (p->flags & PCRT_DIFFUSE) && !(p->flags & PCRT_DPS_LAUNCH))
                  ? (uint8_t *)at(L.dvis)
@@ -409,6 +411,7 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
             L.dkey_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
             L.dchunk_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
             L.dcnt = b.take(sizeof(uint64_t) * PCRT_CNT_COUNT);
+            L.vis_words = b.take(sizeof(uint64_t) * D.n_sets * ((D.n_rx + kWave - 1) / kWave));
             if (!spec) {  // the compaction's scan buffers
                 L.scan = b.take(sizeof(uint32_t) * nrec);
                 L.scan_blk = b.take(sizeof(uint32_t) * ((nrec + 1023) / 1024 + 1));

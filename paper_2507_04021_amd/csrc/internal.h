@@ -119,6 +119,7 @@ struct SolveDims {
     uint32_t spill_lanes;  // lanes of the widest traversal launch of this solve
     uint32_t spill_depth;  // traversal stack entries beyond the LDS part (stack bound - kStackLds)
     uint32_t width;        // node width of the scene's hierarchy (2, 4, 8)
+    uint32_t n_sets;       // point sets of the scene
 };
 
 constexpr uint32_t kSlotChunk = 512;    // slots per label-gradient reduction chunk (one 64-lane block each)
@@ -133,7 +134,7 @@ constexpr uint32_t kMaxGradLabels = 64;   // label-gradient LDS: 64 lanes x 64 l
 struct SolveLayout {
     size_t items, counters, work, rec_id, rec_xl, rec_cs, rec_coef, rec_slot, hkey, hrep, scan, scan_blk, keylist,
         key_off, chunk_off, spec_part, diff_part, los_part, sp_valid, sp_len, sp_amp, sp_hit, sp_cs, dvis, spill,
-        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid,
+        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid, vis_words,
         rec_dslot, dhkey, dhrep, dkeylist, dkey_off, dchunk_off, dcnt;
     size_t total;
 };
@@ -187,6 +188,7 @@ struct LaunchArgs {
     int *spec_hid;         // refinement: per block, interaction and lane, the validated disk of the lane's candidate
     float4 *spec_ovr;      // refinement with point-set averaging: per lane and interaction, the replaced plane
     double *diff_part;
+    uint64_t *vis_words;   // reception-point launch: dps_vis in words of 64 receivers, [n_rx / 64 rounded up][n_sets]
     double *los_part;
     uint8_t *dvis;
     uint16_t *slot_label;  // RECORD tape: material label per interaction slot (0xffff: empty)

@@ -207,3 +207,25 @@ def test_diffraction_lanes_per_pair_agree(P, office, n_rx, n_edges):
     tol = (2.0 ** -22 + n_edges * 2.0 ** -52) * np.abs(amp).sum((1, 2))
     d = np.abs(out.cpu().numpy() - big.cpu().numpy()[-n_rx:])
     assert np.all(d[:, 1:] <= tol[:, None]) and np.all(d[:, 0] <= tol * np.abs(amp).max())
+
+
+@pytest.mark.parametrize("n_rx", [1, 63, 65, 130])
+def test_point_set_sums_do_not_depend_on_the_other_receivers(P, n_rx):
+    """The visibility matrix is read in words of 64 receivers: a receiver's sums are bitwise those of a call of its own."""
+    import torch
+    sc = scenes.office(seed=2507, target_points=60_000)
+    g = P.Scene.from_scene(sc, leaf_size=2, width=4, dps_voxel=0.3)
+    rng = np.random.default_rng(n_rx)
+    base = scenes.office_rx()
+    rx = (base[rng.integers(0, len(base), n_rx)] + rng.uniform(-0.2, 0.2, (n_rx, 3))).astype(np.float32)
+    vis = P.visibility(g, rx)
+    kw = dict(K=3, flags=LOS | SPEC | DIFF | P.DPS_LAUNCH)
+    n = g.info["n_point_sets"]
+
+    def rows(i):
+        r = P.solve(g, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx[i], 3.5e9, n, dps_vis=vis[i].contiguous(), **kw)
+        return np.concatenate([t.cpu().numpy().reshape(len(rx[i]), -1) for t in (r.gain, r.h_te, r.h_tm, r.parts)], 1)
+    a = rows(slice(None))
+    assert a[:, -1].max() > 0
+    for i in {0, n_rx // 2, n_rx - 1}:
+        assert np.array_equal(rows(slice(i, i + 1))[0], a[i])
