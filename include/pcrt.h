@@ -226,7 +226,7 @@ typedef struct {
     uint32_t n_subset;
     pcrt_thresholds thr;
     uint32_t key_capacity;
-    uint32_t wave_rays; /* rays a wavefront takes per work fetch, multiple of 64 up to 1024 (0 = 64) */
+    uint32_t wave_rays; /* rays a wavefront takes per work fetch, multiple of 64 up to 1024 (0 = 64, or 256 in solves of many million rays) */
     float lambda_d;     /* depth attenuation of PCRT_AVERAGE, 1/m (0 = 100) */
     const uint8_t *dps_vis; /* PCRT_DPS_LAUNCH: device uint8[n_rx][n_point_sets] from pcrt_visibility for rx */
     float pol_tx[3];        /* PCRT_POLARIZED: transmit and receive polarisation vectors (any length; */

@@ -141,6 +141,7 @@ struct SolveLayout {
 
 SolveLayout solve_layout(const SolveDims &D, uint32_t flags);
 uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays);
+uint32_t default_wave_rays(const SolveDims &D);
 uint32_t refine_grid(const SolveDims &D);
 uint32_t diffuse_grid(const SolveDims &D);
 

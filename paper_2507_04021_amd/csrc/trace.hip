@@ -18,11 +18,13 @@ __device__ __forceinline__ uint32_t key_insert(const HashBufs &hb, uint32_t base
     uint32_t slot = (uint32_t)mix64(enc) & mask;
     for (uint32_t probe = 0; probe < hb.cap; ++probe) {
         unsigned long long *kp = hb.key + base + slot;
+        uint32_t *rp = hb.rep + base + slot;
         unsigned long long cur = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (read along with the key: a representative only falls, so one read too early costs an atomic at most)
+        const uint32_t rep = __hip_atomic_load(rp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (cur == 0ull) cur = atomicCAS(kp, 0ull, (unsigned long long)enc);
         if (cur == 0ull || cur == enc) {
-            uint32_t *rp = hb.rep + base + slot;
-            if (__hip_atomic_load(rp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > j) atomicMin(rp, j);
+            if (rep > j) atomicMin(rp, j);
             return slot;
         }
         slot = (slot + 1) & mask;
@@ -258,6 +260,16 @@ uint32_t trace_lanes(const SolveDims &D) {
     uint32_t lanes = 4;
     while (lanes < (uint32_t)kWave && (D.T + lanes - 1) / lanes > kSimds) lanes <<= 1;
     return lanes;
+}
+
+// Rays per work fetch where the caller leaves it open. A fetch is an atomic on one
+// word (11 ns each, whoever issues it): 36M rays in fetches of 64 are 562 000 of them, 6 ms one after another. From 16
+// fetches of 256 per wavefront on the last ones no longer matter for the balance. 64 poses, 36M rays: 9.73 ms with 64,
+// 9.38 / 9.27 / 9.28 / 9.51 with 128 / 256 / 512 / 1 024; but a million rays: 27.1 / 27.2 / 27.1 / 28.3 / 31.3 ms,
+// 65 537 rays: 2.1 / 2.3 / 2.7 / 3.4 / 4.9 ms (whole solves).
+uint32_t default_wave_rays(const SolveDims &D) {
+    const uint64_t large = 4 * kWave;
+    return D.T >= 16 * large * trace_cap_w(D.width) ? (uint32_t)large : (uint32_t)kWave;
 }
 
 uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays) {
