@@ -347,6 +347,8 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.spec_hid = (p->flags & PCRT_SPECULAR) ? (int *)at(L.spec_hid) : nullptr;
     A.spec_ovr = ((p->flags & PCRT_SPECULAR) && (p->flags & PCRT_AVERAGE)) ? (float4 *)at(L.spec_ovr) : nullptr;
     A.diff_part = (double *)at(L.diff_part);
+    A.spec_split = (float4 *)at(L.spec_split);
+    A.spec_bits = (uint8_t *)at(L.spec_bits);
     A.vis_words = (uint64_t *)at(L.vis_words);
     A.los_part = (double *)at(L.los_part);
     A.dvis = ((p->flags & PCRT_RECORD) && (p->flags & PCRT_DIFFUSE) && !(p->flags & PCRT_DPS_LAUNCH))
@@ -426,6 +428,9 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
         L.spec_part = b.take(sizeof(double) * 5 * (size_t)D.max_key_chunks * D.n_rx);
         L.spec_res = b.take(sizeof(float4) * (size_t)refine_grid(D) * kRefineResPerBlock);
         L.spec_hid = b.take(sizeof(int) * (size_t)refine_grid(D) * kWave * D.K);
+        // chunks x receivers are fewer than the grid's wavefronts where a chunk is dealt in parts
+        L.spec_split = b.take(sizeof(float4) * (size_t)refine_grid(D) * kKeyChunk);
+        L.spec_bits = b.take((size_t)refine_grid(D) * (kKeyChunk / 8));
         if (flags & PCRT_AVERAGE) L.spec_ovr = b.take(sizeof(float4) * 2 * (size_t)refine_grid(D) * kWave * D.K);
         if (rec) {
             const size_t pairs = (size_t)D.rec_keys * D.n_rx;

@@ -519,14 +519,31 @@ __global__ __launch_bounds__(kWave) void k_los(LaunchArgs A) {
 // diffuse chunks. Lane t sums chunks t, t+256, ... in order; the lanes are
 // then combined by a fixed pairwise tree, so the result is bitwise repeatable.
 __global__ __launch_bounds__(256) void k_combine(LaunchArgs A, double *gain, double *h_te, double *h_tm,
-                                                 double *parts) {
+                                                 double *parts, uint32_t refine_wavefronts) {
     __shared__ double red[256][10];
     const uint32_t p = blockIdx.x;
     const uint32_t it = p / A.D.n_rx, r = p % A.D.n_rx;
     const uint32_t n_rx = A.D.n_rx;
     const int t = threadIdx.x;
     double sp[5] = {0, 0, 0, 0, 0}, df[5] = {0, 0, 0, 0, 0};
-    if (A.flags & 2) {
+    if ((A.flags & 2) && refine_wavefronts &&
+        refine_shape(A.chunk_off[A.D.n_items], n_rx, refine_wavefronts).parts > 1) {
+        // refined in parts: a chunk's paths in key order, as the refinement adds them otherwise
+        for (uint32_t c = A.chunk_off[it] + t; c < A.chunk_off[it + 1]; c += 256) {
+            const size_t v = (size_t)c * n_rx + r;
+            double acc[5] = {0, 0, 0, 0, 0};
+            for (uint64_t m = ((const uint64_t *)A.spec_bits)[v]; m; m &= m - 1) {
+                const float4 x = A.spec_split[v * kKeyChunk + __ffsll((unsigned long long)m) - 1];
+                const double tr = x.x, ti = x.y, mr = x.z, mi = x.w;
+                acc[0] += 0.5 * (tr * tr + ti * ti + mr * mr + mi * mi);
+                acc[1] += tr;
+                acc[2] += ti;
+                acc[3] += mr;
+                acc[4] += mi;
+            }
+            for (int a = 0; a < 5; ++a) sp[a] += acc[a];
+        }
+    } else if (A.flags & 2) {
         for (uint32_t c = A.chunk_off[it] + t; c < A.chunk_off[it + 1]; c += 256)
             for (int a = 0; a < 5; ++a) sp[a] += A.spec_part[((size_t)c * n_rx + r) * 5 + a];
     }
@@ -579,12 +596,14 @@ void launch_los_and_combine(const LaunchArgs &A, double *gain, double *h_te, dou
             default: hipLaunchKernelGGL(k_los<2>, g, dim3(kWave), 0, s, A); break;
         }
     }
-    launch_combine(A, gain, h_te, h_tm, parts, s);
+    launch_combine(A, gain, h_te, h_tm, parts, true, s);
 }
 
-void launch_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts, hipStream_t s) {
+void launch_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts, bool solved,
+                    hipStream_t s) {
     const uint32_t n = A.D.n_items * A.D.n_rx;
-    hipLaunchKernelGGL(k_combine, dim3(n), dim3(256), 0, s, A, gain, h_te, h_tm, parts);
+    hipLaunchKernelGGL(k_combine, dim3(n), dim3(256), 0, s, A, gain, h_te, h_tm, parts,
+                       solved ? refine_grid(A.D) : 0u);
 }
 
 }  // namespace pcrt

@@ -128,13 +128,34 @@ constexpr uint32_t kSlotChunk = 512;    // slots per label-gradient reduction ch
 constexpr uint32_t kRefineRxSlice = 8;
 // Result slots per refinement block: two open units of kKeyChunk keys x kRefineRxSlice receivers.
 constexpr uint32_t kRefineResPerBlock = 2 * kKeyChunk * kRefineRxSlice;
+// Units of the refinement, for n_chunks key chunks on a grid of `grid`
+// wavefronts: receivers per unit, and parts a unit's key chunk is dealt out in.
+// kRefineRxSlice receivers keep the lanes fed, which is best while there is a unit
+// for every wavefront; below that, wavefronts idle while a few work through
+// long chains, so the slices are halved until every wavefront has a unit or a
+// unit is one receiver, then the chunk's keys are dealt in up to 4 parts. The sums
+// per (key chunk, receiver) are the same for every shape. 5 285 keys x 17
+// receivers, 28 858 candidates (a quarter of the wavefront-time used without
+// parts): 1 / 2 / 4 / 8 parts 0.81 / 0.70 / 0.70 / 0.69 ms; 53 keys, 1
+// receiver: 67 / 54 / 58 / 87 us. What is left is the longest candidate's chain.
+constexpr uint32_t kRefineMaxParts = 4;
+struct RefineShape {
+    uint32_t slice, parts;
+};
+__device__ __forceinline__ RefineShape refine_shape(uint32_t n_chunks, uint32_t n_rx, uint32_t grid) {
+    RefineShape s{kRefineRxSlice, 1};
+    while (s.slice > 1 && n_chunks * ((n_rx + s.slice - 1) / s.slice) < grid) s.slice >>= 1;
+    if (s.slice == 1)
+        while (s.parts < kRefineMaxParts && n_chunks * n_rx * s.parts < grid) s.parts <<= 1;
+    return s;
+}
 constexpr uint32_t kRefineQueue = 128;  // refinement ring of queued candidates (at most 127 are queued)
 constexpr uint32_t kMaxGradLabels = 64;   // label-gradient LDS: 64 lanes x 64 labels x 3 doubles
 
 struct SolveLayout {
     size_t items, counters, work, rec_id, rec_xl, rec_cs, rec_coef, rec_slot, hkey, hrep, scan, scan_blk, keylist,
         key_off, chunk_off, spec_part, diff_part, los_part, sp_valid, sp_len, sp_amp, sp_hit, sp_cs, dvis, spill,
-        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid, vis_words,
+        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid, spec_split, spec_bits, vis_words,
         rec_dslot, dhkey, dhrep, dkeylist, dkey_off, dchunk_off, dcnt;
     size_t total;
 };
@@ -189,6 +210,8 @@ struct LaunchArgs {
     int *spec_hid;         // refinement: per block, interaction and lane, the validated disk of the lane's candidate
     float4 *spec_ovr;      // refinement with point-set averaging: per lane and interaction, the replaced plane
     double *diff_part;
+    float4 *spec_split;    // refinement in parts: the paths' amplitudes, [key chunk][n_rx][kKeyChunk]
+    uint8_t *spec_bits;    // ... and a bit per (key, receiver) that is a path, [key chunk][n_rx][kKeyChunk / 8]
     uint64_t *vis_words;   // reception-point launch: dps_vis in words of 64 receivers, [n_rx / 64 rounded up][n_sets]
     double *los_part;
     uint8_t *dvis;
@@ -253,7 +276,9 @@ void launch_dps_diffuse(const LaunchArgs &A, float area, hipStream_t s);
 uint32_t dps_key_cap(const SolveDims &D);
 void launch_los_and_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts,
                             hipStream_t s);
-void launch_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts, hipStream_t s);
+// solved: the specular paths are those of this call's refinement (not of a tape's replay, whose sums are all in spec_part)
+void launch_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts, bool solved,
+                    hipStream_t s);
 void launch_tape_slots(const LaunchArgs &A, hipStream_t s);
 void launch_tape_fresnel(const LaunchArgs &A, const float *mats, uint32_t n_labels, hipStream_t s);
 void launch_tape_forward(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts,

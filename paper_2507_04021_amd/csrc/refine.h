@@ -251,7 +251,7 @@ constexpr int kRefineOpen = 2;          // units open at once per wavefront
 constexpr int kRefineRefillShift = 3;   // lanes decide once at most busy / 8 still walk
 
 struct RefUnit {  // an open unit (wavefront-uniform)
-    uint32_t c, r0, nr, q0, ne, t, pending;  // pending: candidates queued or held by a lane
+    uint32_t c, part, r0, nr, q0, ne, t, pending;  // pending: candidates queued or held by a lane
     f3 tx;
     bool open;
 };
@@ -291,21 +291,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
     float4 *pl_g = AVG ? A.spec_ovr + (size_t)glane * KM * 2 : nullptr;
     const uint32_t n_rx = A.D.n_rx, n_items = A.D.n_items;
     const uint32_t n_chunks = A.chunk_off[n_items];
-    // Receivers per unit: kRefineRxSlice keeps the lanes fed, which is best while
-    // there is a unit for every wavefront of the grid; below that, wavefronts
-    // idle while a few work through long chains, so the slices are halved until
-    // every wavefront has a unit or a unit is one receiver. The sums per (key
-    // chunk, receiver) are the same for every slice.
-    uint32_t slice = kRefineRxSlice;
-    while (slice > 1 && n_chunks * ((n_rx + slice - 1) / slice) < gridDim.x) slice >>= 1;
+    const RefineShape shape = refine_shape(n_chunks, n_rx, gridDim.x);
+    const uint32_t slice = shape.slice, parts = shape.parts, part_keys = kKeyChunk / parts;
     const uint32_t n_slices = (n_rx + slice - 1) / slice;
-    const uint32_t n_units = n_chunks * n_slices;
+    const uint32_t n_units = n_chunks * n_slices * parts;
+    const bool one_open = parts > 1;  // parts are few pairs: a second would only take them from another wavefront
     const bool rec = A.flags & 8;
     const float eps_self = A.thr.eps_self, eps_tie = A.thr.eps_tie;
     uint32_t n_cand = 0, n_valid = 0;
     RefUnit U[kRefineOpen];
 #pragma unroll
-    for (int k = 0; k < kRefineOpen; ++k) U[k] = RefUnit{0, 0, 0, 0, 0, 0, 0, mk(0.f, 0.f, 0.f), false};
+    for (int k = 0; k < kRefineOpen; ++k) U[k] = RefUnit{0, 0, 0, 0, 0, 0, 0, 0, mk(0.f, 0.f, 0.f), false};
     bool exhausted = false;       // the unit counter has run out
     uint32_t head = 0, tail = 0;  // queue ring positions (wavefront-uniform)
     // this lane's candidate: entry of the queue, passes that ended in a plane
@@ -428,7 +424,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
         for (int k = 0; k < kRefineOpen; ++k) {
             if (!(U[k].open && U[k].t * kWave >= U[k].ne && U[k].pending == 0)) continue;
             block_sync_global();  // result slots written by other lanes are visible
-            if ((uint32_t)lane < U[k].nr) {
+            if (parts > 1) {  // the paths and their bits; k_combine adds the chunk's
+                const uint32_t v = U[k].c * n_rx + U[k].r0, j0 = U[k].part * part_keys, e = lane;
+                if (e < U[k].ne && ((vbits[k][e >> 5] >> (e & 31)) & 1u))
+                    A.spec_split[(size_t)v * kKeyChunk + j0 + e] = res[k * kUnitPairs + e];
+                if (e < part_keys / 8)
+                    A.spec_bits[(size_t)v * (kKeyChunk / 8) + j0 / 8 + e] = (uint8_t)(vbits[k][e >> 2] >> (8 * (e & 3)));
+            } else if ((uint32_t)lane < U[k].nr) {
                 double acc[5] = {0, 0, 0, 0, 0};
                 for (uint32_t e = (uint32_t)lane; e < U[k].ne; e += U[k].nr)  // increasing key
                     if ((vbits[k][e >> 5] >> (e & 31)) & 1u) {
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
             if (s < 0 && !exhausted) {
 #pragma unroll
                 for (int k = 0; k < kRefineOpen; ++k) {
-                    if (s >= 0 || U[k].open || exhausted) continue;
+                    if (s >= 0 || U[k].open || exhausted || (k && one_open)) continue;
                     uint32_t u = 0;
                     if (lane == 0) u = atomicAdd(&A.work[1], 1u);
                     u = __builtin_amdgcn_readfirstlane(u);
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
                         exhausted = true;
                         continue;
                     }
-                    const uint32_t c = u / n_slices;
+                    const uint32_t part = u % parts, cs = u / parts, c = cs / n_slices;
                     int lo = 0, hi = (int)n_items - 1;  // item of this chunk
                     while (lo < hi) {
                         int mid = (lo + hi + 1) >> 1;
@@ -474,10 +476,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
                     }
                     const Item I = A.items[lo];
                     U[k].c = c;
-                    U[k].r0 = (u % n_slices) * slice;
+                    U[k].part = part;
+                    U[k].r0 = (cs % n_slices) * slice;
                     U[k].nr = min(slice, n_rx - U[k].r0);
-                    U[k].q0 = A.key_off[lo] + (c - A.chunk_off[lo]) * kKeyChunk;
-                    const uint32_t q1 = min(U[k].q0 + kKeyChunk, A.key_off[lo + 1]);
+                    U[k].q0 = A.key_off[lo] + (c - A.chunk_off[lo]) * kKeyChunk + part * part_keys;
+                    const uint32_t q1 = max(U[k].q0, min(U[k].q0 + part_keys, A.key_off[lo + 1]));
                     U[k].ne = (q1 - U[k].q0) * U[k].nr;
                     U[k].t = 0;
                     U[k].pending = 0;
@@ -555,7 +558,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
         wave_sync();  // taken entries are read before their ring slots are reused
         const uint32_t n_busy = (uint32_t)__popcll(__ballot(busy));
         // nothing is left that could feed an idle lane
-        const bool dry = exhausted && tail == head && !(U[0].open && U[0].t * kWave < U[0].ne) &&
+        const bool dry = (exhausted || one_open) && tail == head && !(U[0].open && U[0].t * kWave < U[0].ne) &&
                          !(U[1].open && U[1].t * kWave < U[1].ne);
         if (n_busy == 0) {
             if (!U[0].open && !U[1].open) break;  // no unit left to open, every unit closed

@@ -283,7 +283,7 @@ void launch_tape_forward(const LaunchArgs &A, double *gain, double *h_te, double
         hipLaunchKernelGGL(k_tape_specular, dim3(std::min<uint32_t>(std::max<uint32_t>(A.D.max_key_chunks, 1), 2048)),
                            dim3(256), 0, s, A);
     // line of sight does not depend on the materials: the solve's values are reused
-    launch_combine(A, gain, h_te, h_tm, parts, s);
+    launch_combine(A, gain, h_te, h_tm, parts, false, s);
 }
 
 // Adjoint of one path's power 1/2 (|a_TE|^2 + |a_TM|^2) with respect to its

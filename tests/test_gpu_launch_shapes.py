@@ -229,3 +229,14 @@ def test_point_set_sums_do_not_depend_on_the_other_receivers(P, n_rx):
     assert a[:, -1].max() > 0
     for i in {0, n_rx // 2, n_rx - 1}:
         assert np.array_equal(rows(slice(i, i + 1))[0], a[i])
+
+
+@pytest.mark.parametrize("rays,n_rx", [(200, 1), (2000, 2), (20_000, 5), (60_000, 17)])
+def test_refinement_parts_do_not_change_a_receiver(P, office, rays, n_rx):
+    """A few key chunks and receivers are dealt in parts of a chunk; 1 024 receivers have a unit for every wavefront and
+    are not. The sums of a chunk are added in key order either way."""
+    rx = np.tile(scenes.office_rx(), (16, 1))
+    a, r = _solve(P, office, rx[:n_rx], rays, 3)
+    assert int(r.counters[P.CNT["keys"]]) > 0
+    b, _ = _solve(P, office, rx, rays, 3)
+    assert np.array_equal(a, b[:n_rx])
