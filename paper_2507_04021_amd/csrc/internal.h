@@ -142,7 +142,7 @@ constexpr uint32_t kRefineMaxParts = 4;
 struct RefineShape {
     uint32_t slice, parts;
 };
-__device__ __forceinline__ RefineShape refine_shape(uint32_t n_chunks, uint32_t n_rx, uint32_t grid) {
+__device__ __forceinline__ RefineShape refine_shape(uint64_t n_chunks, uint32_t n_rx, uint32_t grid) {
     RefineShape s{kRefineRxSlice, 1};
     while (s.slice > 1 && n_chunks * ((n_rx + s.slice - 1) / s.slice) < grid) s.slice >>= 1;
     if (s.slice == 1)

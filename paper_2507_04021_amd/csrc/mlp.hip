@@ -494,8 +494,9 @@ __global__ __launch_bounds__(64 * kBwdW) void k_mlp_backward(MlpArgs M) {
         F = S.frag + fo;
         B = S.bias + bo;
         const uint32_t row = (t0 + wave) * kTileRows + n;
-        const uint16_t lab = row < M.n ? M.label[row] : (uint16_t)0xffff;
-        const bool live = row < M.n && lab < M.n_labels;
+        const bool has = t0 + wave < n_tiles && row < M.n;
+        const uint16_t lab = has ? M.label[row] : (uint16_t)0xffff;
+        const bool live = has && lab < M.n_labels;
         const bf16x8 x = input_frag(M, row, lab, g);
         bf16x8 h1[2], h2[2], h3[2];
         float gp1[16], gp2[16], gp3[16];
