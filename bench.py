@@ -67,15 +67,15 @@ def ops_node(width):
 # built from; a figure is reported only while its sources still match.
 _CSRC = "paper_2507_04021_amd/csrc/"
 TRAFFIC = {
-    "k_diffuse": {"bytes": 2047087526, "l2_hit_rate": 0.980,
+    "k_diffuse": {"bytes": 2522012080, "l2_hit_rate": 0.976,
                   "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "field.hip", "bvh.hip")),
-                  "src_sha256": "8410874cea60a1f9076e51a0a325025136d300afe9d5737e5ef95dd3495685a0"},
-    "k_trace": {"bytes": 10116536819, "l2_hit_rate": 0.505,
-                "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "trace.hip", "bvh.hip")),
-                "src_sha256": "fb739f401a6570b72102c2dfbef48612751ed02a815505ef5542482615c18322"},
-    "k_refine": {"bytes": 10320811085, "l2_hit_rate": 0.481,
-                 "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "refine.h", "specular.hip", "bvh.hip")),
-                 "src_sha256": "edccdd494dc47c62a96fff9d50eb96697bc8eab3ad0248d8cfa0917d7e0f6162"},
+                  "src_sha256": "b99643828367db4236af4e672b5ab519d601ab88c6663d6682f28beeed1c1d97"},
+    "k_trace": {"bytes": 9855077664, "l2_hit_rate": 0.486,
+                "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "trace.hip", "bvh.hip")),
+                "src_sha256": "05bbbf581f6d7610f21c6da522d8dc9f123ff216495aa00e28595c1f5cbb0b93"},
+    "k_refine": {"bytes": 8891694384, "l2_hit_rate": 0.551,
+                 "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "refine.h", "specular.hip", "bvh.hip")),
+                 "src_sha256": "0c2ecd447e005e387d664c760a0a9b1639cb92bf4a8d039f6c5c7b9f235aff8a"},
 }
 
 
