@@ -85,7 +85,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     const Ties ties{tie_list + lane};
     Walk w;
     walk_start(w, ties, A.S.root, o, d);
-    uint32_t q_next = 0, q_end = 0;  // this wavefront's reserved ray slots [q_next, q_end)
+    // This wavefront's reserved ray slots [q_next, q_end): the first are dealt (all wavefronts start together, and an
+    // atomic on one word costs 11 ns whoever issues it), further ones come from a counter.
+    const uint32_t dealt = gridDim.x * take;
+    uint32_t q_next = min(blockIdx.x * take, T), q_end = min(q_next + take, T);
     bool q_dry = false;
     uint32_t n_int = 0, n_ray = 0, n_spill = 0;
     for (;;) {
@@ -94,8 +97,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
             const uint64_t idle = __ballot(!busy && (uint32_t)lane < n_lanes);
             if (!idle || q_dry) break;
             if (q_next >= q_end) {
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&A.work[0], take);
+                uint32_t base = T;
+                if (lane == 0 && dealt < T) base = dealt + atomicAdd(&A.work[0], take);
                 base = __builtin_amdgcn_readfirstlane(base);
                 if (base >= T) {
                     q_dry = true;
