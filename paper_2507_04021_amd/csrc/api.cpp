@@ -264,7 +264,7 @@ struct InitArgs {
 
 __global__ __launch_bounds__(256) void k_init(InitArgs I) {
     const uint64_t t = blockIdx.x * 256ull + threadIdx.x, nt = gridDim.x * 256ull;
-    if (t < kWorkWords) I.work[t] = 0u;
+    for (uint64_t i = t; i < kWorkWords; i += nt) I.work[i] = 0u;
     if (t < PCRT_CNT_COUNT) I.counters[t] = 0ull;
     if (t < I.b.n) I.items[t] = I.b.it[t];
     for (uint64_t i = t; i < I.n_off; i += nt) I.key_off[i] = I.chunk_off[i] = 0u;
@@ -347,6 +347,8 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.spec_hid = (p->flags & PCRT_SPECULAR) ? (int *)at(L.spec_hid) : nullptr;
     A.spec_ovr = ((p->flags & PCRT_SPECULAR) && (p->flags & PCRT_AVERAGE)) ? (float4 *)at(L.spec_ovr) : nullptr;
     A.diff_part = (double *)at(L.diff_part);
+    A.diff_parts = diffuse_parts(P.D);
+    A.vis_bits = (uint32_t *)at(L.vis_bits);
     A.spec_split = (float4 *)at(L.spec_split);
     A.spec_bits = (uint8_t *)at(L.spec_bits);
     A.vis_words = (uint64_t *)at(L.vis_words);
@@ -403,6 +405,7 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
         L.rec_coef = b.take(sizeof(float4) * nrec);
         L.dpack = b.take(2 * sizeof(float4) * nrec);
         L.diff_part = b.take(sizeof(double) * 5 * (size_t)D.n_ray_chunks * D.n_rx);
+        if (!(flags & PCRT_DPS_LAUNCH)) L.vis_bits = b.take(sizeof(uint32_t) * diffuse_bits_words(D));
         if (rec && !(flags & PCRT_DPS_LAUNCH)) L.dvis = b.take(nrec * D.n_rx);  // ray-tube connections only
         if (flags & PCRT_DPS_LAUNCH) {  // voxel diffuse keys of the reception-point launch
             const size_t cap = dps_key_cap(D);

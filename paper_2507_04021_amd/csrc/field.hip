@@ -161,7 +161,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     const uint32_t n_chunks = A.D.n_ray_chunks;
     const bool rec = A.flags & 8;
     const float eps = A.thr.eps_self;
-    const uint32_t n_groups = kRayChunk * K / kWave;  // groups of 64 records per chunk
+    const uint32_t chunk_groups = kRayChunk * K / kWave;  // groups of 64 records per chunk
+    const uint32_t parts = A.diff_parts;                  // a unit takes a chunk's groups in so many parts
     uint32_t n_seg = 0, n_vis = 0;
     uint64_t n_occ_visits = 0;  // instrumented builds: node visits of occluded segments
     // Workgroups are dealt to the XCDs round robin, and each XCD has its own
@@ -170,15 +171,28 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     // of the scene, then help the other ranges in turn. Within a range, units
     // are receiver-minor, so consecutive units reuse a chunk's records.
     const uint32_t xcd = blockIdx.x % kXcds;
+    // A wavefront's first unit is dealt, the others come from a counter per
+    // range. All wavefronts end by looking through all ranges, and an atomic on one
+    // line costs 11 ns whoever issues it, so a range is looked at before it is
+    // asked, and the counters are a line apart: a launch of 4 369 units took 0.85 ms
+    // with 39 000 such atomics on one line, 0.64 with these.
     enum { kIdle = 0, kWalk = 1, kDone = 2 };
+    auto range = [&](uint32_t x) {
+        return (uint32_t)((uint64_t)x * n_chunks / kXcds) * n_rx * parts;
+    };
+    auto dealt = [&](uint32_t x) { return (gridDim.x + kXcds - 1 - x) / kXcds; };  // blocks of XCD x
+    uint32_t first = range(xcd) + blockIdx.x / kXcds;
+    if (first >= range(xcd + 1)) first = 0xffffffffu;
     for (;;) {
-        uint32_t u = 0xffffffffu;
-        if (lane == 0) {
+        uint32_t u = first;
+        first = 0xffffffffu;
+        if (u == 0xffffffffu && lane == 0) {
             for (uint32_t k = 0; k < kXcds; ++k) {
                 const uint32_t x = (xcd + k) % kXcds;
-                const uint32_t lo = (uint32_t)((uint64_t)x * n_chunks / kXcds) * n_rx;
-                const uint32_t hi = (uint32_t)((uint64_t)(x + 1) * n_chunks / kXcds) * n_rx;
-                const uint32_t uu = lo + atomicAdd(&A.work[8 + x], 1u);
+                uint32_t *next = A.work + 32 * (1 + x);
+                const uint32_t lo = range(x), hi = range(x + 1), at = lo + dealt(x);
+                if (at + __hip_atomic_load(next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= hi) continue;
+                const uint32_t uu = at + atomicAdd(next, 1u);
                 if (uu < hi) {
                     u = uu;
                     break;
@@ -187,11 +201,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
         }
         u = __builtin_amdgcn_readfirstlane(u);
         if (u == 0xffffffffu) break;
-        const uint32_t c = u / n_rx, r = u % n_rx;
+        const uint32_t part = u % parts, cr = u / parts, c = cr / n_rx, r = cr % n_rx;
         const uint32_t g0 = c * kRayChunk;
+        const uint32_t q0 = chunk_groups * part / parts, n_groups = chunk_groups * (part + 1) / parts;
         const f3 rx = mk(A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]);
         for (uint32_t i = lane; i < 2 * n_groups; i += kWave) vis_bits[i] = 0u;
-        uint32_t q = 0, head = 0, tail = 0;  // next group to classify; queue positions (wave-uniform)
+        uint32_t q = q0, head = 0, tail = 0;  // next group to classify; queue positions (wave-uniform)
         int phase = kIdle;
         uint32_t mo = 0;  // this lane's record, chunk-relative
         int excl = -1, ref = kNoRef, sp = 0, park = kNoRef;
@@ -292,6 +307,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
             }
         }
         __syncthreads();
+        if (parts > 1) {  // k_diffuse_sum adds the chunk's records once all parts are there
+            for (uint32_t i = 2 * q0 + lane; i < 2 * n_groups; i += kWave)
+                A.vis_bits[(size_t)cr * (2 * chunk_groups) + i] = vis_bits[i];
+            __syncthreads();
+            continue;
+        }
         // The visible records in record order, listed in the LDS of the walks'
         // stacks (every walk has ended: at most 2 KiB of offsets); lane l then
         // adds list entries l, l + 64, ..., so every lane computes amplitudes
@@ -334,16 +355,79 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     }
 }
 
+// Sums of the units that were walked in parts: a wavefront lists a unit's visible
+// records in record order; lane l adds list entries l, l + 64, ... (so every
+// lane computes amplitudes, not only those whose own record of a group is
+// visible), and one fixed butterfly adds the lanes. Units are dealt like the
+// connections, an eighth of the chunks per XCD, receiver-minor: the units of a chunk
+// read its records from one L2. The additions are those of k_diffuse, so the sums are bitwise the same.
+__global__ __launch_bounds__(kWave) void k_diffuse_sum(LaunchArgs A) {
+    __shared__ uint16_t vlist[kRayChunk * kMaxK];
+    const uint32_t lane = threadIdx.x, K = A.D.K, n_rx = A.D.n_rx, n_groups = kRayChunk * K / kWave;
+    const uint32_t x = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
+    const uint32_t lo = (uint32_t)((uint64_t)x * A.D.n_ray_chunks / kXcds) * n_rx;
+    const uint32_t hi = (uint32_t)((uint64_t)(x + 1) * A.D.n_ray_chunks / kXcds) * n_rx;
+    for (uint32_t u = lo + blockIdx.x / kXcds; u < hi; u += nb) {
+        const uint32_t c = u / n_rx, r = u % n_rx, g0 = c * kRayChunk;
+        const f3 rx = mk(A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]);
+        const uint32_t w = lane < 2 * n_groups ? A.vis_bits[(size_t)u * (2 * n_groups) + lane] : 0u;
+        uint32_t n_list = 0;
+        for (uint32_t g = 0; g < n_groups; ++g) {
+            const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(w, 2 * g) |
+                               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(w, 2 * g + 1) << 32);
+            if ((m >> lane) & 1u) vlist[n_list + mbcnt(m)] = (uint16_t)(g * kWave + lane);
+            n_list += (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        const Item I = A.items[find_item(A.items, A.D.n_items, g0)];
+        const float budget = (float)I.budget;
+        double acc[5] = {};
+        for (uint32_t i = lane; i < n_list; i += kWave) {
+            const uint32_t j = g0 * K + vlist[i];
+            const float4 p0 = A.dsort.pack[2 * (size_t)j], p1 = A.dsort.pack[2 * (size_t)j + 1];
+            double v5[5];
+            diffuse_amplitude(A, A.dsort.order[j], xyz(p0), xyz(p1), p0.w, rx, budget, v5);
+            for (int a = 0; a < 5; ++a) acc[a] += v5[a];
+        }
+        double sv[5];
+        for (int a = 0; a < 5; ++a) sv[a] = wave_sum_d(acc[a]);
+        if (lane == 0) {
+            double *o = A.diff_part + ((size_t)c * n_rx + r) * 5;
+            for (int a = 0; a < 5; ++a) o[a] = sv[a];
+        }
+        __syncthreads();  // the list is rewritten for the next unit
+    }
+}
+
 template <int W>
 uint32_t diffuse_cap() {
     static const uint32_t cap = resident_blocks((const void *)k_diffuse<W>, kWave);
     return cap;
 }
 
+static uint32_t diffuse_cap_w(uint32_t width) {
+    return width == 8 ? diffuse_cap<8>() : width == 4 ? diffuse_cap<4>() : diffuse_cap<2>();
+}
+
+// Parts a (chunk, receiver) unit is walked in: one while there is a unit for every wavefront that fits the chip,
+// else as many as that takes, a group of 64 records each at least. The connections of 100k points (units: with one part,
+// in parts): 64: 411 -> 97 us, 257: 334 -> 130, 1 028: 432 -> 278, 2 056: 438 -> 372, 4 369: 0.64 -> 0.575 ms; with two units
+// for every wavefront 0.575, with four 0.67.
+uint32_t diffuse_parts(const SolveDims &D) {
+    const uint64_t units = (uint64_t)D.n_ray_chunks * D.n_rx, want = diffuse_cap_w(D.width);
+    uint32_t parts = 1;
+    while (units * parts < want && 2 * parts <= kRayChunk * D.K / kWave) parts *= 2;
+    return parts;
+}
+
+// Words of the visible connections, for units walked in parts.
+size_t diffuse_bits_words(const SolveDims &D) {
+    return diffuse_parts(D) > 1 ? (size_t)D.n_ray_chunks * D.n_rx * (kRayChunk * D.K / 32) : 0;
+}
+
 uint32_t diffuse_grid(const SolveDims &D) {
-    const uint32_t cap = D.width == 8 ? diffuse_cap<8>() : D.width == 4 ? diffuse_cap<4>() : diffuse_cap<2>();
-    const uint32_t units = D.n_ray_chunks * D.n_rx;
-    return std::max<uint32_t>(1, std::min(cap, units));
+    const uint64_t units = (uint64_t)D.n_ray_chunks * D.n_rx * diffuse_parts(D);
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(diffuse_cap_w(D.width), units));
 }
 
 const uint32_t *launch_diffuse_order(const LaunchArgs &A, hipStream_t s) {
@@ -366,6 +450,10 @@ void launch_diffuse(const LaunchArgs &A, hipStream_t s) {
         case 4: hipLaunchKernelGGL(k_diffuse<4>, g, dim3(kWave), 0, s, A); break;
         default: hipLaunchKernelGGL(k_diffuse<2>, g, dim3(kWave), 0, s, A); break;
     }
+    if (A.diff_parts == 1) return;
+    static const uint32_t cap = resident_blocks((const void *)k_diffuse_sum, kWave);
+    const uint32_t per_xcd = (A.D.n_ray_chunks + kXcds - 1) / kXcds * A.D.n_rx;
+    hipLaunchKernelGGL(k_diffuse_sum, dim3(kXcds * std::max(1u, std::min(cap / kXcds, per_xcd))), dim3(kWave), 0, s, A);
 }
 
 // Diffuse paths of the reception-point launch (Sec. II-B.1, II-B.4): one per

@@ -18,8 +18,8 @@ namespace pcrt {
 uint32_t resident_blocks(const void *kernel, int block_threads);
 constexpr uint32_t kMaxPairs = 262144;  // (transmitter, receiver) pairs in one solve
 // Work counters of the persistent launches: [0] trace units, [1] refine chunks,
-// [8, 16) diffuse chunks, one counter per XCD range.
-constexpr uint32_t kWorkWords = 32;
+// [32 (1 + x)] diffuse units of XCD range x (a line each).
+constexpr uint32_t kWorkWords = 32 * 9;
 constexpr uint32_t kXcds = 8;  // MI355X: 8 accelerator complex dies, workgroups dealt round robin
 constexpr uint32_t kDefaultWidth = 4;    // 4-wide nodes: fastest on the 1M-point office (binary and 8-wide slower)
 constexpr uint32_t kDefaultBuilder = 2;  // clustering: 6 % fewer node visits than the radix tree on the office
@@ -155,7 +155,7 @@ constexpr uint32_t kMaxGradLabels = 64;   // label-gradient LDS: 64 lanes x 64 l
 struct SolveLayout {
     size_t items, counters, work, rec_id, rec_xl, rec_cs, rec_coef, rec_slot, hkey, hrep, scan, scan_blk, keylist,
         key_off, chunk_off, spec_part, diff_part, los_part, sp_valid, sp_len, sp_amp, sp_hit, sp_cs, dvis, spill,
-        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid, spec_split, spec_bits, vis_words,
+        slot_label, slot_cos, slot_coef, slot_adj, grad_part, dkey0, dkey1, dval0, dval1, dhist, dblk, spec_res, dpack, rec_nk, spec_ovr, spec_hid, spec_split, spec_bits, vis_bits, vis_words,
         rec_dslot, dhkey, dhrep, dkeylist, dkey_off, dchunk_off, dcnt;
     size_t total;
 };
@@ -165,6 +165,8 @@ uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays);
 uint32_t default_wave_rays(const SolveDims &D);
 uint32_t refine_grid(const SolveDims &D);
 uint32_t diffuse_grid(const SolveDims &D);
+uint32_t diffuse_parts(const SolveDims &D);
+size_t diffuse_bits_words(const SolveDims &D);
 
 struct SortBufs {  // spatial ordering of the diffuse records
     uint64_t *key0, *key1;
@@ -210,6 +212,8 @@ struct LaunchArgs {
     int *spec_hid;         // refinement: per block, interaction and lane, the validated disk of the lane's candidate
     float4 *spec_ovr;      // refinement with point-set averaging: per lane and interaction, the replaced plane
     double *diff_part;
+    uint32_t diff_parts;   // diffuse: parts a (chunk, receiver) unit is walked in
+    uint32_t *vis_bits;    // ... and the visible connections of units walked in parts, a bit per record
     float4 *spec_split;    // refinement in parts: the paths' amplitudes, [key chunk][n_rx][kKeyChunk]
     uint8_t *spec_bits;    // ... and a bit per (key, receiver) that is a path, [key chunk][n_rx][kKeyChunk / 8]
     uint64_t *vis_words;   // reception-point launch: dps_vis in words of 64 receivers, [n_rx / 64 rounded up][n_sets]

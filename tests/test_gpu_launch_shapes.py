@@ -240,3 +240,21 @@ def test_refinement_parts_do_not_change_a_receiver(P, office, rays, n_rx):
     assert int(r.counters[P.CNT["keys"]]) > 0
     b, _ = _solve(P, office, rx, rays, 3)
     assert np.array_equal(a, b[:n_rx])
+
+
+@pytest.mark.parametrize("rays,K", [(2000, 1), (2000, 3), (4000, 5), (2100, 8)])
+def test_diffuse_parts_do_not_change_a_receiver(P, office, rays, K):
+    """Two receivers have few (ray chunk, receiver) units, which are walked in parts and summed afterwards; 1 024
+    receivers have a unit for every wavefront. The additions are the same, and so are the connections counted."""
+    rx = np.tile(scenes.office_rx(), (16, 1))
+
+    def solve(rx):
+        r = P.solve(office, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx, 3.5e9, rays, K=K, flags=LOS | DIFF)
+        return np.concatenate([t.cpu().numpy().reshape(len(rx), -1) for t in (r.gain, r.h_te, r.h_tm, r.parts)], 1), r
+    a, ra = solve(rx[:2])
+    b, _ = solve(rx)
+    assert a[:, -1].max() > 0 and np.array_equal(a, b[:2])
+    c, rc = solve(rx[:64])
+    _, rb = solve(np.tile(rx[:64], (16, 1)))
+    for k in ("segments", "diffuse"):
+        assert 16 * int(rc.counters[P.CNT[k]]) == int(rb.counters[P.CNT[k]])
