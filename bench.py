@@ -67,15 +67,15 @@ def ops_node(width):
 # built from; a figure is reported only while its sources still match.
 _CSRC = "paper_2507_04021_amd/csrc/"
 TRAFFIC = {
-    "k_diffuse": {"bytes": 2522012080, "l2_hit_rate": 0.976,
+    "k_diffuse": {"bytes": 2464665824, "l2_hit_rate": 0.977,
                   "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "field.hip", "bvh.hip")),
-                  "src_sha256": "b99643828367db4236af4e672b5ab519d601ab88c6663d6682f28beeed1c1d97"},
-    "k_trace": {"bytes": 9855077664, "l2_hit_rate": 0.486,
+                  "src_sha256": "8fc7f7404c99ffdb8a02c2506ee51de2cce91619e0a2d5c849bc4154aab98b52"},
+    "k_trace": {"bytes": 9825531952, "l2_hit_rate": 0.487,
                 "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "trace.hip", "bvh.hip")),
-                "src_sha256": "05bbbf581f6d7610f21c6da522d8dc9f123ff216495aa00e28595c1f5cbb0b93"},
-    "k_refine": {"bytes": 8891694384, "l2_hit_rate": 0.551,
+                "src_sha256": "6679726330fd032e564a6e29d2880a3ca4988cb1bcec4ca4c85930d6faa25f7f"},
+    "k_refine": {"bytes": 8871682816, "l2_hit_rate": 0.550,
                  "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "refine.h", "specular.hip", "bvh.hip")),
-                 "src_sha256": "0c2ecd447e005e387d664c760a0a9b1639cb92bf4a8d039f6c5c7b9f235aff8a"},
+                 "src_sha256": "5e5038d91e6b7ec6ac438f53ee12a894c87c6022423bf6098cdfa877396c56fa"},
 }
 
 
