@@ -20,7 +20,7 @@
 // and dealt in advance, with a drain at the end of each of its one or two units,
 // the slowest wavefront set the time. On the office's 64 x 181 523 matrix: 2.65 ms
 // with one 64-set batch per unit and no refill, 2.2 ms with refill over
-// 1024-set units dealt in advance, 1.63 ms so.
+// 1024-set units dealt in advance, 1.63 ms so, 1.52 with 20 stack entries in LDS.
 #include "common.h"
 #include "internal.h"
 
