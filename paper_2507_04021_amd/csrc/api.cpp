@@ -527,20 +527,17 @@ pcrt_status pcrt_scene_create(const pcrt_points *pts, const pcrt_bvh_opts *opts,
     HIP_TRY(hipEventRecord(e1, s));
     uint32_t stat[8], dstat[2] = {0, 0};
     float bounds[6];
-    // stat, bounds, dps_stat and ticket follow each other in the workspace
-    uint32_t ticket[4];
-    std::vector<char> back(L.ticket + sizeof ticket - L.stat);
+    // stat, bounds and dps_stat follow each other in the workspace
+    std::vector<char> back(L.dps_stat + sizeof dstat - L.stat);
     HIP_TRY(hipMemcpyAsync(back.data(), (char *)ws + L.stat, back.size(), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     memcpy(stat, back.data(), sizeof stat);
     memcpy(bounds, back.data() + (L.bounds - L.stat), sizeof bounds);
-    memcpy(ticket, back.data() + (L.ticket - L.stat), sizeof ticket);
     if (rho > 0.f) memcpy(dstat, back.data() + (L.dps_stat - L.stat), sizeof dstat);
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
     hipEventDestroy(e0);
     hipEventDestroy(e1);
-    if (ticket[3]) return fail(PCRT_EDEVICE, "the hierarchy build did not finish");
     if (stat[0] & 1) return fail(PCRT_EINVAL, "non-finite point position");
     if (stat[0] & 2) return fail(PCRT_EINVAL, "zero or non-finite normal");
     if (dstat[0] & 1) return fail(PCRT_EUNSUPPORTED, "voxel index beyond +-2^20 (dps_voxel too small for the scene)");

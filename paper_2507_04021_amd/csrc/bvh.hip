@@ -344,8 +344,8 @@ __device__ __forceinline__ float merged_half_area(const float *a, const float *b
 // and payload (two 31-bit counts) share one 64-bit word, so relaxed atomics do.
 // Every wait ends: after kTilePolls looks (a second or so; a wait takes some
 // microseconds) the tile gives up with a prefix of 0 and sets the build's fail
-// word: later levels then find no frontier, and the host refuses the scene
-// before it follows any reference.
+// word: later levels then find no frontier, and the host, which looks at the
+// word before it follows any count or reference, refuses the scene.
 constexpr uint64_t kTileSum = 1ull << 62, kTilePrefix = 2ull << 62, kTileMask = kTileSum - 1;
 constexpr uint32_t kTilePolls = 1u << 20;
 
@@ -888,15 +888,23 @@ __device__ int wide_children(const float4 *__restrict__ bnode, int b, WSlot *sl)
 // One level of the collapse in one launch: every block takes tiles of 256
 // frontier nodes by ticket, finds their wide children once, and writes the
 // nodes and the next frontier at its scanned places. A launch after the last
-// level finds an empty frontier and ends. Five launches and a host round trip
+// level finds an empty frontier and ends, and so does one after a failed level:
+// one thread looks at the fail word, which another block may be setting, so
+// that a block takes one decision. Five launches and a host round trip
 // per level before: 14 levels of a 1M-point build 1.0 -> 0.3 ms.
 template <int W>
 __global__ __launch_bounds__(256) void k_wide_level(const float4 *__restrict__ bnode, const uint8_t *__restrict__ choice,
                                                     const int *__restrict__ frontier, PassBufs B, uint32_t level,
                                                     int *__restrict__ next, float *__restrict__ wnode) {
     __shared__ uint32_t tile_s;
+    __shared__ PassState now;
     pass_clear(B, level);
-    const uint32_t nf = B.ticket[3] ? 0u : B.st[level].m, base_cur = B.st[level].base, base_next = base_cur + nf;
+    if (threadIdx.x == 0) {
+        now = B.st[level];
+        if (__hip_atomic_load(&B.ticket[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) now.m = 0u;
+    }
+    __syncthreads();
+    const uint32_t nf = now.m, base_cur = now.base, base_next = base_cur + nf;
     if (nf == 0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) B.st[level + 1] = {0u, base_cur};
         return;
@@ -1041,7 +1049,8 @@ SceneLayout scene_layout(uint32_t n, uint32_t width, uint32_t builder, bool dps)
     L.stat = b.take(sizeof(uint32_t) * 8);
     L.bounds = b.take(sizeof(float) * 8);
     L.dps_stat = b.take(sizeof(uint32_t) * 2);
-    L.ticket = b.take(sizeof(uint32_t) * 4);  // stat, bounds, dps_stat, ticket: cleared and read back together
+    L.ticket = b.take(sizeof(uint32_t) * 4);  // stat, bounds, dps_stat, ticket: cleared together
+    if (width > 2) L.level_st = b.take(sizeof(PassState) * (kMaxLevels + 8));  // read back with the ticket's fail word
     L.blk_bounds = b.take(sizeof(float) * 6 * blk);
     L.code0 = b.take(sizeof(uint64_t) * n);
     L.code1 = b.take(sizeof(uint64_t) * n);
@@ -1078,7 +1087,6 @@ SceneLayout scene_layout(uint32_t n, uint32_t width, uint32_t builder, bool dps)
         L.qref = b.take(sizeof(int) * width * (size_t)ni);
         L.front0 = b.take(sizeof(int) * ni);
         L.front1 = b.take(sizeof(int) * ni);
-        L.level_st = b.take(sizeof(PassState) * (kMaxLevels + 8));
         L.sah_pending = b.take(sizeof(uint32_t) * ni);
         L.sah_cost = b.take(sizeof(float) * width * (size_t)ni);
         L.sah_choice = b.take((size_t)width * ni);
@@ -1102,9 +1110,12 @@ static PassBufs pass_bufs(const SceneLayout &L, char *ws, uint32_t n, size_t st)
             (uint32_t *)(ws + L.ticket)};
 }
 
-__global__ __launch_bounds__(256) void k_pass_init(PassBufs B, PassState first, int *front, int root, uint32_t *depth) {
+// n_st: states to clear, the first included (a failed level may leave the next one's unwritten)
+__global__ __launch_bounds__(256) void k_pass_init(PassBufs B, PassState first, uint32_t n_st, int *front, int root,
+                                                   uint32_t *depth) {
     const uint32_t t = blockIdx.x * 256 + threadIdx.x;
     for (uint32_t i = t; i < B.n_status; i += gridDim.x * 256) B.status[0][i] = B.status[1][i] = 0ull;
+    for (uint32_t i = t + 1; i < n_st; i += gridDim.x * 256) B.st[i] = {0u, 0u};
     if (t != 0) return;
     B.ticket[0] = B.ticket[1] = 0u;
     B.st[0] = first;
@@ -1145,7 +1156,7 @@ hipError_t build_ploc(const SceneLayout &L, char *ws, uint32_t n, const uint32_t
     float *ibox = (float *)P(L.ibox);
     const PassBufs B = pass_bufs(L, ws, n, L.pass_st);
     hipLaunchKernelGGL(k_pass_init, dim3(std::min<uint32_t>(cdiv(B.n_status, 256), 256)), dim3(256), 0, s, B,
-                       PassState{n, 0u}, (int *)nullptr, 0, depth);
+                       PassState{n, 0u}, 1u, (int *)nullptr, 0, depth);
     auto clusters = [&](uint32_t pass) {
         if (pass == 0) return Clusters{(const float *)P(L.dbox), nullptr, nullptr};
         return Clusters{cbox[pass & 1], cid[pass & 1], csz[pass & 1]};
@@ -1219,23 +1230,28 @@ hipError_t build_wide_w(const SceneLayout &L, char *ws, hipStream_t s, int broot
     }
     const PassBufs B = pass_bufs(L, ws, ni, L.level_st);
     hipLaunchKernelGGL(k_pass_init, dim3(std::min<uint32_t>(cdiv(B.n_status, 256), 256)), dim3(256), 0, s, B,
-                       PassState{1u, 0u}, fr[0], broot, (uint32_t *)nullptr);
+                       PassState{1u, 0u}, kMaxLevels + 8, fr[0], broot, (uint32_t *)nullptr);
     uint32_t lv = 0;
     uint64_t bound = 1;  // of the frontier
-    std::vector<PassState> st(1, PassState{1u, 0u});
-    while (st.back().m > 0) {
+    struct {
+        uint32_t ticket[64];  // (256 bytes: the layout's alignment)
+        PassState st[kMaxLevels + 8];
+    } back;
+    const PassState *st = back.st;
+    PassState last{1u, 0u};
+    while (last.m > 0) {
         // every wide node stands for a distinct binary internal node
-        if ((uint64_t)st.back().base + st.back().m > ni || lv >= kMaxLevels) return hipErrorUnknown;
+        if ((uint64_t)last.base + last.m > ni || lv >= kMaxLevels) return hipErrorUnknown;
         for (uint32_t k = 0; k < kLevelBatch; ++k, ++lv) {
             const uint32_t g = (uint32_t)std::min<uint64_t>(cdiv(bound, 256), 1024);
             hipLaunchKernelGGL(k_wide_level<W>, dim3(g), dim3(256), 0, s, bnode, choice, fr[lv & 1], B, lv,
                                fr[(lv + 1) & 1], wnode);
             bound = std::min<uint64_t>(bound * W, ni);
         }
-        st.resize((size_t)lv + 1);
-        const hipError_t e = read_back(&st[lv + 1 - kLevelBatch], B.st + lv + 1 - kLevelBatch,
-                                       sizeof(PassState) * kLevelBatch, s);
+        const hipError_t e = read_back(&back, ws + L.ticket, sizeof back, s);
         if (e != hipSuccess) return e;
+        if (back.ticket[3]) return hipErrorUnknown;  // a look-back gave up
+        last = st[lv];
     }
     uint32_t n_lv = 0;
     while (st[n_lv].m > 0) ++n_lv;
