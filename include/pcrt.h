@@ -226,7 +226,8 @@ typedef struct {
     uint32_t n_subset;
     pcrt_thresholds thr;
     uint32_t key_capacity;
-    uint32_t wave_rays; /* rays a wavefront takes per work fetch, multiple of 64 up to 1024 (0 = 64, or 256 in solves of many million rays) */
+    uint32_t wave_rays; /* rays a wavefront takes per work fetch, multiple of 64 up to 1024; 0: the library chooses (64; */
+                        /* 256 in solves of many million rays; 4 to 32 in those too small to give every SIMD 64 rays) */
     float lambda_d;     /* depth attenuation of PCRT_AVERAGE, 1/m (0 = 100) */
     const uint8_t *dps_vis; /* PCRT_DPS_LAUNCH: device uint8[n_rx][n_point_sets] from pcrt_visibility for rx */
     float pol_tx[3];        /* PCRT_POLARIZED: transmit and receive polarisation vectors (any length; */
@@ -344,7 +345,7 @@ pcrt_status pcrt_graph_destroy(pcrt_graph *graph);
 
 /* Autotuner: times reps solves of p on every given scene (built by the
  * caller with the leaf sizes and widths to compare) for every wave_rays
- * value (HIP events on stream; synchronises), fills table[n_scenes * n_wave]
+ * value (0 stands for the library's choice; HIP events on stream; synchronises), fills table[n_scenes * n_wave]
  * (optional, scene-major) and the fastest configuration. solve_ws must fit
  * the solve on every scene (else ENOMEM, with the size needed). */
 typedef struct {

@@ -214,11 +214,11 @@ Plan make_plan(const pcrt_scene *sc, const pcrt_solve_params *p, std::vector<Ite
         D.rec_keys = D.n_slots = D.n_slot_chunks = 0;
     }
     // every traversal launch indexes the stack spill by its global lane
-    const uint32_t wr = p->wave_rays ? p->wave_rays : default_wave_rays(D);
+    const uint32_t take = trace_shape(D, p->wave_rays).take;
     // the first kStackLds stack entries live in LDS, the rest in the spill area
     // (set first: the diffuse grid depends on whether there is one)
     D.spill_depth = sc->info.stack_entries > (uint32_t)kStackLds ? sc->info.stack_entries - kStackLds : 0;
-    D.spill_lanes = std::max({trace_grid(D, wr) * kWave, diffuse_grid(D) * kWave, refine_grid(D) * kWave,
+    D.spill_lanes = std::max({trace_grid(D, take) * kWave, diffuse_grid(D) * kWave, refine_grid(D) * kWave,
                               round_up(D.n_items * D.n_rx, kWave)});
     P.L = solve_layout(D, p->flags);
     P.thr = make_thr(p->thr);
@@ -318,7 +318,9 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.thr = P.thr;
     A.fc = P.fc;
     A.D = P.D;
-    A.wave_rays = p->wave_rays ? p->wave_rays : default_wave_rays(P.D);
+    const TraceShape tr = trace_shape(P.D, p->wave_rays);
+    A.trace_lanes = tr.lanes;
+    A.wave_rays = tr.take;
     A.rb.id = (int *)at(L.rec_id);
     A.rb.xl = (float4 *)at(L.rec_xl);
     A.rb.cs = (float *)at(L.rec_cs);

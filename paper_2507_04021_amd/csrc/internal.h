@@ -161,8 +161,12 @@ struct SolveLayout {
 };
 
 SolveLayout solve_layout(const SolveDims &D, uint32_t flags);
-uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays);
-uint32_t default_wave_rays(const SolveDims &D);
+// Bounce loop: lanes of a wavefront that take rays, and rays it takes per work fetch.
+struct TraceShape {
+    uint32_t lanes, take;
+};
+TraceShape trace_shape(const SolveDims &D, uint32_t wave_rays);  // wave_rays: the caller's, 0 where it leaves the choice
+uint32_t trace_grid(const SolveDims &D, uint32_t take);
 uint32_t refine_grid(const SolveDims &D);
 uint32_t diffuse_grid(const SolveDims &D);
 uint32_t diffuse_parts(const SolveDims &D);
@@ -192,7 +196,7 @@ struct LaunchArgs {
     RecBufs rb;
     HashBufs hb;
     SpecBufs sb;
-    uint32_t wave_rays; // rays a wavefront takes per work fetch (multiple of 64)
+    uint32_t wave_rays; // rays a wavefront takes per work fetch
     uint32_t trace_lanes; // lanes of a wavefront that take rays (a power of two)
     f3 pol_tx, pol_rx;  // polarised field: transmit and receive polarisation vectors
     float dps_area;     // point sets: the area rho^2 a voxel diffuse path stands for

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     const bool want_geom = A.flags & (4 | 8 | 32);  // points/lengths/cosines: diffuse, tape, averaged planes
     const bool avg = A.flags & 32;                  // weighted-average intersection over point sets
     const float eps_self = A.thr.eps_self, eps_tie = A.thr.eps_tie;
-    const uint32_t n_lanes = A.trace_lanes, take = n_lanes < (uint32_t)kWave ? n_lanes : A.wave_rays;
+    const uint32_t n_lanes = A.trace_lanes, take = A.wave_rays;
     bool busy = false, walking = false;  // this lane has a ray; its walk has not ended
     uint32_t g = 0, j = 0, k = 0;
     int it = 0, excl = -1;
@@ -252,13 +252,13 @@ uint32_t trace_cap_w(uint32_t width) {
     return width == 8 ? trace_cap<8>() : width == 4 ? trace_cap<4>() : trace_cap<2>();
 }
 
-// Lanes of a wavefront that take rays. A wavefront of few rays steps faster (a
+// Lanes of a wavefront that take rays, where the caller leaves the fetch open. A wavefront of few rays steps faster (a
 // node step costs its lanes' separate cache lines, and it waits for its longest
 // walk), so a launch too small to give every SIMD a wavefront of 64 rays is
 // spread over one wavefront per SIMD, of 4 rays at least. 2 000 rays, K = 2:
 // 88 us with 64 lanes, 72 / 67 / 62 / 98 with 16 / 8 / 4 / 1; but 65 537 rays,
 // K = 3 (already a wavefront of 64 per SIMD): 0.295 ms, 0.304 / 0.366 with 32 / 16.
-uint32_t trace_lanes(const SolveDims &D) {
+static uint32_t trace_lanes(const SolveDims &D) {
     constexpr uint32_t kSimds = 1024;
     uint32_t lanes = 4;
     while (lanes < (uint32_t)kWave && (D.T + lanes - 1) / lanes > kSimds) lanes <<= 1;
@@ -270,25 +270,29 @@ uint32_t trace_lanes(const SolveDims &D) {
 // fetches of 256 per wavefront on the last ones no longer matter for the balance. 64 poses, 36M rays: 9.73 ms with 64,
 // 9.38 / 9.27 / 9.28 / 9.51 with 128 / 256 / 512 / 1 024; but a million rays: 27.1 / 27.2 / 27.1 / 28.3 / 31.3 ms,
 // 65 537 rays: 2.1 / 2.3 / 2.7 / 3.4 / 4.9 ms (whole solves).
-uint32_t default_wave_rays(const SolveDims &D) {
+static uint32_t default_wave_rays(const SolveDims &D) {
     const uint64_t large = 4 * kWave;
     return D.T >= 16 * large * trace_cap_w(D.width) ? (uint32_t)large : (uint32_t)kWave;
 }
 
-uint32_t trace_grid(const SolveDims &D, uint32_t wave_rays) {
-    const uint32_t lanes = trace_lanes(D), take = lanes < (uint32_t)kWave ? lanes : wave_rays;
+// A value that the caller gives is taken at every size, by whole wavefronts.
+TraceShape trace_shape(const SolveDims &D, uint32_t wave_rays) {
+    if (wave_rays) return {(uint32_t)kWave, wave_rays};
+    const uint32_t lanes = trace_lanes(D);
+    return {lanes, lanes < (uint32_t)kWave ? lanes : default_wave_rays(D)};
+}
+
+uint32_t trace_grid(const SolveDims &D, uint32_t take) {
     const uint32_t units = (D.T + take - 1) / take;
     return std::max<uint32_t>(1, std::min(trace_cap_w(D.width), units));
 }
 
 void launch_trace(const LaunchArgs &A, hipStream_t s) {
     const uint32_t grid = trace_grid(A.D, A.wave_rays);
-    LaunchArgs B = A;
-    B.trace_lanes = trace_lanes(A.D);
     switch (A.D.width) {
-        case 8: hipLaunchKernelGGL(k_trace<8>, dim3(grid), dim3(kWave), 0, s, B); break;
-        case 4: hipLaunchKernelGGL(k_trace<4>, dim3(grid), dim3(kWave), 0, s, B); break;
-        default: hipLaunchKernelGGL(k_trace<2>, dim3(grid), dim3(kWave), 0, s, B); break;
+        case 8: hipLaunchKernelGGL(k_trace<8>, dim3(grid), dim3(kWave), 0, s, A); break;
+        case 4: hipLaunchKernelGGL(k_trace<4>, dim3(grid), dim3(kWave), 0, s, A); break;
+        default: hipLaunchKernelGGL(k_trace<2>, dim3(grid), dim3(kWave), 0, s, A); break;
     }
 }
 
