@@ -16,6 +16,7 @@ namespace pcrt {
 // (blocks per compute unit from the occupancy API x compute units); their
 // waves pull work from atomic counters until it runs out.
 uint32_t resident_blocks(const void *kernel, int block_threads);
+uint32_t compute_units();
 constexpr uint32_t kMaxPairs = 262144;  // (transmitter, receiver) pairs in one solve
 // Work counters of the persistent launches: [0] trace units, [1] refine chunks,
 // [32 (1 + x)] diffuse units of XCD range x (a line each).

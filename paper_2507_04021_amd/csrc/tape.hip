@@ -616,16 +616,16 @@ void launch_tape_cfr(const LaunchArgs &A, double bw, uint32_t N, double *cfr, hi
 }
 
 // dL/da_p (as gR + j gI per polarisation) of one path from dL/dH_r:
-// sum over n of dL/dH_r(f_n) exp(+j 2 pi (f_n - f_c) tau_p), by one lane, n
-// rising; runs of 64 samples by rotation. r is wavefront-uniform, so the samples'
-// gradients are scalar loads.
-__device__ __forceinline__ void cfr_lane_grad(const double *__restrict__ dldh, uint32_t r, uint32_t N, double bw,
-                                              double tau, cd &gte, cd &gtm) {
+// the sum over n in [a, b) of dL/dH_r(f_n) exp(+j 2 pi (f_n - f_c) tau_p), by one
+// lane, n rising; runs of 64 samples by rotation. Where r and n are
+// wavefront-uniform the samples' gradients are scalar loads.
+__device__ __forceinline__ void cfr_lane_grad(const double *__restrict__ dldh, uint32_t r, uint32_t N, uint32_t first,
+                                              uint32_t last, double bw, double tau, cd &gte, cd &gtm) {
     const cd step = cd_cycles(cfr_step(N, bw) * tau);
     gte = gtm = {0.0, 0.0};
-    for (uint32_t n0 = 0; n0 < N; n0 += 64) {
+    for (uint32_t n0 = first; n0 < last; n0 += 64) {
         cd e = cd_cycles(cfr_df(n0, N, bw) * tau);
-        const uint32_t n1 = min(N, n0 + 64);
+        const uint32_t n1 = min(last, n0 + 64);
         for (uint32_t n = n0; n < n1; ++n) {
             const double *g = dldh + ((size_t)r * N + n) * 4;
             const double a = g[0], b = g[1], c = g[2], d = g[3];
@@ -709,17 +709,28 @@ __device__ __forceinline__ void chain_adjoint_c(int k, const SlotCoef *cf, const
 // gradient on its own, and wavefront 0 adds the wavefronts' E in order and
 // evaluates the chain. FP64 issue bounds it, 12 instructions per path and
 // sample. One wavefront per ray, its lanes on the samples with a sincos and a
-// 24-shuffle butterfly per path, took 92 us for 12k records x 6 receivers x 129
-// samples; now 43 us.
+// 24-shuffle butterfly per path, took 97 us for 12k records x 6 receivers x 129
+// samples; so 40 us, and 33 with kSplit: where that leaves the chip idle (cfr_split), several
+// lanes of each wavefront share a ray, and (receiver, run of samples) pairs are
+// dealt to wavefronts and lanes instead of receivers; the lanes are added by a
+// fixed butterfly first.
 constexpr uint32_t kCfrAdjWaves = 8;
-template <int KM>
+struct CfrSplit {
+    uint32_t lanes;  // lanes per ray
+    uint32_t runs;   // runs a receiver's samples are cut into
+    uint32_t run;    // samples of a run
+};
+template <int KM, bool kSplit>
 __global__ __launch_bounds__(kCfrAdjWaves * kWave) void k_tape_cfr_adjoint_trace(LaunchArgs A, double bw, uint32_t N,
-                                                                                 const double *__restrict__ dldh) {
+                                                                                 const double *__restrict__ dldh,
+                                                                                 CfrSplit P) {
     __shared__ double red[kCfrAdjWaves][4][kWave];
     const uint32_t K = A.D.K, n_rx = A.D.n_rx, lane = threadIdx.x % kWave;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (uint32_t g0 = blockIdx.x * kWave; g0 < A.D.T; g0 += gridDim.x * kWave) {
-        const uint32_t g = g0 + lane;  // ray slots come in multiples of 256
+    const uint32_t rays = kSplit ? kWave / P.lanes : kWave, sub = kSplit ? lane / rays : 0;
+    const uint32_t first = kSplit ? wv * P.lanes + sub : wv, next = kSplit ? kCfrAdjWaves * P.lanes : kCfrAdjWaves;
+    for (uint32_t g0 = blockIdx.x * rays; g0 < A.D.T; g0 += gridDim.x * rays) {
+        const uint32_t g = g0 + (kSplit ? lane % rays : lane);  // ray slots come in multiples of 256
         double adj[KM][5];
 #pragma unroll
         for (int m = 0; m < KM; ++m)
@@ -739,20 +750,29 @@ __global__ __launch_bounds__(kCfrAdjWaves * kWave) void k_tape_cfr_adjoint_trace
                 const uint32_t ri = g * K + k;
                 const bool hit = A.rb.id[ri] >= 0;
                 cd Ete = {0.0, 0.0}, Etm = {0.0, 0.0};
-                for (uint32_t r = wv; r < n_rx; r += kCfrAdjWaves) {
+                for (uint32_t i = first; i < n_rx * (kSplit ? P.runs : 1u); i += next) {
+                    const uint32_t r = kSplit ? i / P.runs : i;
+                    const uint32_t n0 = kSplit ? i % P.runs * P.run : 0u, n1 = kSplit ? min(N, n0 + P.run) : N;
                     if (!(hit && A.dvis[(size_t)ri * n_rx + r])) continue;
                     float a0, plen;
                     diffuse_geom(A, ri, mk(A.rx[3 * r], A.rx[3 * r + 1], A.rx[3 * r + 2]), budget, a0, plen);
                     const c32 ph = propagate(plen, A.fc.inv_lam_hi, A.fc.inv_lam_lo);
                     const cd G = {(double)a0 * ph.re, (double)a0 * ph.im};
                     cd gte, gtm;
-                    cfr_lane_grad(dldh, r, N, bw, (double)plen / kC0, gte, gtm);
+                    cfr_lane_grad(dldh, r, N, n0, n1, bw, (double)plen / kC0, gte, gtm);
                     const cd ete = cdmul(gte, cdconj(G)), etm = cdmul(gtm, cdconj(G));
                     Ete.re += ete.re;
                     Ete.im += ete.im;
                     Etm.re += etm.re;
                     Etm.im += etm.im;
                 }
+                if (kSplit)  // the lanes of a ray, alike in each of them
+                    for (uint32_t o = rays; o < (uint32_t)kWave; o <<= 1) {
+                        Ete.re += __shfl_xor(Ete.re, (int)o, kWave);
+                        Ete.im += __shfl_xor(Ete.im, (int)o, kWave);
+                        Etm.re += __shfl_xor(Etm.re, (int)o, kWave);
+                        Etm.im += __shfl_xor(Etm.im, (int)o, kWave);
+                    }
                 red[wv][0][lane] = Ete.re;
                 red[wv][1][lane] = Ete.im;
                 red[wv][2][lane] = Etm.re;
@@ -769,7 +789,7 @@ __global__ __launch_bounds__(kCfrAdjWaves * kWave) void k_tape_cfr_adjoint_trace
                 __syncthreads();
             }
         }
-        if (wv != 0) continue;
+        if (wv != 0 || sub != 0) continue;
 #pragma unroll
         for (int m = 0; m < KM; ++m) {
             if (m >= (int)K) continue;
@@ -821,15 +841,37 @@ __global__ __launch_bounds__(256) void k_tape_cfr_adjoint_spec(LaunchArgs A, dou
     }
 }
 
+// Lanes per ray and runs per receiver of the traced adjoint. While the wavefronts that have a receiver are one per SIMD
+// at least, a lane keeps its ray and whole receivers: 12 000 rays, 12 receivers, 1 000 samples 0.37 ms, in runs 0.35 to
+// 0.70; 100 000 rays, 3 receivers 0.71, 0.69 to 0.96. Below, lanes share a ray until there is a block per compute unit, and
+// a receiver's samples are cut until the lanes' shares are even and at most 128 samples long, at 16 samples a run at least
+// (a run starts with the path's geometry and two sincospi). Whole receivers -> runs, us, for 1 000 / 4 001 samples: 300 rays,
+// 1 receiver 180 / 686 -> 26 / 39; 6 000 rays, 1 receiver 181 / 690 -> 35 / 100; 1 000 rays, 6 receivers 310 / 1 189 -> 51 /
+// 138; 2 000 rays, 64 receivers 1 599 / 10 773 -> 330 / 1 945.
+static CfrSplit cfr_split(const SolveDims &D, uint32_t N) {
+    constexpr uint32_t kRunMin = 16, kRunMax = 128;
+    static const uint64_t cus = compute_units();
+    const uint64_t n_rx = D.n_rx, blocks = D.T / kWave;
+    if (blocks * std::min<uint64_t>(kCfrAdjWaves, n_rx) >= 4 * cus) return {1, 1, N};
+    uint32_t lanes = 1, runs = 1;
+    while (lanes < (uint32_t)kWave && 2 * lanes * blocks <= cus && 2 * lanes * kCfrAdjWaves * kRunMin <= n_rx * N)
+        lanes *= 2;
+    const uint32_t share = kCfrAdjWaves * lanes;
+    while (2 * runs * kRunMin <= N && (N > runs * kRunMax || (n_rx * runs % share && n_rx * runs < 2 * share))) runs *= 2;
+    return {lanes, runs, (N + runs - 1) / runs};
+}
+
 void launch_tape_cfr_backward(const LaunchArgs &A, double bw, uint32_t N, const double *dldh, hipStream_t s) {
-    const uint32_t gt = std::min<uint32_t>((A.D.T + kWave - 1) / kWave, 16384);
+    const CfrSplit P = cfr_split(A.D, N);
+    const uint32_t gt = std::min<uint32_t>((A.D.T * P.lanes + kWave - 1) / kWave, 16384);
     const size_t np = (size_t)A.D.rec_keys * A.D.n_rx;
     const uint32_t gs = (uint32_t)std::min<size_t>((np + 3) / 4, 16384);  // four wavefronts per block
     switch (A.D.K) {
 #define PCRT_TC_CASE(KK)                                                                                       \
     case KK:                                                                                                   \
-        hipLaunchKernelGGL(k_tape_cfr_adjoint_trace<KK>, dim3(std::max<uint32_t>(gt, 1)),                      \
-                           dim3(kCfrAdjWaves * kWave), 0, s, A, bw, N, dldh);                                  \
+        hipLaunchKernelGGL((P.lanes * P.runs > 1 ? k_tape_cfr_adjoint_trace<KK, true>                          \
+                                                 : k_tape_cfr_adjoint_trace<KK, false>),                       \
+                           dim3(std::max<uint32_t>(gt, 1)), dim3(kCfrAdjWaves * kWave), 0, s, A, bw, N, dldh, P); \
         hipLaunchKernelGGL(k_tape_cfr_adjoint_spec<KK>, dim3(std::max<uint32_t>(gs, 1)), dim3(256), 0, s, A, bw, N, \
                            dldh);                                                                              \
         break;

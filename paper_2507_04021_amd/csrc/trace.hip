@@ -231,15 +231,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     }
 }
 
-uint32_t resident_blocks(const void *kernel, int block_threads) {
-    int dev = 0, cus = 0, per_cu = 0;
+uint32_t compute_units() {
+    int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block_threads, 0) != hipSuccess) {
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 256;  // no device to ask
+    }
+    return (uint32_t)std::max(cus, 1);
+}
+
+uint32_t resident_blocks(const void *kernel, int block_threads) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block_threads, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 2048;  // no device to ask: an upper bound for 256 compute units
     }
-    return (uint32_t)std::max(per_cu, 1) * (uint32_t)std::max(cus, 1);
+    return (uint32_t)std::max(per_cu, 1) * compute_units();
 }
 
 template <int W>

@@ -162,3 +162,65 @@ def test_cir_learning_recovers_materials(env, orc):
         opt.step()
         losses.append(float(loss))
     assert losses[-1] < 0.1 * losses[0], (losses[0], losses[-1])
+
+
+def _room_tape(P, diff, rays, K, n_rx):
+    sg = P.Scene.from_scene(scenes.box_room(spacing=0.1, radius=0.08, labels="surface"))
+    mats = scenes.hidden_materials(7, 8, scatter=(0.1, 0.5))
+    rx = np.random.default_rng(n_rx).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (n_rx, 3)).astype(np.float32)
+    rec = diff.record(sg, mats, scenes.BOX_TX, rx, FC, rays, K=K, flags=LOS | SPEC | DIFF)
+    P.tape_fresnel(rec, mats)
+    return rec
+
+
+@pytest.mark.parametrize("rays,K,n_rx,n", [(1, 1, 1, 33), (300, 2, 1, 129), (300, 2, 1, 4001), (1000, 3, 6, 1001),
+                                           (2000, 2, 64, 301), (6000, 2, 1, 1001), (3000, 8, 4, 257), (700, 5, 3, 65)])
+def test_cfr_adjoint_rows_do_not_depend_on_the_split(env, rays, K, n_rx, n):
+    """Few rays, receivers and many samples: the lanes share a ray and its samples are cut into runs. Sample k of n is
+    sample 2 k of 2 n - 1, and samples 0, (n - 1) / 2 and n - 1 are those of a response of three, which is not cut: with
+    zeros elsewhere the adjoint rows must agree. A row is a sum in FP64 (phases of 500 cycles at most, n terms that cancel
+    down to sqrt(n): 1e-10 of the largest row) rounded to FP32 (one unit apart at most)."""
+    torch, P, diff, _, _, _ = env
+    print("[gpu-test] adjoint rows rays=%d K=%d rx=%d n=%d" % (rays, K, n_rx, n), flush=True)
+    rec = _room_tape(P, diff, rays, K, n_rx)
+
+    def rows(w):
+        P.tape_cfr_backward(rec, BW, w.shape[1], w)
+        return P.tape(rec)["adj"].clone().double()
+
+    def same(a, b):
+        big = float(a.abs().max())
+        assert big > 0
+        assert bool(torch.all((a - b).abs() <= 2.0 ** -23 * a.abs() + 1e-10 * big))
+    w = torch.randn(n_rx, n, 2, dtype=torch.complex128, generator=torch.Generator().manual_seed(n)).cuda()
+    fine = torch.zeros(n_rx, 2 * n - 1, 2, dtype=torch.complex128, device="cuda")
+    fine[:, ::2] = w
+    same(rows(w), rows(fine))
+    if n % 2:
+        three = w[:, [0, n // 2, n - 1]].contiguous()
+        sparse = torch.zeros_like(w)
+        sparse[:, [0, n // 2, n - 1]] = three
+        same(rows(three), rows(sparse))
+
+
+def test_cfr_adjoint_of_few_rays_and_many_samples_shares_the_samples(env):
+    """31 times the samples of one receiver: the chip is idle enough at 129 of them for much less than 31 times the time
+    (3 times with the lanes on the samples, 22 times with every ray's samples in one lane)."""
+    torch, P, diff, _, _, _ = env
+    print("[gpu-test] adjoint time", flush=True)
+    rec = _room_tape(P, diff, 300, 2, 1)
+    ms = []
+    for n in (129, 4001):
+        w = torch.ones(1, n, 2, dtype=torch.complex128, device="cuda")
+        P.tape_cfr_backward(rec, BW, n, w)
+        best = 1e9
+        for _ in range(8):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(8):
+                P.tape_cfr_backward(rec, BW, n, w)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 8)
+        ms.append(best)
+    assert ms[1] < 8 * ms[0], ms
