@@ -546,73 +546,205 @@ __device__ __forceinline__ cd cd_cycles(double t) {  // e^{j 2 pi t}
     return {c, sn};
 }
 
-// Block (receiver r, 4 frequencies), 16 wavefronts: the path list is cut into 16
-// contiguous ranges, one per wavefront. Lane l takes paths l, l + 64, ... of its
-// range and adds their rotated amplitudes to the block's 4 frequencies in
-// its own registers (16 sums); at the end the wavefront's lanes are added by
+// A path's share of a sample (TE re, im, TM re, im), and its phasor at the next one.
+__device__ __forceinline__ void cfr_add(const CfrPath &p, cd step, double *acc, cd &e) {
+    acc[0] = fma(p.te.re, e.re, fma(-p.te.im, e.im, acc[0]));
+    acc[1] = fma(p.te.re, e.im, fma(p.te.im, e.re, acc[1]));
+    acc[2] = fma(p.tm.re, e.re, fma(-p.tm.im, e.im, acc[2]));
+    acc[3] = fma(p.tm.re, e.im, fma(p.tm.im, e.re, acc[3]));
+    e = {fma(e.re, step.re, -e.im * step.im), fma(e.re, step.im, e.im * step.re)};
+}
+
+// Block (receiver r, kCfrF samples): the path list is cut into 16 contiguous
+// ranges, dealt to the block's wavefronts. Lane l takes paths l, l + 64, ... of a range
+// and adds their rotated amplitudes to the block's samples in its own
+// registers (4 sums each); at the end of a range the wavefront's lanes are added by
 // halves, then the ranges in order. The order of the FP64 sums is fixed and
 // independent of the sample count, so results are reproducible.
 //
 // What bounds it: FP64 issue and the number of blocks. A path is evaluated once
-// per lane, tile and receiver (some 150 FP32 operations and two sincospi),
-// then 12 multiply-adds per sample; tiles of 4 keep enough blocks for the chip
-// (tiles of 16 would repeat less, on a fifth of the compute units). A sincos
-// per path and sample in tiles of 16 took 176 us for 12k paths x 6 receivers x
-// 129 samples; this takes 50.
-constexpr uint32_t kCfrWaves = 16, kCfrF = 4;
+// per lane, block and receiver (some 150 FP32 operations and a sincospi), then a
+// sincospi and 48 multiply-adds per run of 4 samples. A sincos per path and sample in
+// tiles of 16 took 176 us for 12k paths x 6 receivers x 129 samples; this takes 50.
+// Eight wavefronts with 16 samples: 64 sums are 128 registers, of 256 there.
+constexpr uint32_t kCfrRanges = 16, kCfrRun = 4;
+template <uint32_t kCfrF, uint32_t kCfrWaves>
 __global__ __launch_bounds__(kCfrWaves * kWave) void k_tape_cfr(LaunchArgs A, double bw, uint32_t N, double *cfr) {
-    __shared__ double red[kCfrWaves][4 * kCfrF];
+    __shared__ double red[kCfrRanges][4 * kCfrF];
     const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     const uint32_t r = blockIdx.x, n0 = blockIdx.y * kCfrF;
     const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0;
     const uint32_t nd = (A.flags & 4) ? A.D.T * A.D.K : 0;
     const uint32_t total = 1 + nk + nd;
-    const double f0 = -cfr_df(n0, N, bw), df = -cfr_step(N, bw);
-    const uint32_t lo = (uint32_t)((uint64_t)total * wv / kCfrWaves);
-    const uint32_t hi = (uint32_t)((uint64_t)total * (wv + 1) / kCfrWaves);
-    double acc[4 * kCfrF];
+    const double df = -cfr_step(N, bw);
+    for (uint32_t q = wv; q < kCfrRanges; q += kCfrWaves) {
+        const uint32_t lo = (uint32_t)((uint64_t)total * q / kCfrRanges);
+        const uint32_t hi = (uint32_t)((uint64_t)total * (q + 1) / kCfrRanges);
+        double acc[4 * kCfrF];
 #pragma unroll
-    for (uint32_t i = 0; i < 4 * kCfrF; ++i) acc[i] = 0.0;
-    for (uint32_t j = lo + lane; j < hi; j += kWave) {
-        CfrPath p{};
-        if (!cfr_path(A, j, r, nk, p)) continue;
-        cd e = cd_cycles(f0 * p.tau);
-        const cd step = cd_cycles(df * p.tau);
+        for (uint32_t i = 0; i < 4 * kCfrF; ++i) acc[i] = 0.0;
+        for (uint32_t j = lo + lane; j < hi; j += kWave) {
+            CfrPath p{};
+            if (!cfr_path(A, j, r, nk, p)) continue;
+            const cd step = cd_cycles(df * p.tau);
 #pragma unroll
-        for (uint32_t k = 0; k < kCfrF; ++k) {
-            acc[4 * k] = fma(p.te.re, e.re, fma(-p.te.im, e.im, acc[4 * k]));
-            acc[4 * k + 1] = fma(p.te.re, e.im, fma(p.te.im, e.re, acc[4 * k + 1]));
-            acc[4 * k + 2] = fma(p.tm.re, e.re, fma(-p.tm.im, e.im, acc[4 * k + 2]));
-            acc[4 * k + 3] = fma(p.tm.re, e.im, fma(p.tm.im, e.re, acc[4 * k + 3]));
-            e = {fma(e.re, step.re, -e.im * step.im), fma(e.re, step.im, e.im * step.re)};
+            for (uint32_t k0 = 0; k0 < kCfrF; k0 += kCfrRun) {
+                cd e = cd_cycles(-cfr_df(n0 + k0, N, bw) * p.tau);
+#pragma unroll
+                for (uint32_t k = k0; k < k0 + kCfrRun; ++k) cfr_add(p, step, acc + 4 * k, e);
+            }
         }
-    }
-    // lane sums by halves: a lane keeps the half of its sums that its bit names, so
-    // lane l ends with sum l / 4 of its 16-lane class, and two plain steps add those
+        // lane sums by halves: a lane keeps the half of its sums that its bit names, from bit 5
+        // on, until one sum is left, and plain steps over the bits that remain end it
+        constexpr uint32_t kKeep = kWave / (4 * kCfrF);  // lanes that end with the same sum
+        static_assert(kKeep >= 1, "a sum per lane at most");
 #pragma unroll
-    for (uint32_t o = 2 * kCfrF; o > 0; o >>= 1) {
-        const bool up = lane & (4 * o);
+        for (uint32_t o = 2 * kCfrF; o > 0; o >>= 1) {
+            const bool up = lane & (kKeep * o);
 #pragma unroll
-        for (uint32_t i = 0; i < o; ++i) {
-            const double keep = up ? acc[o + i] : acc[i], give = up ? acc[i] : acc[o + i];
-            acc[i] = keep + __shfl_xor(give, (int)(4 * o), kWave);
+            for (uint32_t i = 0; i < o; ++i) {
+                const double keep = up ? acc[o + i] : acc[i], give = up ? acc[i] : acc[o + i];
+                acc[i] = keep + __shfl_xor(give, (int)(kKeep * o), kWave);
+            }
         }
+#pragma unroll
+        for (uint32_t o = kKeep / 2; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], (int)o, kWave);
+        if (lane % kKeep == 0) red[q][lane / kKeep] = acc[0];
     }
-    acc[0] += __shfl_xor(acc[0], 2, kWave);
-    acc[0] += __shfl_xor(acc[0], 1, kWave);
-    if (lane % 4 == 0) red[wv][lane / 4] = acc[0];
     __syncthreads();
     const uint32_t n = n0 + threadIdx.x / 4;
     if (threadIdx.x < 4 * kCfrF && n < N) {
         double v = 0.0;
-        for (uint32_t k = 0; k < kCfrWaves; ++k) v += red[k][threadIdx.x];
+        for (uint32_t k = 0; k < kCfrRanges; ++k) v += red[k][threadIdx.x];
         cfr[((size_t)r * N + n) * 4 + threadIdx.x % 4] = v;
     }
 }
 
+// Recordings without diffuse connections: many keys, of which a receiver has a
+// few paths. The paths that exist, in their order, are cut into the 16 ranges; a
+// range fills a few lanes, and the wavefront's other lanes take further runs of the
+// receiver's samples. A lane with one path evaluates it once for all runs of its
+// block. A block marks the keys that are paths, 64 to a word, and counts the
+// marks before each word; path i is found from those. What bounds it is a block's
+// fixed cost (the keys looked through, one path's chain of loads), so blocks are as
+// many as the chip holds at once (one per compute unit: 127 registers). 6 receivers,
+// 129 / 4 001 / 20 001 samples, us, launch to launch: 55 keys 11 / 14 / 40, 231 keys 11 / 16 / 43;
+// with the kernel above 10 / 106 / 513 and 11 / 117 / 554, with a sincos per path and sample 15 / 28 /
+// 107 and 15 / 40 / 169. (734 keys, 129 samples: 14, the kernel above 11.)
+constexpr uint32_t kCfrWords = 4096;
+__device__ __forceinline__ uint32_t nth_bit(uint64_t m, uint32_t n) {  // place of the n-th set bit
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t s = 32; s > 0; s >>= 1) {
+        const uint32_t below = (uint32_t)__popcll(m >> at & ((1ull << s) - 1));
+        if (n >= below) {
+            n -= below;
+            at += s;
+        }
+    }
+    return at;
+}
+__global__ __launch_bounds__(kCfrRanges * kWave) void k_tape_cfr_spec(LaunchArgs A, double bw, uint32_t N, double *cfr) {
+    constexpr uint32_t kMin = 4, kMax = 32, kSums = 4 * kCfrRun;  // lanes of a run of samples, sums of one
+    __shared__ double red[kCfrRanges][kWave / kMin][kSums];
+    __shared__ uint64_t mark[kCfrWords];
+    __shared__ uint32_t before[kCfrWords];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, r = blockIdx.x;
+    const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0, n_words = (nk + kWave - 1) / kWave;
+    for (uint32_t c = wv; c < n_words; c += kCfrRanges) {
+        const uint32_t q = c * kWave + lane;
+        const uint64_t m = __ballot(q < nk && A.sb.valid[(size_t)q * A.D.n_rx + r]);
+        if (lane == 0) mark[c] = m;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        uint32_t n = 0;
+        for (uint32_t c0 = 0; c0 < n_words; c0 += kWave) {
+            const uint32_t c = c0 + lane, own = c < n_words ? (uint32_t)__popcll(mark[c]) : 0u;
+            uint32_t in = own;
+            for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+                const uint32_t v = __shfl_up(in, o, kWave);
+                if (lane >= o) in += v;
+            }
+            if (c < n_words) before[c] = n + in - own;
+            n += __shfl(in, kWave - 1, kWave);
+        }
+    }
+    __syncthreads();
+    // path 0 is the line of sight
+    const uint32_t n_paths = 1 + (n_words ? before[n_words - 1] + (uint32_t)__popcll(mark[n_words - 1]) : 0u);
+    const uint32_t lo = n_paths * wv / kCfrRanges, hi = n_paths * (wv + 1) / kCfrRanges;
+    uint32_t lanes = kMin;
+    while (lanes < kMax && lanes * kCfrRanges < n_paths) lanes *= 2;
+    const bool once = lanes * kCfrRanges >= n_paths;
+    const uint32_t runs = kWave / lanes, groups = (N + runs * kCfrRun - 1) / (runs * kCfrRun);
+    const double df = -cfr_step(N, bw);
+    CfrPath p{};
+    bool is = false;
+    cd step = {1.0, 0.0};
+    auto path = [&](uint32_t i) {
+        uint32_t j = 0;
+        if (i > 0) {
+            uint32_t a = 0, b = n_words - 1;  // the last word with at most i - 1 marks before it
+            while (a < b) {
+                const uint32_t m = (a + b + 1) / 2;
+                if (before[m] < i) a = m;
+                else b = m - 1;
+            }
+            j = 1 + a * kWave + nth_bit(mark[a], i - 1 - before[a]);
+        }
+        is = cfr_path(A, j, r, nk, p);
+        step = cd_cycles(df * p.tau);
+    };
+    bool have = false;
+    for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
+        const uint32_t n0 = (g * runs + lane / lanes) * kCfrRun;
+        double acc[kSums];
+#pragma unroll
+        for (uint32_t i = 0; i < kSums; ++i) acc[i] = 0.0;
+        for (uint32_t i = lo + lane % lanes; i < hi; i += lanes) {
+            if (!have) {
+                path(i);
+                have = once;
+            }
+            if (!is) continue;  // (no line of sight)
+            cd e = cd_cycles(-cfr_df(n0, N, bw) * p.tau);
+#pragma unroll
+            for (uint32_t k = 0; k < kCfrRun; ++k) cfr_add(p, step, acc + 4 * k, e);
+        }
+        for (uint32_t o = lanes / 2; o > 0; o >>= 1)
+#pragma unroll
+            for (uint32_t i = 0; i < kSums; ++i) acc[i] += __shfl_xor(acc[i], (int)o, kWave);
+        if (lane % lanes == 0)
+#pragma unroll
+            for (uint32_t i = 0; i < kSums; ++i) red[wv][lane / lanes][i] = acc[i];
+        __syncthreads();
+        const uint32_t n = g * runs * kCfrRun + threadIdx.x / 4;
+        if (threadIdx.x < runs * kSums && n < N) {
+            double v = 0.0;
+            for (uint32_t k = 0; k < kCfrRanges; ++k) v += (&red[k][0][0])[threadIdx.x];
+            cfr[((size_t)r * N + n) * 4 + threadIdx.x % 4] = v;
+        }
+        __syncthreads();
+    }
+}
+
+// Samples of a block: the more, the less a path is evaluated again, and the fewer blocks there are. 4 while those
+// are no more than the compute units, 8 while blocks of 8 are not, then 16. 12 000 rays, 12 receivers, us with 4 / 8 / 16:
+// 17 samples 75 / 91 / 151, 129: 159 / 99 / 151, 300: 302 / 185 / 152, 4 001: 3 424 / 2 147 / 1 804; 6 000 rays, 1 receiver: 1 000
+// samples 50 / 56 / 88, 2 000: 94 / 60 / 88, 4 001: 173 / 107 / 88. (A response's bits are the same with each.)
 void launch_tape_cfr(const LaunchArgs &A, double bw, uint32_t N, double *cfr, hipStream_t s) {
-    hipLaunchKernelGGL(k_tape_cfr, dim3(A.D.n_rx, (N + kCfrF - 1) / kCfrF), dim3(kCfrWaves * kWave), 0, s, A, bw, N,
-                       cfr);
+    static const uint32_t cus = compute_units();
+    const uint32_t n_rx = A.D.n_rx;
+    if (!(A.flags & 4) && A.D.rec_keys <= kCfrWords * kWave) {
+        const uint32_t g = std::max(1u, std::min((N + 15) / 16, cus / n_rx));
+        hipLaunchKernelGGL(k_tape_cfr_spec, dim3(n_rx, g), dim3(kCfrRanges * kWave), 0, s, A, bw, N, cfr);
+        return;
+    }
+    auto blocks = [&](uint32_t f) { return (uint64_t)n_rx * ((N + f - 1) / f); };
+    const uint32_t f = blocks(4) <= cus ? 4 : blocks(8) <= cus ? 8 : 16;
+    auto *k = f == 4 ? k_tape_cfr<4, 16> : f == 8 ? k_tape_cfr<8, 16> : k_tape_cfr<16, 8>;
+    hipLaunchKernelGGL(k, dim3(n_rx, (N + f - 1) / f), dim3((f == 16 ? 8 : 16) * kWave), 0, s, A, bw, N, cfr);
 }
 
 // dL/da_p (as gR + j gI per polarisation) of one path from dL/dH_r:

@@ -224,3 +224,68 @@ def test_cfr_adjoint_of_few_rays_and_many_samples_shares_the_samples(env):
             best = min(best, e[0].elapsed_time(e[1]) / 8)
         ms.append(best)
     assert ms[1] < 8 * ms[0], ms
+
+
+@pytest.mark.parametrize("flags", [LOS, LOS | SPEC, LOS | SPEC | DIFF])
+def test_cfr_centre_sample_has_the_same_bits_in_every_tiling(env, flags):
+    """Blocks take 4, 8 or 16 samples by the number of them (3 receivers: up to 341, 682 and more), or several runs of 4
+    where there are few paths. The centre of 8 m + 1 samples starts a run of 4, with the phase factor 1."""
+    torch, P, diff, s, sg, rx = env
+    rec = diff.record(sg, _mats(7, 0.3), scenes.BOX_TX, rx, FC, NR, K=3, flags=flags)
+    P.tape_fresnel(rec, _mats(7, 0.3))
+    one = P.tape_cfr(rec, BW, 1)[:, 0]
+    for n in (9, 129, 337, 345, 513, 681, 689, 1001, 4001, 20_001):
+        assert torch.equal(P.tape_cfr(rec, BW, n)[:, n // 2], one), n
+
+
+@pytest.mark.parametrize("flags,rays,K,n_rx", [(LOS | SPEC, 1, 1, 1), (LOS | SPEC, 6000, 2, 6), (LOS | SPEC, 6000, 3, 70),
+                                               (LOS | SPEC | DIFF, 300, 2, 1), (LOS | SPEC | DIFF, 1000, 3, 6),
+                                               (LOS | SPEC | DIFF, 3000, 8, 4)])
+def test_cfr_sample_counts_agree_at_many_samples(env, flags, rays, K, n_rx):
+    """Sample k of n is sample 2 k of 2 n - 1 (phases of 500 cycles at most in FP64: 1e-11 of the largest sample)."""
+    torch, P, diff, s, sg, _ = env
+    rx = np.random.default_rng(n_rx).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (n_rx, 3)).astype(np.float32)
+    rec = diff.record(sg, _mats(7, 0.3), scenes.BOX_TX, rx, FC, rays, K=K, flags=flags)
+    P.tape_fresnel(rec, _mats(7, 0.3))
+    for n in (3, 171, 342, 601, 1001):
+        a, b = P.tape_cfr(rec, BW, n), P.tape_cfr(rec, BW, 2 * n - 1)[:, ::2]
+        assert float((a - b).abs().max()) <= 1e-11 * float(a.abs().max()) > 0, n
+
+
+def test_cfr_of_many_specular_paths(env):
+    """More paths than a block's lanes hold at once, out of many thousand keys, against the kernel that goes through all
+    keys (taken by recordings of more than 2^18 keys): the same FP64 sums in another order (1e-12 of the sum of |terms|)."""
+    torch, P, diff, s, sg, rx = env
+    out = []
+    for cap in (0, (1 << 18) + 64):
+        rec = diff.record(sg, _mats(7, 0.0), scenes.BOX_TX, rx[:2], FC, 100_000, K=8, flags=LOS | SPEC, key_capacity=cap)
+        P.tape_fresnel(rec, _mats(7, 0.0))
+        v = P.paths(rec)
+        assert v["valid"].sum(0).max() > 512
+        mag = float(np.abs(v["amp_te"]).sum(0).max() + np.abs(v["amp_tm"]).sum(0).max())
+        out.append([P.tape_cfr(rec, BW, n) for n in (1, 130, 1001)])
+        del rec
+    for a, b in zip(*out):
+        assert float((a - b).abs().max()) <= 1e-12 * max(mag, 1e-6) and float(a.abs().max()) > 0
+
+
+def test_cfr_of_few_paths_and_many_samples_shares_the_lanes(env):
+    """31 times the samples of some 50 keys: the lanes without a path take further samples (1.3 times the time; 10 times
+    with a block of 16 wavefronts per 4 samples)."""
+    torch, P, diff, s, sg, rx = env
+    rec = diff.record(sg, _mats(7, 0.0), scenes.BOX_TX, np.tile(rx, (2, 1)), FC, NR, K=2, flags=LOS | SPEC)
+    P.tape_fresnel(rec, _mats(7, 0.0))
+    ms = []
+    for n in (129, 4001):
+        P.tape_cfr(rec, BW, n)
+        best = 1e9
+        for _ in range(8):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(8):
+                P.tape_cfr(rec, BW, n)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 8)
+        ms.append(best)
+    assert ms[1] < 5 * ms[0], ms
