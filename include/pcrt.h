@@ -82,7 +82,7 @@ typedef struct {
 enum {
     PCRT_BUILD_LBVH = 1, /* Karras radix tree over Morton codes of the disk centres */
     PCRT_BUILD_PLOC = 2  /* locally-ordered clustering: mutual nearest neighbours by merged surface area within
-                            +-16 positions of the Morton order, disks renumbered depth-first */
+                            +-6 positions of the Morton order, disks renumbered depth-first */
 };
 
 /* Scene statistics filled by pcrt_scene_create. */
@@ -383,8 +383,9 @@ pcrt_status pcrt_diffraction_workspace_size(const pcrt_scene *scene, uint32_t n_
  * leaves this field to its EM back end. Amplitudes are normalised like the
  * other path types (isotropic antennas, lambda/4pi). edges, mats (pcrt_material
  * [n_labels]; labels beyond it read label n_labels - 1), rx (float[n_rx][3]):
- * device. out: device double[n_rx][5] = G, h_TE re, im, h_TM re, im (sums over
- * edges in edge order). pair_amp: optional device float[n_rx][n_edges][4]
+ * device. out: device double[n_rx][5] = G, h_TE re, im, h_TM re, im (FP64 sums
+ * in a fixed order: edges i, i + L, ... for every i < L, then those pairwise in a
+ * fixed tree, with L = 64 or the power of two from n_edges on). pair_amp: optional device float[n_rx][n_edges][4]
  * (TE re, im, TM re, im; 0 where no path). Asynchronous, allocates nothing.
  * Errors: EINVAL for NULL pointers, zero sizes, freq <= 0; ENOMEM for a small ws. */
 pcrt_status pcrt_diffraction(const pcrt_scene *scene, const pcrt_edge *edges, uint32_t n_edges,

@@ -67,3 +67,49 @@ def test_diffraction_errors(P, small_office):
     with pytest.raises(P.PcrtError) as e:
         P.diffraction(sg, edges, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, scenes.office_rx()[:2], -1.0)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("n_edges,n_rx", [(1, 1), (1, 65), (1, 5001), (2, 33), (3, 22), (5, 7), (32, 3), (33, 2), (64, 2),
+                                          (65, 1), (160, 9)])
+def test_diffraction_sums_of_a_receiver(P, small_office, n_edges, n_rx):
+    """A receiver has as many lanes as there are edges, a power of two: the sums against those of the per-pair
+    amplitudes (FP64 sums of at most n_edges FP32 terms)."""
+    sg = P.Scene.from_scene(small_office, leaf_size=2, width=4)
+    edges = scenes.office_edges(small_office)
+    edges = (edges[0][-n_edges:], edges[1][-n_edges:])
+    rx = np.resize(scenes.office_rx(), (n_rx, 3))
+    step("diffraction sums, %d edges, %d receivers" % (n_edges, n_rx))
+    out, amp = P.diffraction(sg, edges, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx, 3.5e9, want_pairs=True)
+    amp, out = np.asarray(amp).astype(np.complex128), out.cpu().numpy()
+    te, tm = amp[..., 0], amp[..., 1]
+    want = np.stack([0.5 * (abs(te) ** 2 + abs(tm) ** 2).sum(1), te.real.sum(1), te.imag.sum(1), tm.real.sum(1),
+                     tm.imag.sum(1)], 1)
+    size = np.abs(amp).sum((1, 2))
+    assert np.all(np.abs(out - want) <= 2.0 ** -52 * (n_edges + 4) * np.maximum(size, size ** 2)[:, None])
+
+
+def test_diffraction_of_one_edge_takes_a_lane_per_receiver(P, small_office):
+    """400 times the receivers of one edge: the chip is idle at 1 000 of them (1.2 times the time with a lane per receiver,
+    15 times with a wavefront each)."""
+    import torch
+    sg = P.Scene.from_scene(small_office, leaf_size=2, width=4)
+    edges = scenes.office_edges(small_office)
+    edges = P.edges_tensor(edges[0][:1], edges[1][:1])
+    mats = P.materials_tensor(scenes.OFFICE_MATERIALS)
+    ms = []
+    for n in (1000, 400_000):
+        rx = torch.as_tensor(np.resize(scenes.office_rx(), (n, 3)).astype(np.float32), device="cuda")
+        step("diffraction time, %d receivers" % n)
+        P.diffraction(sg, edges, mats, scenes.OFFICE_TX, rx, 3.5e9)
+        best = 1e9
+        for _ in range(8):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(4):
+                P.diffraction(sg, edges, mats, scenes.OFFICE_TX, rx, 3.5e9)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 4)
+        ms.append(best)
+    print(ms)
+    assert ms[1] < 6 * ms[0], ms
