@@ -659,6 +659,12 @@ __device__ __forceinline__ void flush_visits(const St &stk, uint64_t *counters, 
     }
 }
 
+// A wavefront's share of a result counter: thousands of wavefronts end with one, most launches with some that have
+// nothing to add, and an atomic on one word costs 11 ns whoever issues it.
+__device__ __forceinline__ void add_to(uint32_t v, uint64_t *counter) {
+    if (v) atomicAdd((unsigned long long *)counter, (unsigned long long)v);
+}
+
 // Item of a flattened ray slot (items sorted by ray_off).
 __device__ __forceinline__ int find_item(const Item *items, int n_items, uint32_t g) {
     int lo = 0, hi = n_items - 1;

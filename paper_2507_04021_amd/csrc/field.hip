@@ -349,8 +349,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     if (kCountVisits)
         for (int o = 32; o > 0; o >>= 1) n_occ_visits += __shfl_xor(n_occ_visits, o, kWave);
     if (lane == 0) {
-        atomicAdd((unsigned long long *)&A.counters[2], (unsigned long long)n_seg);
-        atomicAdd((unsigned long long *)&A.counters[5], (unsigned long long)n_vis);
+        add_to(n_seg, &A.counters[2]);
+        add_to(n_vis, &A.counters[5]);
         if (kCountVisits) atomicAdd((unsigned long long *)&A.counters[15], (unsigned long long)n_occ_visits);
     }
 }
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(kDpsWaves * kWave) void k_dps_diffuse(LaunchArgs A,
     }
     dps_block_sum(red, w, lane, acc, r < n_rx ? A.diff_part + ((size_t)c * n_rx + r) * 5 : nullptr);
     n_vis = warp_sum_u(n_vis);
-    if (lane == 0 && n_vis) atomicAdd((unsigned long long *)&A.counters[5], (unsigned long long)n_vis);
+    if (lane == 0) add_to(n_vis, &A.counters[5]);
 }
 
 // The visibility matrix of 64 receivers in words, [receivers / 64][set]: bit b of group y is receiver 64 y + b.

@@ -295,6 +295,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
     const uint32_t slice = shape.slice, parts = shape.parts, part_keys = kKeyChunk / parts;
     const uint32_t n_slices = (n_rx + slice - 1) / slice;
     const uint32_t n_units = n_chunks * n_slices * parts;
+    if (blockIdx.x >= n_units) return;  // (3 072 wavefronts asking the counter for 36 units: 104 us, 29 so)
     const bool one_open = parts > 1;  // parts are few pairs: a second would only take them from another wavefront
     const bool rec = A.flags & 8;
     const float eps_self = A.thr.eps_self, eps_tie = A.thr.eps_tie;
@@ -570,8 +571,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
     n_cand = warp_sum_u(n_cand);
     n_valid = warp_sum_u(n_valid);
     if (lane == 0) {
-        atomicAdd((unsigned long long *)&A.counters[7], (unsigned long long)n_cand);
-        atomicAdd((unsigned long long *)&A.counters[4], (unsigned long long)n_valid);
+        add_to(n_cand, &A.counters[7]);
+        add_to(n_valid, &A.counters[4]);
     }
 }
 

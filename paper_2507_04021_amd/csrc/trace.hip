@@ -225,9 +225,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     n_ray = warp_sum_u(n_ray);
     n_spill = warp_sum_u(n_spill);
     if (lane == 0) {
-        atomicAdd((unsigned long long *)&A.counters[0], (unsigned long long)n_int);
-        atomicAdd((unsigned long long *)&A.counters[1], (unsigned long long)n_ray);
-        atomicAdd((unsigned long long *)&A.counters[8], (unsigned long long)n_spill);
+        add_to(n_int, &A.counters[0]);
+        add_to(n_ray, &A.counters[1]);
+        add_to(n_spill, &A.counters[8]);
     }
 }
 

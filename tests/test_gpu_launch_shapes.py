@@ -258,3 +258,22 @@ def test_diffuse_parts_do_not_change_a_receiver(P, office, rays, K):
     _, rb = solve(np.tile(rx[:64], (16, 1)))
     for k in ("segments", "diffuse"):
         assert 16 * int(rc.counters[P.CNT[k]]) == int(rb.counters[P.CNT[k]])
+
+
+def test_a_solve_with_few_hits_does_not_pay_for_idle_wavefronts(P, office):
+    """A transmitter outside the scan: a few of its rays hit, and thousands of wavefronts have nothing to refine or
+    connect. Those two stages take as long as the bounce loop (1.0 to 1.3 of it), not a queue of every wavefront at one
+    counter (3.4). The nine receivers, of which none has a path, agree with a solve of one."""
+    rx = scenes.office_rx()[:9]
+    kw = dict(K=3, flags=LOS | SPEC | DIFF)
+    ratio = []
+    for _ in range(12):
+        r = P.solve(office, scenes.OFFICE_MATERIALS, [100.0, 100.0, 100.0], rx, 3.5e9, 9000, K=3,
+                    flags=LOS | SPEC | DIFF | P.TIMING)
+        t = list(P.stage_times().values())
+        ratio.append((t[3] + t[5]) / t[1])
+    assert 0 < r.counter("interactions") < 100
+    one = P.solve(office, scenes.OFFICE_MATERIALS, [100.0, 100.0, 100.0], rx[3:4], 3.5e9, 9000, **kw)
+    assert np.array_equal(one.gain.cpu().numpy(), r.gain[3:4].cpu().numpy())
+    print(ratio)
+    assert min(ratio) < 2.2, ratio
