@@ -1,5 +1,5 @@
-"""Hierarchy builds at the edges of the builder's launches: one block's tail (1 024 clusters), tiles of 256, passes of
-4 096 nodes, both builders and all widths. Every answer of a solve is independent of the hierarchy, so each scene's
+"""Hierarchy builds at the edges of the builder's launches: one block's tail (1 024 clusters), tiles of 1 012 clusters,
+passes of 1 024 nodes, both builders and all widths. Every answer of a solve is independent of the hierarchy, so each scene's
 results on the radix tree and on wider nodes must equal those on the clustering tree's binary nodes bitwise."""
 import numpy as np
 import pytest
@@ -55,3 +55,21 @@ def test_point_sets_sort_the_bits_of_the_scene(P, rho):
     got = P.reception_points(g).cpu().numpy()
     assert got.shape == want.shape
     assert np.max(np.abs(got - want)) <= 2.0 ** -23 * 1.5  # one FP32 rounding of coordinates up to 1.5
+
+
+@pytest.mark.parametrize("n", [1012, 1013, 2024, 2025, 3037, 70_001, 300_001])
+def test_build_sizes_at_the_edges_of_a_tile(P, n):
+    """A block of a clustering pass takes 1 012 clusters (the look-back goes past one tile from 1 013 on, past the 64 that
+    one look covers from 64 769 on; a level of the wide collapse, in tiles of 256 nodes, in the largest); results as on the
+    radix tree, bitwise."""
+    sc = _scene(n, False)
+    mats = np.tile([4.0, 0.05, 0.3], (3, 1))
+    base = None
+    for builder, width in ((1, 4), (2, 4), (2, 2), (2, 8)):
+        print("[gpu-test] build n=%d builder=%d width=%d" % (n, builder, width), flush=True)
+        g = P.Scene.from_scene(sc, leaf_size=2, width=width, builder=builder)
+        r = P.solve(g, mats, [0.05, -0.02, 0.61], [[0.3, 0.2, 0.5], [-0.4, 0.1, 0.9]], 3.5e9, 2000, K=2, flags=7,
+                    want_seq=True)
+        got = [x.cpu().numpy() for x in (r.seq, r.gain, r.h_te, r.parts)]
+        base = base or got
+        assert all(np.array_equal(a, b) for a, b in zip(got, base))

@@ -96,6 +96,35 @@ def test_mlp_backward_matches_reference(env, n):
     assert np.all(grads["W4"].cpu().numpy()[5:] == 0)
 
 
+@pytest.mark.parametrize("n,n_labels", [(1, 1), (127, 3), (129, 17), (2049, 64), (32_769, 8), (33_000, 8), (65_537, 5)])
+def test_mlp_backward_counts_every_row_once(env, n, n_labels):
+    """A block takes 128 rows at a time and 256 blocks at most do, so row 32 769 starts a second round. The outputs'
+    gradients are zero but for the last row, then but for the last block's first: the sum of |terms| in the bar is that
+    row's alone. Then all rows, where a lost or doubled one of the small sizes shows in the norm (as above)."""
+    torch, P, M = env
+    params = _params(n_labels, 2)
+    rng = np.random.default_rng(n)
+    labels = rng.integers(0, n_labels, n).astype(np.int64)
+    cosv = rng.uniform(0.0, 1.0, n).astype(np.float32)
+    full = rng.normal(size=(n, 8)).astype(np.float32)
+    full[:, 5:] = 0
+    net = M.MaterialMLP(params)
+    lab, cs = _gpu_inputs(torch, labels, cosv)
+    for rows in ([n - 1], [(n - 1) // 128 * 128], range(n)):
+        rows = np.asarray(rows)
+        print("[gpu-test] mlp backward n=%d, %d rows with a gradient" % (n, rows.size), flush=True)
+        g_out = np.zeros_like(full)
+        g_out[rows] = full[rows]
+        grads = net.backward_rows(lab, cs, 3.5e9, torch.tensor(g_out, device="cuda"))
+        ref, mag = R.backward(params, labels[rows], cosv[rows].astype(np.float64), 3.5e9, g_out[rows, :5],
+                              precision="kernel", magnitudes=True)
+        for k, v in ref.items():
+            got = grads[k].cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - v) <= (2.0 ** -8 + rows.size * 2.0 ** -24) * mag[k]), (rows.size, k)
+            if rows.size > 1:
+                assert np.linalg.norm(got - v) <= 1e-3 * np.linalg.norm(v), k
+
+
 def _channel_sets(P, sg, n_sets, rays, seed):
     tx, rx = scenes.random_links(seed, n_sets, 8)
     freqs = [3.5e9 if i % 2 == 0 else 28e9 for i in range(n_sets)]
