@@ -1060,8 +1060,6 @@ SceneLayout scene_layout(uint32_t n, uint32_t width, uint32_t builder, bool dps)
     L.scan_blk = b.take(sizeof(uint32_t) * scan_blk_words(radix_hist_words(n)));
     L.child = b.take(sizeof(int2) * ni);
     L.range = b.take(sizeof(int2) * ni);
-    L.parent_int = b.take(sizeof(int) * ni);
-    L.parent_leaf = b.take(sizeof(int) * n);
     L.dbox = b.take(sizeof(float) * 6 * n);
     L.ibox = b.take(sizeof(float) * 6 * ni);
     L.flags = b.take(sizeof(uint32_t) * ni);
@@ -1080,6 +1078,10 @@ SceneLayout scene_layout(uint32_t n, uint32_t width, uint32_t builder, bool dps)
         L.leaf_pos = b.take(sizeof(uint32_t) * n);
         L.perm2 = b.take(sizeof(uint32_t) * n);
         L.pass_st = b.take(sizeof(PassState) * ((size_t)n + 8));  // every pass merges a pair
+    } else {  // the radix tree is climbed from its leaves
+        L.parent_int = b.take(sizeof(int) * ni);
+        L.parent_leaf = b.take(sizeof(int) * n);
+        if (width > 2) L.sah_pending = b.take(sizeof(uint32_t) * ni);
     }
     if (width > 2) {  // every wide node stands for a distinct binary internal node
         L.wnode = b.take(sizeof(float) * 8 * width * (size_t)ni);
@@ -1087,7 +1089,6 @@ SceneLayout scene_layout(uint32_t n, uint32_t width, uint32_t builder, bool dps)
         L.qref = b.take(sizeof(int) * width * (size_t)ni);
         L.front0 = b.take(sizeof(int) * ni);
         L.front1 = b.take(sizeof(int) * ni);
-        L.sah_pending = b.take(sizeof(uint32_t) * ni);
         L.sah_cost = b.take(sizeof(float) * width * (size_t)ni);
         L.sah_choice = b.take((size_t)width * ni);
     }

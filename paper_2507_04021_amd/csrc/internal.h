@@ -43,16 +43,17 @@ constexpr uint32_t kBuildPloc = 2;  // locally-ordered clustering (surface-area 
 
 struct SceneLayout {
     size_t pos_id, nrm_id, disk, node, stat, bounds, blk_bounds;
-    size_t code0, code1, idx0, idx1, hist, scan_blk, child, range, parent_int, parent_leaf, dbox, ibox, flags;
+    size_t code0, code1, idx0, idx1, hist, scan_blk, child, range, dbox, ibox, flags;
     uint32_t width = 2;                             // node width of the traversed hierarchy
     uint32_t n_internal = 1;                        // binary internal nodes (buffer capacity)
     uint32_t builder = kBuildLbvh;
+    size_t parent_int = 0, parent_leaf = 0, sah_pending = 0;    // radix tree (builder == kBuildLbvh)
     size_t cbox[2] = {0, 0}, cid[2] = {0, 0}, csz[2] = {0, 0};  // clustering build (builder == kBuildPloc)
     size_t nsize = 0, noff = 0, leaf_pos = 0, perm2 = 0, pass_st = 0;
     size_t tile_status[2] = {0, 0}, ticket = 0;     // scans of the passes (clustering) and levels (wide collapse)
     size_t wnode = 0, front0 = 0, front1 = 0, level_st = 0;         // wide collapse (width > 2)
     size_t qnode = 0, qref = 0;                                     // its compact any-hit copy
-    size_t sah_pending = 0, sah_cost = 0, sah_choice = 0;           // its surface-area choices
+    size_t sah_cost = 0, sah_choice = 0;                            // its surface-area choices
     size_t dps_pt = 0, dps_off = 0, dps_of = 0, dps_flag = 0, dps_blk = 0, dps_stat = 0, dps_recv = 0;  // point sets
     size_t total;
 };

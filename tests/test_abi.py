@@ -194,3 +194,20 @@ def test_status_poll_decodes_every_bit(L):
     c[6] = 0
     c[0] = 123  # other counters are not status
     assert L.pcrt_status_poll(c) == 0
+
+
+def test_scene_workspace_holds_what_its_builder_uses(L):
+    """The clustering build adds, per point, two lists of clusters (box, node, size: 32 B each), a node's size, offset
+    and pass, a leaf's place and the final order (24 B); the radix tree's parent links (8 B) and, with wide nodes, its
+    countdown (4 B) are the radix build's own."""
+    n = 1 << 20
+    nb = ctypes.c_size_t(0)
+    size = {}
+    for builder in (1, 2):
+        for width in (2, 4, 8):
+            o = P.BvhOpts(4, width, builder)
+            assert L.pcrt_scene_workspace_size(n, ctypes.byref(o), ctypes.byref(nb)) == 0
+            size[builder, width] = nb.value
+    for width in (2, 4, 8):
+        extra = 64 + 24 - 8 - (4 if width > 2 else 0)
+        assert abs(size[2, width] - size[1, width] - extra * n) < 65536
