@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kWave) void k_diffraction_sum(const float4 *amp, ui
 // Four lanes per pair while their wavefronts (24 KiB of stacks each, 6 to a compute unit) are resident together; beyond,
 // the chip is full and the geometry done four times over is lost. 64 receivers x 160 edges of the 1M-point office, call
 // to call: 108 us with one lane per pair, 77 with four, 64 with the series' terms taken by fours.
-constexpr uint32_t kFourLanePairs = 6 * 256 * kWave / 4;
+constexpr uint32_t kFourLaneWaves = 6;  // per compute unit
 
 uint32_t diffraction_blocks(uint32_t n_edges, uint32_t n_rx) { return (n_edges * n_rx + kWave - 1) / kWave; }
 
@@ -294,7 +294,8 @@ void launch_diffraction(const DevScene &S, const pcrt_edge *edges, uint32_t n_ed
     A.trim = 2.0f * sqrtf(S.r2);
     A.amp = amp;
     const uint32_t pairs = n_edges * n_rx;
-    const bool four = pairs <= kFourLanePairs;
+    static const uint32_t four_lane_pairs = kFourLaneWaves * compute_units() * kWave / 4;
+    const bool four = pairs <= four_lane_pairs;
     const dim3 g(four ? (4 * pairs + kWave - 1) / kWave : diffraction_blocks(n_edges, n_rx));
     auto *k = S.width == 8   ? (four ? k_diffraction<8, 4> : k_diffraction<8, 1>)
               : S.width == 4 ? (four ? k_diffraction<4, 4> : k_diffraction<4, 1>)

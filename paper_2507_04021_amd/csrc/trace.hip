@@ -267,9 +267,9 @@ uint32_t trace_cap_w(uint32_t width) {
 // 88 us with 64 lanes, 72 / 67 / 62 / 98 with 16 / 8 / 4 / 1; but 65 537 rays,
 // K = 3 (already a wavefront of 64 per SIMD): 0.295 ms, 0.304 / 0.366 with 32 / 16.
 static uint32_t trace_lanes(const SolveDims &D) {
-    constexpr uint32_t kSimds = 1024;
+    static const uint32_t simds = 4 * compute_units();
     uint32_t lanes = 4;
-    while (lanes < (uint32_t)kWave && (D.T + lanes - 1) / lanes > kSimds) lanes <<= 1;
+    while (lanes < (uint32_t)kWave && (D.T + lanes - 1) / lanes > simds) lanes <<= 1;
     return lanes;
 }
 
