@@ -67,15 +67,15 @@ def ops_node(width):
 # built from; a figure is reported only while its sources still match.
 _CSRC = "paper_2507_04021_amd/csrc/"
 TRAFFIC = {
-    "k_diffuse": {"bytes": 2464665824, "l2_hit_rate": 0.977,
+    "k_diffuse": {"bytes": 2453585760, "l2_hit_rate": 0.977,
                   "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "field.hip", "bvh.hip")),
-                  "src_sha256": "8fc7f7404c99ffdb8a02c2506ee51de2cce91619e0a2d5c849bc4154aab98b52"},
-    "k_trace": {"bytes": 9825531952, "l2_hit_rate": 0.487,
+                  "src_sha256": "3b0b7518efbc2be86f8eb797fd546614838ac5c2063eb050369c6c26caaee09c"},
+    "k_trace": {"bytes": 9831484416, "l2_hit_rate": 0.486,
                 "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "trace.hip", "bvh.hip")),
-                "src_sha256": "6679726330fd032e564a6e29d2880a3ca4988cb1bcec4ca4c85930d6faa25f7f"},
-    "k_refine": {"bytes": 8871682816, "l2_hit_rate": 0.550,
+                "src_sha256": "98f921e57b61da2536679877155ef1f8c2de3a569e299768bd4d30ddf16dd0fb"},
+    "k_refine": {"bytes": 8786833792, "l2_hit_rate": 0.553,
                  "sources": tuple(_CSRC + f for f in ("common.h", "internal.h", "walk.h", "refine.h", "specular.hip", "bvh.hip")),
-                 "src_sha256": "5e5038d91e6b7ec6ac438f53ee12a894c87c6022423bf6098cdfa877396c56fa"},
+                 "src_sha256": "fef713ac7f6285d7e189dd5c3e256f9d344cf3b307b430a799624ae85ed4cdaa"},
 }
 
 

@@ -337,7 +337,8 @@ __device__ __forceinline__ float merged_half_area(const float *a, const float *b
 }
 
 // Exclusive prefixes of the tiles of one launch, passed on from tile to tile
-// (decoupled look-back): a tile publishes its sum, adds up what the tiles
+// (decoupled look-back; Merrill, Garland: Single-pass Parallel Prefix Scan with Decoupled
+// Look-back, 2016): a tile publishes its sum, adds up what the tiles
 // before it have published, 64 at a time, back to the first that already has
 // its inclusive prefix, and publishes its own. Tiles are numbered by an atomic
 // ticket, so every tile waited for has been started by a running block. Flag

@@ -206,7 +206,7 @@ struct LaunchArgs {
     HashBufs dhb;            // ... and its voxel diffuse keys (labels before the last interaction, last set)
     uint32_t *dkeylist, *dkey_off, *dchunk_off;
     uint64_t *dcnt;
-    uint32_t *work;     // [8] atomic work counters
+    uint32_t *work;     // [kWorkWords] work counters of the persistent launches
     uint64_t *counters; // [16]
     uint32_t *scan;
     uint32_t *scan_blk;

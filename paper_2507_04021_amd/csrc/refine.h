@@ -225,7 +225,7 @@ __device__ __forceinline__ void path_field(const LaunchArgs &A, uint32_t q, uint
 // of them first segments that end in a plane replacement), that is L2
 // latency and the lanes that wait for longer walks. So the walks are those of
 // the bounce loop: resumable, leaves parked, the wavefront steps them until at
-// most half of its busy lanes still walk, and the lanes whose walks ended
+// most an eighth of its busy lanes still walk, and the lanes whose walks ended
 // then decide together (plane replacement, next segment or end) and walk on
 // or take the next candidate. A lane keeps its candidate until it ends; what
 // it needs besides the walk (key planes, replaced planes, image points) is
