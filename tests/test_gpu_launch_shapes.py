@@ -277,3 +277,51 @@ def test_a_solve_with_few_hits_does_not_pay_for_idle_wavefronts(P, office):
     assert np.array_equal(one.gain.cpu().numpy(), r.gain[3:4].cpu().numpy())
     print(ratio)
     assert min(ratio) < 2.2, ratio
+
+
+def test_connections_of_one_chunk_are_dealt_over_the_chip(P, office):
+    """One transmitter with 40 000 receivers, and eight equal ones with 5 000 each: the same 40 000 units of connections,
+    in one chunk of records and in eight. A receiver's numbers are the same, and so are the times, bar the rest of
+    the call: twice as long would mean that the units of one chunk are handed out one by one."""
+    import time
+    import torch
+    n, rays = 40_000, 30
+    rng = np.random.default_rng(n)
+    at = scenes.office_rx()
+    rx = np.asarray(at[rng.integers(0, len(at), n)] + rng.uniform(-0.1, 0.1, (n, 3)), np.float32)
+    tx = np.repeat(np.asarray(scenes.OFFICE_TX, np.float32)[None], 8, 0)
+    mats = P.materials_tensor(scenes.OFFICE_MATERIALS)
+    print("[gpu-test] one chunk, many receivers", flush=True)
+
+    def timed(f):
+        r = f()
+        t = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return r, min(t)
+
+    one, t1 = timed(lambda: P.solve(office, mats, scenes.OFFICE_TX, rx, 3.5e9, rays, K=2, flags=DIFF))
+    eight, t8 = timed(lambda: P.solve_batch(office, mats, tx, np.full(8, rays), rx[:n // 8], 3.5e9, K=2, flags=DIFF))
+    assert one.counter("diffuse") > 0
+    for i in range(8):
+        assert torch.equal(eight.gain[i].reshape(-1), one.gain.reshape(-1)[:n // 8])
+    assert t1 < 2 * t8, (t1, t8)
+
+
+@pytest.mark.parametrize("n_rx,rays,K", [(1, 30, 2), (7, 300, 3), (2000, 30, 2), (2000, 700, 1), (3100, 600, 2)])
+def test_connections_of_few_chunks_do_not_change_a_receiver(P, office, n_rx, rays, K):
+    """Fewer chunks than ranges of units, walked in parts and whole, with ranges that end inside a chunk: a receiver's
+    numbers are those of a call with 6 500 receivers (a unit for every wavefront)."""
+    rng = np.random.default_rng(rays)
+    at = scenes.office_rx()
+    rx = np.asarray(at[rng.integers(0, len(at), 6500)] + rng.uniform(-0.1, 0.1, (6500, 3)), np.float32)
+    print("[gpu-test] few chunks %d x %d x %d" % (n_rx, rays, K), flush=True)
+    full = P.solve(office, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx, 3.5e9, rays, K=K, flags=DIFF)
+    part = P.solve(office, scenes.OFFICE_MATERIALS, scenes.OFFICE_TX, rx[:n_rx], 3.5e9, rays, K=K, flags=DIFF)
+    assert part.counter("diffuse") > 0 or n_rx == 1
+    for a, b in ((part.gain, full.gain), (part.h_te, full.h_te), (part.parts, full.parts)):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy()[:n_rx])
