@@ -464,11 +464,12 @@ pcrt_status pcrt_tape_backward(const pcrt_scene *scene, const pcrt_solve_params 
  * (n_freq - 1) (the centre frequency alone when n_freq == 1). The channel
  * impulse response is the inverse DFT of these samples. Paths: line of sight,
  * specular paths by key, diffuse connections by record, in that order, cut
- * into 16 contiguous ranges; 64 lanes take every 64th place of a range each, the
- * lanes' sums are added pairwise in a fixed tree and the ranges' sums in
+ * into at most 16 contiguous ranges, one per 52 records; 64 lanes take every 64th place of a
+ * range each, the lanes' sums are added pairwise in a fixed tree and the ranges' sums in
  * order, in FP64 (the paths' phasors by rotation from every fourth sample).
- * Recordings without diffuse connections (and of at most 2^18 keys) cut the list of
- * the paths that a receiver has; 4 to 32 lanes, by its length, take a range. The
+ * Recordings of at most 128 records (rays x interactions), and those without diffuse
+ * connections (and of at most 2^18 keys), add the list of the paths that a receiver has,
+ * 512 at a time: 16 lanes take every 16th each, added pairwise. The
  * order does not depend on n_freq, so results are reproducible. cfr: device double[n_rx][n_freq][4] = (H_TE re, im, H_TM
  * re, im). n_freq in 1..65535, bandwidth_hz >= 0; EINVAL otherwise. */
 pcrt_status pcrt_tape_cfr(const pcrt_scene *scene, const pcrt_solve_params *p, void *ws, double bandwidth_hz,

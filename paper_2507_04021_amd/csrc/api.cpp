@@ -1129,7 +1129,7 @@ pcrt_status pcrt_tape_cfr(const pcrt_scene *scene, const pcrt_solve_params *p, v
     if (!cfr) return fail(PCRT_EINVAL, "cfr is required");
     if (n_freq == 0 || n_freq > 65535) return fail(PCRT_EINVAL, "n_freq must be in 1..65535");
     if (!(bandwidth_hz >= 0.0) || !std::isfinite(bandwidth_hz)) return fail(PCRT_EINVAL, "bandwidth_hz must be >= 0");
-    launch_tape_cfr(A, bandwidth_hz, n_freq, cfr, (hipStream_t)stream);
+    launch_tape_cfr(A, P.n_trace, bandwidth_hz, n_freq, cfr, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return ok();
 }

@@ -555,8 +555,8 @@ __device__ __forceinline__ void cfr_add(const CfrPath &p, cd step, double *acc, 
     e = {fma(e.re, step.re, -e.im * step.im), fma(e.re, step.im, e.im * step.re)};
 }
 
-// Block (receiver r, kCfrF samples): the path list is cut into 16 contiguous
-// ranges, dealt to the block's wavefronts. Lane l takes paths l, l + 64, ... of a range
+// Block (receiver r, kCfrF samples): the path list is cut into up to 16 contiguous
+// ranges (cfr_ranges), dealt to the block's wavefronts. Lane l takes paths l, l + 64, ... of a range
 // and adds their rotated amplitudes to the block's samples in its own
 // registers (4 sums each); at the end of a range the wavefront's lanes are added by
 // halves, then the ranges in order. The order of the FP64 sums is fixed and
@@ -569,17 +569,17 @@ __device__ __forceinline__ void cfr_add(const CfrPath &p, cd step, double *acc, 
 // Eight wavefronts with 16 samples: 64 sums are 128 registers, of 256 there.
 constexpr uint32_t kCfrRanges = 16, kCfrRun = 4;
 template <uint32_t kCfrF, uint32_t kCfrWaves>
-__global__ __launch_bounds__(kCfrWaves * kWave) void k_tape_cfr(LaunchArgs A, double bw, uint32_t N, double *cfr) {
+__global__ __launch_bounds__(kCfrWaves * kWave) void k_tape_cfr(LaunchArgs A, uint32_t nd, double bw, uint32_t N,
+                                                                 uint32_t ranges, double *cfr) {
     __shared__ double red[kCfrRanges][4 * kCfrF];
     const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     const uint32_t r = blockIdx.x, n0 = blockIdx.y * kCfrF;
     const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0;
-    const uint32_t nd = (A.flags & 4) ? A.D.T * A.D.K : 0;
     const uint32_t total = 1 + nk + nd;
     const double df = -cfr_step(N, bw);
-    for (uint32_t q = wv; q < kCfrRanges; q += kCfrWaves) {
-        const uint32_t lo = (uint32_t)((uint64_t)total * q / kCfrRanges);
-        const uint32_t hi = (uint32_t)((uint64_t)total * (q + 1) / kCfrRanges);
+    for (uint32_t q = wv; q < ranges; q += blockDim.x / kWave) {
+        const uint32_t lo = (uint32_t)((uint64_t)total * q / ranges);
+        const uint32_t hi = (uint32_t)((uint64_t)total * (q + 1) / ranges);
         double acc[4 * kCfrF];
 #pragma unroll
         for (uint32_t i = 0; i < 4 * kCfrF; ++i) acc[i] = 0.0;
@@ -615,23 +615,22 @@ __global__ __launch_bounds__(kCfrWaves * kWave) void k_tape_cfr(LaunchArgs A, do
     const uint32_t n = n0 + threadIdx.x / 4;
     if (threadIdx.x < 4 * kCfrF && n < N) {
         double v = 0.0;
-        for (uint32_t k = 0; k < kCfrRanges; ++k) v += red[k][threadIdx.x];
+        for (uint32_t k = 0; k < ranges; ++k) v += red[k][threadIdx.x];
         cfr[((size_t)r * N + n) * 4 + threadIdx.x % 4] = v;
     }
 }
 
-// Recordings without diffuse connections: many keys, of which a receiver has a
-// few paths. The paths that exist, in their order, are cut into the 16 ranges; a
-// range fills a few lanes, and the wavefront's other lanes take further runs of the
-// receiver's samples. A lane with one path evaluates it once for all runs of its
-// block. A block marks the keys that are paths, 64 to a word, and counts the
-// marks before each word; path i is found from those. What bounds it is a block's
-// fixed cost (the keys looked through, one path's chain of loads), so blocks are as
-// many as the chip holds at once (one per compute unit: 127 registers). 6 receivers,
-// 129 / 4 001 / 20 001 samples, us, launch to launch: 55 keys 11 / 14 / 40, 231 keys 11 / 16 / 43;
-// with the kernel above 10 / 106 / 513 and 11 / 117 / 554, with a sincos per path and sample 15 / 28 /
-// 107 and 15 / 40 / 169. (734 keys, 129 samples: 14, the kernel above 11.)
-constexpr uint32_t kCfrWords = 4096;
+// Short lists: recordings of few rays, and those without diffuse connections (many keys, of which
+// a receiver has a few paths). A block marks the entries that are paths, 64 to a word,
+// counts the marks before each word, and evaluates the paths once into LDS, kCfrList
+// at a time; its wavefronts then take tiles of 16 samples, 16 lanes per run of 4: lane s adds
+// paths s, s + 16, ..., and the 16 sums of a run, added by halves, end one per lane. What bounds it
+// is FP64 issue (a sincospi and 48 multiply-adds per path and run) with many receivers
+// or samples, the chain of marks, prefix and one path's loads with few. Four wavefronts per block: 8 / 16 leave 10
+// rays x 2, 3 000 receivers, 1 sample at 49 / 74 us for 30. us, launch to launch, the kernel above (16 ranges) in brackets: 10 rays
+// x 2, 3 000 receivers, 1 / 64 / 700 samples: 24 (50) / 29 (383) / 128 (4 131); 64 x 2, 1 receiver: 13.7 (13.2) / 13.7
+// (13.4) / 14.2 (13.3); specular only, 1 000 x 2, 1 000 receivers: 14 / 15 / 50 (24 / 283 / 3 017).
+constexpr uint32_t kCfrWords = 4096, kCfrList = 512, kCfrListWaves = 4, kCfrTile = 16;
 __device__ __forceinline__ uint32_t nth_bit(uint64_t m, uint32_t n) {  // place of the n-th set bit
     uint32_t at = 0;
 #pragma unroll
@@ -644,16 +643,27 @@ __device__ __forceinline__ uint32_t nth_bit(uint64_t m, uint32_t n) {  // place 
     }
     return at;
 }
-__global__ __launch_bounds__(kCfrRanges * kWave) void k_tape_cfr_spec(LaunchArgs A, double bw, uint32_t N, double *cfr) {
-    constexpr uint32_t kMin = 4, kMax = 32, kSums = 4 * kCfrRun;  // lanes of a run of samples, sums of one
-    __shared__ double red[kCfrRanges][kWave / kMin][kSums];
-    __shared__ uint64_t mark[kCfrWords];
-    __shared__ uint32_t before[kCfrWords];
-    const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, r = blockIdx.x;
-    const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0, n_words = (nk + kWave - 1) / kWave;
-    for (uint32_t c = wv; c < n_words; c += kCfrRanges) {
+template <uint32_t kWords>
+__global__ __launch_bounds__(kCfrListWaves * kWave) void k_tape_cfr_list(LaunchArgs A, uint32_t nd, double bw,
+                                                                           uint32_t N, double *cfr) {
+    constexpr uint32_t kSums = 4 * kCfrRun;  // of a run, and lanes
+    static_assert(kWave / kSums * kCfrRun == kCfrTile, "a wavefront's samples");
+    struct Listed {
+        CfrPath p;
+        cd step;
+    };
+    __shared__ Listed list[kCfrList];
+    __shared__ uint64_t mark[kWords];
+    __shared__ uint32_t before[kWords];
+    __shared__ uint32_t n_marks;
+    const uint32_t lane = threadIdx.x % kWave, wv = threadIdx.x / kWave, r = blockIdx.x;
+    const uint32_t nk = (A.flags & 2) ? n_keys_rec(A) : 0, n_words = (nk + nd + kWave - 1) / kWave;
+    for (uint32_t c = wv; c < n_words; c += kCfrListWaves) {
         const uint32_t q = c * kWave + lane;
-        const uint64_t m = __ballot(q < nk && A.sb.valid[(size_t)q * A.D.n_rx + r]);
+        bool is = false;
+        if (q < nk) is = A.sb.valid[(size_t)q * A.D.n_rx + r];
+        else if (q < nk + nd) is = (A.rb.id[q - nk] >= 0) & (A.dvis[(size_t)(q - nk) * A.D.n_rx + r] != 0);
+        const uint64_t m = __ballot(is);
         if (lane == 0) mark[c] = m;
     }
     __syncthreads();
@@ -669,82 +679,101 @@ __global__ __launch_bounds__(kCfrRanges * kWave) void k_tape_cfr_spec(LaunchArgs
             if (c < n_words) before[c] = n + in - own;
             n += __shfl(in, kWave - 1, kWave);
         }
+        if (lane == 0) n_marks = n;
     }
     __syncthreads();
-    // path 0 is the line of sight
-    const uint32_t n_paths = 1 + (n_words ? before[n_words - 1] + (uint32_t)__popcll(mark[n_words - 1]) : 0u);
-    const uint32_t lo = n_paths * wv / kCfrRanges, hi = n_paths * (wv + 1) / kCfrRanges;
-    uint32_t lanes = kMin;
-    while (lanes < kMax && lanes * kCfrRanges < n_paths) lanes *= 2;
-    const bool once = lanes * kCfrRanges >= n_paths;
-    const uint32_t runs = kWave / lanes, groups = (N + runs * kCfrRun - 1) / (runs * kCfrRun);
+    const uint32_t n_paths = 1 + n_marks;  // path 0 is the line of sight
+    const uint32_t n_tiles = (N + kCfrTile - 1) / kCfrTile, sub = lane % kSums;
     const double df = -cfr_step(N, bw);
-    CfrPath p{};
-    bool is = false;
-    cd step = {1.0, 0.0};
-    auto path = [&](uint32_t i) {
-        uint32_t j = 0;
-        if (i > 0) {
-            uint32_t a = 0, b = n_words - 1;  // the last word with at most i - 1 marks before it
-            while (a < b) {
-                const uint32_t m = (a + b + 1) / 2;
-                if (before[m] < i) a = m;
-                else b = m - 1;
+    for (uint32_t i0 = 0; i0 < n_paths; i0 += kCfrList) {
+        const uint32_t n = min(n_paths - i0, kCfrList);
+        for (uint32_t i = threadIdx.x; i < n; i += kCfrListWaves * kWave) {
+            uint32_t j = 0;
+            if (i0 + i > 0) {
+                const uint32_t at = i0 + i - 1;
+                uint32_t a = 0, b = n_words - 1;  // the last word with at most `at` marks before it
+                while (a < b) {
+                    const uint32_t m = (a + b + 1) / 2;
+                    if (before[m] <= at) a = m;
+                    else b = m - 1;
+                }
+                j = 1 + a * kWave + nth_bit(mark[a], at - before[a]);
             }
-            j = 1 + a * kWave + nth_bit(mark[a], i - 1 - before[a]);
-        }
-        is = cfr_path(A, j, r, nk, p);
-        step = cd_cycles(df * p.tau);
-    };
-    bool have = false;
-    for (uint32_t g = blockIdx.y; g < groups; g += gridDim.y) {
-        const uint32_t n0 = (g * runs + lane / lanes) * kCfrRun;
-        double acc[kSums];
-#pragma unroll
-        for (uint32_t i = 0; i < kSums; ++i) acc[i] = 0.0;
-        for (uint32_t i = lo + lane % lanes; i < hi; i += lanes) {
-            if (!have) {
-                path(i);
-                have = once;
-            }
-            if (!is) continue;  // (no line of sight)
-            cd e = cd_cycles(-cfr_df(n0, N, bw) * p.tau);
-#pragma unroll
-            for (uint32_t k = 0; k < kCfrRun; ++k) cfr_add(p, step, acc + 4 * k, e);
-        }
-        for (uint32_t o = lanes / 2; o > 0; o >>= 1)
-#pragma unroll
-            for (uint32_t i = 0; i < kSums; ++i) acc[i] += __shfl_xor(acc[i], (int)o, kWave);
-        if (lane % lanes == 0)
-#pragma unroll
-            for (uint32_t i = 0; i < kSums; ++i) red[wv][lane / lanes][i] = acc[i];
-        __syncthreads();
-        const uint32_t n = g * runs * kCfrRun + threadIdx.x / 4;
-        if (threadIdx.x < runs * kSums && n < N) {
-            double v = 0.0;
-            for (uint32_t k = 0; k < kCfrRanges; ++k) v += (&red[k][0][0])[threadIdx.x];
-            cfr[((size_t)r * N + n) * 4 + threadIdx.x % 4] = v;
+            Listed l{};  // (no line of sight: nothing is added)
+            if (cfr_path(A, j, r, nk, l.p)) l.step = cd_cycles(df * l.p.tau);
+            else l.p = CfrPath{};
+            list[i] = l;
         }
         __syncthreads();
+        for (uint32_t t = blockIdx.y * kCfrListWaves + wv; t < n_tiles; t += gridDim.y * kCfrListWaves) {
+            const uint32_t n0 = t * kCfrTile + lane / kSums * kCfrRun;
+            const double f0 = -cfr_df(n0, N, bw);
+            double acc[kSums];
+#pragma unroll
+            for (uint32_t k = 0; k < kSums; ++k) acc[k] = 0.0;
+            for (uint32_t i = sub; i < n; i += kSums) {
+                const Listed &l = list[i];
+                const cd step = l.step;
+                cd e = cd_cycles(f0 * l.p.tau);
+#pragma unroll
+                for (uint32_t k = 0; k < kCfrRun; ++k) cfr_add(l.p, step, acc + 4 * k, e);
+            }
+#pragma unroll
+            for (uint32_t o = kSums / 2; o > 0; o >>= 1) {
+                const bool up = lane & o;
+#pragma unroll
+                for (uint32_t k = 0; k < o; ++k) {
+                    const double keep = up ? acc[o + k] : acc[k], give = up ? acc[k] : acc[o + k];
+                    acc[k] = keep + __shfl_xor(give, (int)o, kWave);
+                }
+            }
+            if (n0 + sub / 4 < N) {
+                double *out = cfr + ((size_t)r * N + n0) * 4 + sub;
+                *out = i0 ? *out + acc[0] : acc[0];
+            }
+        }
+        __syncthreads();  // the list is written again
     }
+}
+
+// Records (rays x interactions) of a short list: a receiver's paths are among them, the keys, of which there are
+// no more than records, and the line of sight. By the recording alone, so that a receiver's sums have one order. 500 records,
+// 1 receiver, 1 sample: 22 us with the list, 13.6 without; 256 records 16.0 and 12.9, 100 records 13.4 and 12.8.
+constexpr uint32_t kCfrFew = 128, kCfrFewWords = 2 * kCfrFew / kWave;
+
+// Ranges of a long list: 52 of the records each and some keys, since a lane has a path of a range then, and a range's
+// cost is that of full lanes and a tree of 64 sums however few paths it has. With the wavefronts below, 16 ranges
+// before: 300 rays x 1, 500 receivers, 700 samples 912 -> 478 us; 250 x 2, 300 receivers, 700 samples 645 -> 421.
+static uint32_t cfr_ranges(uint64_t records) {
+    return (uint32_t)std::min<uint64_t>(kCfrRanges, (records + 51) / 52);
 }
 
 // Samples of a block: the more, the less a path is evaluated again, and the fewer blocks there are. 4 while those
 // are no more than the compute units, 8 while blocks of 8 are not, then 16. 12 000 rays, 12 receivers, us with 4 / 8 / 16:
 // 17 samples 75 / 91 / 151, 129: 159 / 99 / 151, 300: 302 / 185 / 152, 4 001: 3 424 / 2 147 / 1 804; 6 000 rays, 1 receiver: 1 000
-// samples 50 / 56 / 88, 2 000: 94 / 60 / 88, 4 001: 173 / 107 / 88. (A response's bits are the same with each.)
-void launch_tape_cfr(const LaunchArgs &A, double bw, uint32_t N, double *cfr, hipStream_t s) {
+// samples 50 / 56 / 88, 2 000: 94 / 60 / 88, 4 001: 173 / 107 / 88. No more than there are samples: 1 000 rays x 2, 1 000
+// receivers, 1 sample 55 us with 4, 104 with 16. Wavefronts: no more than ranges; 16 samples (189 registers, eight
+// wavefronts per compute unit) take four where two such blocks per compute unit are there, so one can be in its tree
+// while the other adds: 12 000 x 2, 12 receivers, 4 001 samples 1 804 -> 1 653 us; eight below: 6 000 x 2, 6 receivers, 700
+// samples, 164. (A response's bits are the same with each.)
+void launch_tape_cfr(const LaunchArgs &A, uint32_t n_rays, double bw, uint32_t N, double *cfr, hipStream_t s) {
     static const uint32_t cus = compute_units();
-    const uint32_t n_rx = A.D.n_rx;
-    if (!(A.flags & 4) && A.D.rec_keys <= kCfrWords * kWave) {
-        const uint32_t g = std::max(1u, std::min((N + 15) / 16, cus / n_rx));
-        hipLaunchKernelGGL(k_tape_cfr_spec, dim3(n_rx, g), dim3(kCfrRanges * kWave), 0, s, A, bw, N, cfr);
+    const uint32_t n_rx = A.D.n_rx, records = n_rays * A.D.K, nd = (A.flags & 4) ? records : 0;
+    const bool few = records <= kCfrFew;
+    if (few || (!(A.flags & 4) && A.D.rec_keys <= kCfrWords * kWave)) {
+        auto *k = few ? k_tape_cfr_list<kCfrFewWords> : k_tape_cfr_list<kCfrWords>;
+        static const uint32_t cap[2] = {resident_blocks((const void *)k_tape_cfr_list<kCfrWords>, kCfrListWaves * kWave),
+                                        resident_blocks((const void *)k_tape_cfr_list<kCfrFewWords>, kCfrListWaves * kWave)};
+        const uint32_t per_block = kCfrTile * kCfrListWaves;
+        const uint32_t g = std::max(1u, std::min((N + per_block - 1) / per_block, cap[few] / n_rx));
+        hipLaunchKernelGGL(k, dim3(n_rx, g), dim3(kCfrListWaves * kWave), 0, s, A, nd, bw, N, cfr);
         return;
     }
     auto blocks = [&](uint32_t f) { return (uint64_t)n_rx * ((N + f - 1) / f); };
-    const uint32_t f = blocks(4) <= cus ? 4 : blocks(8) <= cus ? 8 : 16;
+    const uint32_t f = N <= 4 || blocks(4) <= cus ? 4 : N <= 8 || blocks(8) <= cus ? 8 : 16;
     auto *k = f == 4 ? k_tape_cfr<4, 16> : f == 8 ? k_tape_cfr<8, 16> : k_tape_cfr<16, 8>;
-    hipLaunchKernelGGL(k, dim3(n_rx, (N + f - 1) / f), dim3((f == 16 ? 8 : 16) * kWave), 0, s, A, bw, N, cfr);
+    const uint32_t ranges = cfr_ranges(records), waves = std::min(f < 16 ? 16u : blocks(16) < 2 * cus ? 8u : 4u, ranges);
+    hipLaunchKernelGGL(k, dim3(n_rx, (N + f - 1) / f), dim3(waves * kWave), 0, s, A, nd, bw, N, ranges, cfr);
 }
 
 // dL/da_p (as gR + j gI per polarisation) of one path from dL/dH_r:

@@ -289,3 +289,47 @@ def test_cfr_of_few_paths_and_many_samples_shares_the_lanes(env):
             best = min(best, e[0].elapsed_time(e[1]) / 8)
         ms.append(best)
     assert ms[1] < 5 * ms[0], ms
+
+
+@pytest.mark.parametrize("rays,K", [(1, 1), (64, 2), (65, 2), (128, 1), (129, 1), (16, 8), (17, 8), (200, 2), (416, 2), (417, 2)])
+def test_cfr_of_few_rays_at_many_receivers(env, orc, rays, K):
+    """Up to 128 records the paths are listed, beyond them in ranges of 52 records: against the oracle (the bar of
+    test_cfr_matches_oracle), and a receiver's numbers are the same bits alone, at every sample count and among 600."""
+    torch, P, diff, s, sg, rx3 = env
+    mats = _mats(7, 0.3)
+    rx = np.random.default_rng(rays).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (600, 3)).astype(np.float32)
+    rx[:3] = rx3
+    many = diff.record(sg, mats, scenes.BOX_TX, rx, FC, rays, K=K, flags=LOS | SPEC | DIFF)
+    few = diff.record(sg, mats, scenes.BOX_TX, rx3, FC, rays, K=K, flags=LOS | SPEC | DIFF)
+    for rec in (many, few):
+        P.tape_fresnel(rec, mats)
+    ref = orc.solve(s, mats, scenes.BOX_TX, rx3, FC, rays, K=K, flags=LOS | SPEC | DIFF, cfr=(BW, 17)).cfr
+    for n in (1, 4, 5, 8, 9, 16, 17, 65, 129, 700):
+        a, b = P.tape_cfr(many, BW, n), P.tape_cfr(few, BW, n)
+        assert torch.equal(a[:3], b), n
+        if n == 17:
+            for r in range(3):
+                assert np.abs(b[r].cpu().numpy() - ref[r]).max() <= 5e-4 * np.abs(ref[r]).max(), r
+
+
+def test_cfr_of_few_rays_at_many_receivers_costs_by_the_path(env):
+    """20 records at 3 000 receivers and 2 000 at 300, 700 samples: a tenth of the paths takes less time (a twelfth; it
+    took three times as long where every receiver's few paths were spread over a block of 16 ranges)."""
+    torch, P, diff, s, sg, _ = env
+    rx = np.random.default_rng(1).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (3000, 3)).astype(np.float32)
+    ms = []
+    for rays, n_rx in ((10, 3000), (1000, 300)):
+        rec = diff.record(sg, _mats(7, 0.3), scenes.BOX_TX, rx[:n_rx], FC, rays, K=2, flags=LOS | SPEC | DIFF)
+        P.tape_fresnel(rec, _mats(7, 0.3))
+        P.tape_cfr(rec, BW, 700)
+        best = 1e9
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            P.tape_cfr(rec, BW, 700)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        ms.append(best)
+        del rec
+    assert ms[0] < ms[1], ms
