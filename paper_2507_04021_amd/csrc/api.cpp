@@ -349,6 +349,7 @@ LaunchArgs make_args(const pcrt_scene *sc, const pcrt_material *mats, uint32_t n
     A.spec_hid = (p->flags & PCRT_SPECULAR) ? (int *)at(L.spec_hid) : nullptr;
     A.spec_ovr = ((p->flags & PCRT_SPECULAR) && (p->flags & PCRT_AVERAGE)) ? (float4 *)at(L.spec_ovr) : nullptr;
     A.diff_part = (double *)at(L.diff_part);
+    A.refine_waves = refine_grid(P.D);
     A.diff_parts = diffuse_parts(P.D);
     A.vis_bits = (uint32_t *)at(L.vis_bits);
     A.spec_split = (float4 *)at(L.spec_split);
@@ -395,7 +396,7 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
     L.rec_cs = b.take(sizeof(float) * nrec);
     if (flags & PCRT_AVERAGE) L.rec_nk = b.take(sizeof(float4) * nrec);
     L.key_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
-    L.chunk_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
+    L.chunk_off = b.take(sizeof(uint32_t) * (D.n_items + 2));
     L.los_part = b.take(sizeof(double) * 5 * (size_t)D.n_items * D.n_rx);
     if (diff) {
         L.dkey0 = b.take(sizeof(uint64_t) * nrec);
@@ -416,7 +417,7 @@ SolveLayout solve_layout(const SolveDims &D, uint32_t flags) {
             L.dhrep = b.take(sizeof(uint32_t) * cap);
             L.dkeylist = b.take(sizeof(uint32_t) * nrec);
             L.dkey_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
-            L.dchunk_off = b.take(sizeof(uint32_t) * (D.n_items + 1));
+            L.dchunk_off = b.take(sizeof(uint32_t) * (D.n_items + 2));
             L.dcnt = b.take(sizeof(uint64_t) * PCRT_CNT_COUNT);
             L.vis_words = b.take(sizeof(uint64_t) * D.n_sets * ((D.n_rx + kWave - 1) / kWave));
             if (!spec) {  // the compaction's scan buffers

@@ -612,15 +612,14 @@ __global__ __launch_bounds__(kWave) void k_los(LaunchArgs A) {
 // diffuse chunks. Lane t sums chunks t, t+256, ... in order; the lanes are
 // then combined by a fixed pairwise tree, so the result is bitwise repeatable.
 __global__ __launch_bounds__(256) void k_combine(LaunchArgs A, double *gain, double *h_te, double *h_tm,
-                                                 double *parts, uint32_t refine_wavefronts) {
+                                                 double *parts, bool solved) {
     __shared__ double red[256][10];
     const uint32_t p = blockIdx.x;
     const uint32_t it = p / A.D.n_rx, r = p % A.D.n_rx;
     const uint32_t n_rx = A.D.n_rx;
     const int t = threadIdx.x;
     double sp[5] = {0, 0, 0, 0, 0}, df[5] = {0, 0, 0, 0, 0};
-    if ((A.flags & 2) && refine_wavefronts &&
-        refine_shape(A.chunk_off[A.D.n_items], n_rx, refine_wavefronts).parts > 1) {
+    if ((A.flags & 2) && solved && planned_refine(A).parts > 1) {
         // refined in parts: a chunk's paths in key order, as the refinement adds them otherwise
         for (uint32_t c = A.chunk_off[it] + t; c < A.chunk_off[it + 1]; c += 256) {
             const size_t v = (size_t)c * n_rx + r;
@@ -695,8 +694,7 @@ void launch_los_and_combine(const LaunchArgs &A, double *gain, double *h_te, dou
 void launch_combine(const LaunchArgs &A, double *gain, double *h_te, double *h_tm, double *parts, bool solved,
                     hipStream_t s) {
     const uint32_t n = A.D.n_items * A.D.n_rx;
-    hipLaunchKernelGGL(k_combine, dim3(n), dim3(256), 0, s, A, gain, h_te, h_tm, parts,
-                       solved ? refine_grid(A.D) : 0u);
+    hipLaunchKernelGGL(k_combine, dim3(n), dim3(256), 0, s, A, gain, h_te, h_tm, parts, solved);
 }
 
 }  // namespace pcrt

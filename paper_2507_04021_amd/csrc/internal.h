@@ -140,15 +140,23 @@ constexpr uint32_t kRefineResPerBlock = 2 * kKeyChunk * kRefineRxSlice;
 // receivers, 28 858 candidates (a quarter of the wavefront-time used without
 // parts): 1 / 2 / 4 / 8 parts 0.81 / 0.70 / 0.70 / 0.69 ms; 53 keys, 1
 // receiver: 67 / 54 / 58 / 87 us. What is left is the longest candidate's chain.
+// A unit of few keys, all of whose pairs are one tile already, is halved only while
+// there are fewer than a quarter of the wavefronts: beyond that it gives lanes without pairs, and
+// more units than wavefronts ask one counter. 6 keys x 2 000 / 4 096 receivers, whole
+// call: halved to the end 220 / 267 us, up to the wavefronts 218 / 174, to a quarter 141 / 154.
 constexpr uint32_t kRefineMaxParts = 4;
 struct RefineShape {
     uint32_t slice, parts;
 };
-__device__ __forceinline__ RefineShape refine_shape(uint64_t n_chunks, uint32_t n_rx, uint32_t grid) {
+__device__ __forceinline__ RefineShape refine_shape(uint64_t n_chunks, uint32_t n_keys, uint32_t n_rx, uint32_t grid) {
     RefineShape s{kRefineRxSlice, 1};
-    while (s.slice > 1 && n_chunks * ((n_rx + s.slice - 1) / s.slice) < grid) s.slice >>= 1;
+    auto units = [&](uint32_t slice, uint32_t parts) { return n_chunks * ((n_rx + slice - 1) / slice) * parts; };
+    while (s.slice > 1 && units(s.slice, 1) < grid) {
+        if ((uint64_t)n_keys * s.slice <= n_chunks * kWave && units(s.slice, 1) * 4 > grid) return s;
+        s.slice >>= 1;
+    }
     if (s.slice == 1)
-        while (s.parts < kRefineMaxParts && n_chunks * n_rx * s.parts < grid) s.parts <<= 1;
+        while (s.parts < kRefineMaxParts && units(1, s.parts) < grid) s.parts <<= 1;
     return s;
 }
 constexpr uint32_t kRefineQueue = 128;  // refinement ring of queued candidates (at most 127 are queued)
@@ -218,6 +226,7 @@ struct LaunchArgs {
     int *spec_hid;         // refinement: per block, interaction and lane, the validated disk of the lane's candidate
     float4 *spec_ovr;      // refinement with point-set averaging: per lane and interaction, the replaced plane
     double *diff_part;
+    uint32_t refine_waves; // refinement: its wavefronts
     uint32_t diff_parts;   // diffuse: parts a (chunk, receiver) unit is walked in
     uint32_t *vis_bits;    // ... and the visible connections of units walked in parts, a bit per record
     float4 *spec_split;    // refinement in parts: the paths' amplitudes, [key chunk][n_rx][kKeyChunk]
@@ -232,6 +241,16 @@ struct LaunchArgs {
     double *grad_part;     // [n_slot_chunks][kMaxGradLabels][3]
     SortBufs dsort;
 };
+
+// The refinement's shape, formed once with the key list and kept behind its chunk offsets.
+__device__ __forceinline__ void plan_refine(const LaunchArgs &A, uint32_t n_keys, uint32_t n_chunks) {
+    const RefineShape s = refine_shape(n_chunks, n_keys, A.D.n_rx, A.refine_waves);
+    A.chunk_off[A.D.n_items + 1] = s.slice | s.parts << 16;
+}
+__device__ __forceinline__ RefineShape planned_refine(const LaunchArgs &A) {
+    const uint32_t v = A.chunk_off[A.D.n_items + 1];
+    return {v & 0xffffu, v >> 16};
+}
 
 // Voxel diffuse keys of the reception-point launch: block c of n_blocks (the
 // ray chunks) takes an equal share of the n_keys keys, in key order, and each

@@ -204,9 +204,9 @@ __device__ __forceinline__ void path_field(const LaunchArgs &A, uint32_t q, uint
 }
 
 // Persistent single-wavefront blocks. A work unit is (key chunk, slice of up
-// to kRefineRxSlice receivers, fewer where units are scarce); units are handed
-// out by an atomic counter, slice-minor so that consecutive units reuse a
-// chunk's key planes.
+// to kRefineRxSlice receivers, fewer where units are scarce); units are dealt
+// where each wavefront has one, else handed out by an atomic counter (11 ns for each
+// who asks), slice-minor so that consecutive units reuse a chunk's key planes.
 //
 // The wavefront deals a unit's (key, receiver) pairs to its lanes in tiles
 // of 64 and solves the image method for each pair (cheap, no traversal);
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
     float4 *pl_g = AVG ? A.spec_ovr + (size_t)glane * KM * 2 : nullptr;
     const uint32_t n_rx = A.D.n_rx, n_items = A.D.n_items;
     const uint32_t n_chunks = A.chunk_off[n_items];
-    const RefineShape shape = refine_shape(n_chunks, n_rx, gridDim.x);
+    const RefineShape shape = planned_refine(A);
     const uint32_t slice = shape.slice, parts = shape.parts, part_keys = kKeyChunk / parts;
     const uint32_t n_slices = (n_rx + slice - 1) / slice;
     const uint32_t n_units = n_chunks * n_slices * parts;
@@ -461,12 +461,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ?
 #pragma unroll
                 for (int k = 0; k < kRefineOpen; ++k) {
                     if (s >= 0 || U[k].open || exhausted || (k && one_open)) continue;
-                    uint32_t u = 0;
-                    if (lane == 0) u = atomicAdd(&A.work[1], 1u);
-                    u = __builtin_amdgcn_readfirstlane(u);
-                    if (u >= n_units) {
+                    uint32_t u = blockIdx.x;
+                    if (n_units <= gridDim.x) {  // dealt
                         exhausted = true;
-                        continue;
+                    } else {
+                        if (lane == 0) u = atomicAdd(&A.work[1], 1u);
+                        u = __builtin_amdgcn_readfirstlane(u);
+                        if (u >= n_units) {
+                            exhausted = true;
+                            continue;
+                        }
                     }
                     const uint32_t part = u % parts, cs = u / parts, c = cs / n_slices;
                     int lo = 0, hi = (int)n_items - 1;  // item of this chunk

@@ -85,6 +85,7 @@ __global__ void k_plan(LaunchArgs A, const uint32_t *total) {
     if (threadIdx.x == 1023) {
         A.chunk_off[n_items] = chunks[1023];
         A.key_off[n_items] = *total;
+        plan_refine(A, *total, chunks[1023]);
         A.counters[3] = *total;
     }
 }
@@ -126,6 +127,7 @@ __global__ __launch_bounds__(256) void k_keys_table(LaunchArgs A) {
         A.key_off[0] = A.chunk_off[0] = 0;
         A.key_off[1] = n;
         A.chunk_off[1] = (n + kKeyChunk - 1) / kKeyChunk;
+        plan_refine(A, n, A.chunk_off[1]);
         A.counters[3] = n;
     }
 }
@@ -162,6 +164,7 @@ __global__ __launch_bounds__(1024) void k_plan_counts(LaunchArgs A) {
     if (threadIdx.x == 1023) {
         A.key_off[n_items] = keys[1023];
         A.chunk_off[n_items] = chunks[1023];
+        plan_refine(A, keys[1023], chunks[1023]);
         A.counters[3] = keys[1023];
     }
 }

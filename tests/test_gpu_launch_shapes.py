@@ -325,3 +325,44 @@ def test_connections_of_few_chunks_do_not_change_a_receiver(P, office, n_rx, ray
     assert part.counter("diffuse") > 0 or n_rx == 1
     for a, b in ((part.gain, full.gain), (part.h_te, full.h_te), (part.parts, full.parts)):
         assert np.array_equal(a.cpu().numpy(), b.cpu().numpy()[:n_rx])
+
+
+@pytest.mark.parametrize("n_rx", [1, 95, 96, 97, 383, 384, 385, 767, 768, 769, 3000, 6143, 6144, 6145, 30_000])
+@pytest.mark.parametrize("pol", [None, ((1.0, 0.2, -0.3), (0.1, -1.0, 0.4))])
+def test_few_keys_at_many_receivers(P, room, n_rx, pol):
+    """A handful of keys: units of 1 to 8 receivers, in parts, dealt or from the counter by how many there are (3 072
+    wavefronts). A receiver's numbers are those of a call with 50 receivers."""
+    rng = np.random.default_rng(11)
+    rx = rng.uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (n_rx, 3)).astype(np.float32)
+    mats = scenes.box_room_materials()
+    print("[gpu-test] few keys, %d receivers" % n_rx, flush=True)
+    r = P.solve(room[1], mats, scenes.BOX_TX, rx, 3.5e9, 4096, K=1, flags=SPEC, pol=pol)
+    assert 0 < r.counter("keys") <= 8 and r.counter("specular") > n_rx
+    for lo in sorted({0, max(0, n_rx // 2 - 25), max(0, n_rx - 50)}):
+        p = P.solve(room[1], mats, scenes.BOX_TX, rx[lo:lo + 50], 3.5e9, 4096, K=1, flags=SPEC, pol=pol)
+        for a, b in ((r.gain, p.gain), (r.h_te, p.h_te), (r.h_tm, p.h_tm), (r.parts, p.parts)):
+            assert np.array_equal(a.cpu().numpy()[lo:lo + 50], b.cpu().numpy())
+
+
+def test_few_keys_at_many_receivers_do_not_wait_for_a_counter(P, room):
+    """4 096 receivers of six keys take about as long as 300 (1.2 times the whole call; twice where every receiver is a unit
+    of its own and all wavefronts ask one counter)."""
+    import time
+    import torch
+    mats = P.materials_tensor(scenes.box_room_materials())
+    ms = []
+    for n in (300, 4096):
+        rx = torch.as_tensor(np.random.default_rng(n).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (n, 3)).astype(np.float32),
+                             device="cuda")
+        f = lambda: P.solve(room[1], mats, scenes.BOX_TX, rx, 3.5e9, 4096, K=1, flags=SPEC)
+        f()
+        t = []
+        for _ in range(30):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(4):
+                f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        ms.append(min(t))
+    assert ms[1] < 1.6 * ms[0], ms
