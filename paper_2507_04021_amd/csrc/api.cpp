@@ -600,8 +600,8 @@ static size_t visibility_spill_bytes(const pcrt_scene *sc) {
     const uint32_t depth = sc->info.stack_entries > (uint32_t)kStackLdsVisibility ? sc->info.stack_entries - kStackLdsVisibility : 0;
     return sizeof(int) * (size_t)depth * visibility_grid(sc->info.width) * kWave;
 }
-// then a counter of work units per XCD (64 B each)
-static size_t visibility_ws(const pcrt_scene *sc) { return visibility_spill_bytes(sc) + 64 * kXcds; }
+// then the counters of work units
+static size_t visibility_ws(const pcrt_scene *sc) { return visibility_spill_bytes(sc) + 128 * kVisGroups; }
 
 pcrt_status pcrt_visibility_workspace_size(const pcrt_scene *scene, size_t *bytes) {
     if (!scene || !bytes) return fail(PCRT_EINVAL, "scene and bytes are required");

@@ -65,6 +65,7 @@ void launch_diffraction(const DevScene &S, const pcrt_edge *edges, uint32_t n_ed
                         uint32_t n_labels, const float tx[3], const float *rx, uint32_t n_rx, double freq,
                         float eps_self, float4 *amp, double *out, hipStream_t s);
 // Visibility of the point sets' reception points from receivers (one uint8 per pair).
+constexpr uint32_t kVisGroups = 32;  // visibility: groups of wavefronts with a range and a counter of units (128 B apart) each
 uint32_t visibility_grid(uint32_t width);
 void launch_visibility(const DevScene &S, const float *rx, uint32_t n_rx, const float4 *recv, uint32_t n_sets,
                        float eps_self, uint8_t *out, uint32_t *taken, hipStream_t s);

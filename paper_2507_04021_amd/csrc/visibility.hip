@@ -16,11 +16,15 @@
 // on the schedule. Persistent single-wavefront blocks; the blocks of XCD x
 // take the x-th eighth of the (set chunk, receiver) units, receiver-minor, so
 // one XCD's L2 serves one region of the scene, each unit from a counter per
-// XCD (`taken`): walks of one unit take several times as long as another's,
+// group, a quarter of an XCD's blocks (`taken`): walks of one unit take several times as long as another's,
 // and dealt in advance, with a drain at the end of each of its one or two units,
 // the slowest wavefront set the time. On the office's 64 x 181 523 matrix: 2.65 ms
 // with one 64-set batch per unit and no refill, 2.2 ms with refill over
 // 1024-set units dealt in advance, 1.63 ms so, 1.52 with 20 stack entries in LDS.
+// An atomic on one line costs 11 ns, so short walks wait for their counter: 10 671 sets x 500 receivers of the
+// empty room 119 us with one counter per XCD, 69 with four (68 with eight). Up to two units per wavefront are dealt, with no
+// counter and no launch to clear it: 10 sets x 10 000 receivers 36 -> 16 us, one receiver of 10 671 sets 20 -> 15,
+// and 500 of 2 502 sets of the office, 1.6 units per wavefront, 209 -> 192.
 #include "common.h"
 #include "internal.h"
 
@@ -39,9 +43,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
     const uint32_t glane = blockIdx.x * kWave + lane;
     StackOf<kStackLdsVisibility> stk{lds_stack + lane, S.spill + glane, S.spill_lanes};
     const uint32_t n_units = (n_sets + kVisChunk - 1) / kVisChunk * n_rx;
-    const uint32_t xcd = blockIdx.x % kXcds, nb = gridDim.x / kXcds;
-    const uint32_t end = n_units > xcd * share ? min(share, n_units - xcd * share) : 0;  // units of this XCD
-    uint32_t t = blockIdx.x / kXcds - nb;   // lane 0: the unit to take next, less nb (the first of each wavefront are dealt)
+    // group g's range is the one of XCD g / (groups per XCD)
+    const uint32_t i = blockIdx.x % kVisGroups, g = i % kXcds * (kVisGroups / kXcds) + i / kXcds, nb = gridDim.x / kVisGroups;
+    const uint32_t u0 = g * share, end = n_units > u0 ? min(share, n_units - u0) : 0;  // units of this group
+    uint32_t t = blockIdx.x / kVisGroups - nb;   // lane 0: the unit to take next, less nb (the first of each wavefront are dealt)
     uint32_t next = 0, j1 = 0, r = 0;       // the current unit's next and last set, its receiver (wave-uniform)
     bool walking = false, hit = false;
     f3 a = mk(0.f, 0.f, 0.f);
@@ -56,11 +61,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(W == 8 ? 
             if (next >= j1) {  // the unit is handed out: the next one
                 const uint32_t k = nb + __builtin_amdgcn_readfirstlane(t);
                 if (k >= end) break;
-                const uint32_t u = xcd * share + k, c = u / n_rx;
+                const uint32_t u = u0 + k, c = u / n_rx;
                 r = u % n_rx;
                 next = c * kVisChunk;
                 j1 = min(n_sets, next + kVisChunk);
-                if (lane == 0) t = atomicAdd(&taken[16 * xcd], 1u);  // (used at the next unit: no wait here)
+                if (lane == 0) t = taken ? atomicAdd(&taken[32 * g], 1u) : t + nb;  // (used at the next unit: no wait here)
             }
             const uint32_t avail = min(j1 - next, (uint32_t)__popcll(idle));
             if (!walking && mbcnt(idle) < avail) {
@@ -136,15 +141,16 @@ uint32_t visibility_cap() {
 
 uint32_t visibility_grid(uint32_t width) {
     const uint32_t cap = width == 8 ? visibility_cap<8>() : width == 4 ? visibility_cap<4>() : visibility_cap<2>();
-    return std::max<uint32_t>(kXcds, cap / kXcds * kXcds);  // a multiple of the XCD count
+    return std::max<uint32_t>(kVisGroups, cap / kVisGroups * kVisGroups);
 }
 
 void launch_visibility(const DevScene &S, const float *rx, uint32_t n_rx, const float4 *recv, uint32_t n_sets,
                        float eps_self, uint8_t *out, uint32_t *taken, hipStream_t s) {
-    fill_u32(taken, 0, 16 * kXcds, s);
     const uint32_t grid = visibility_grid((uint32_t)S.width);
     const uint32_t n_units = (n_sets + kVisChunk - 1) / kVisChunk * n_rx;
-    const uint32_t share = (n_units + kXcds - 1) / kXcds;
+    const uint32_t share = (n_units + kVisGroups - 1) / kVisGroups;
+    if (share <= 2 * (grid / kVisGroups)) taken = nullptr;  // one or two units per wavefront: dealt
+    else fill_u32(taken, 0, 32 * kVisGroups, s);
     switch (S.width) {
         case 8: hipLaunchKernelGGL(k_visibility<8>, dim3(grid), dim3(kWave), 0, s, S, rx, n_rx, recv, n_sets, eps_self,
                                    out, share, taken); break;

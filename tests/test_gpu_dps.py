@@ -246,6 +246,41 @@ def test_visibility_matrix_parity(P, orc, room):
             assert np.array_equal(v, base)
 
 
+@pytest.mark.parametrize("rho,sizes", [(RHO, (1, 5, 200, 383, 384, 385, 768, 769, 2000)),
+                                       (20.0, (1, 64, 6143, 6145, 12_287, 12_289, 40_000))])
+def test_visibility_of_many_receivers(P, room, rho, sizes):
+    """One or two units per wavefront are dealt, more come from counters, each group of wavefronts its own (6 144
+    wavefronts, 32 groups): a receiver's row is the one it has alone with 40 others."""
+    sg = P.Scene.from_scene(room, dps_voxel=rho)
+    lo, hi = room.pos.min(0) + 0.1, room.pos.max(0) - 0.1
+    rx = np.random.default_rng(7).uniform(lo, hi, (max(sizes), 3)).astype(np.float32)
+    for n in sizes:
+        step("visibility rho=%g rx=%d" % (rho, n))
+        v = P.visibility(sg, rx[:n]).cpu().numpy()
+        for a in sorted({0, max(0, n // 2 - 20), max(0, n - 40)}):
+            assert np.array_equal(v[a:a + 40], P.visibility(sg, rx[a:min(n, a + 40)]).cpu().numpy()), (n, a)
+
+
+def test_visibility_of_short_walks_does_not_wait_for_a_counter(P):
+    """10 671 sets of an empty room and 2 000 receivers, every walk a few nodes: less than 16 ps per pair (11; 20 with a
+    counter per die, 13.5 before there were counters)."""
+    import torch
+    sg = P.Scene.from_scene(scenes.box_room(spacing=0.1, radius=0.08), dps_voxel=0.06)
+    rx = torch.as_tensor(np.random.default_rng(1).uniform((0.3, 0.3, 0.3), (5.7, 3.7, 2.7), (2000, 3)).astype(np.float32),
+                         device="cuda")
+    step("visibility of short walks")
+    best = 1e9
+    for _ in range(10):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(4):
+            P.visibility(sg, rx)
+        e[1].record()
+        torch.cuda.synchronize()
+        best = min(best, e[0].elapsed_time(e[1]) / 4)
+    assert best * 1e9 < 16 * 2000 * sg.info["n_point_sets"], best
+
+
 def test_visibility_errors(P, room):
     step("visibility errors")
     sg = P.Scene.from_scene(room)
