@@ -266,8 +266,10 @@ __device__ __forceinline__ void block_sync_global() {
 
 // POL: the polarised field (its own instances, so that the scalar ones keep
 // their register allocation). Three wavefronts per SIMD up to K = 5 (168
-// registers: none spilled up to K = 4, about 100 at K = 5): two gave 3.7 ms on
-// the office (no spills), four 3.2 (247 spilled), three 3.06.
+// registers: up to 42 spilled up to K = 4, 111 to 141 at K = 5): at K = 5, two (none spilled) take 0.4 ms
+// more of the office's 27.1, 0.1 of its polarised solve's 3.15, 0.06 of the averaged one's 2.53, though less where most
+// candidates are paths (empty room, 3 000 receivers 2.23 -> 2.10); four took 3.2 ms of the office (247 spilled) where
+// three took 3.06.
 template <int KM, int W, bool AVG, bool POL>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(KM <= 5 ? 3 : 2, 8))) void k_refine(
     LaunchArgs A) {
